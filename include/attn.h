@@ -7,8 +7,10 @@
  * Sq x Skv score matrix is never stored.  Causal masking and grouped-query
  * heads follow the benchmark configurations of sections 4.1 and 4.3.
  *
- * All pointers are DEVICE pointers owned by the caller.  The library holds no
- * device memory, allocates nothing, never synchronises and never throws.
+ * All pointers are DEVICE pointers owned by the caller.  The library allocates
+ * nothing, never synchronises and never throws; its code object brings 64 MiB
+ * of device memory for partial results, which launches share out among
+ * themselves on the device.
  */
 #ifndef PAPER_2603_24517_ATTN_H
 #define PAPER_2603_24517_ATTN_H
@@ -54,15 +56,21 @@ enum {
  * Size limits (ATTN_E_UNSUPPORTED beyond them): Sq + Skv below 2^31 - 1024,
  * Hq and Hkv at most 32768, and fewer than 2^27 work items, one item being 256/p query rows of p query
  * heads that share a K/V head (p = 8, 4, 2 or 1, the largest that divides
- * Hq / Hkv).  The launch is one kernel: with one workgroup per compute unit of
+ * Hq / Hkv).  The launch is one kernel, with one workgroup per compute unit of
  * the current device (all of its LDS), each working through a list of such
  * items -- or, when those items would occupy at most a quarter of the compute
- * units (few query rows, however long the key sequence), with one workgroup per
+ * units or hold at most 64 rows each, one with one workgroup per
  * 32 query rows that share a K/V head (p heads x 32/p positions), whose
- * wavefronts share the item's keys and merge their partial results through LDS.  Either way nothing is allocated.
+ * wavefronts share the item's keys and merge their partial results through LDS.
+ * Where these are fewer than the compute units and the key sequence is long,
+ * several workgroups share an item's keys; the launch is then preceded by one of a
+ * single workgroup, which takes the device memory that the partial results pass
+ * through.  Any number of threads and streams may do so at a time: a launch
+ * that finds the memory in use goes without it, which is slower, and rounds
+ * differently in the last bits.  Nothing is allocated in any case.
  * The first call on a device queries the device once and sets function
  * attributes, so make one ordinary call on a device before recording attn_fwd
- * into a HIP graph (later calls are one kernel launch and nothing else, and
+ * into a HIP graph (later calls are one or two kernel launches and nothing else, and
  * replay correctly).
  *
  * Inputs and outputs must not overlap and must stay alive until the stream

@@ -34,6 +34,8 @@ VARIANTS = {
     # every launch through the 256-row kernel / every launch through the split-key kernel for small problems
     "no_small_path": ["-DATTN_SMALL_PATH=0"],
     "always_small_path": ["-DATTN_SMALL_PATH=2"],
+    # the split-key kernel without its pool for partial results (what a launch does that finds the pool in use)
+    "no_pool": ["-DATTN_POOL=0"],
     "lds_prefetch_1": ["-DATTN_LDS_PREFETCH=1"],
     "lds_prefetch_5": ["-DATTN_LDS_PREFETCH=5"],
     # the shipped kernel plus clock stamps of its first workgroup (exports attn_clocks_read as well)

@@ -79,9 +79,14 @@
 #endif
 // ATTN_SMALL_PATH: which launches go to the split-key kernel for small problems (at the end of this
 // file): 1 (shipped) those whose 256-row work items would occupy at most a quarter of the compute
-// units; 0 none; 2 all.
+// units and those of few query rows; 0 none; 2 all.
 #ifndef ATTN_SMALL_PATH
 #define ATTN_SMALL_PATH 1
+#endif
+// ATTN_POOL: 1 (shipped); 0 every launch of the split-key kernel that would share its items among workgroups finds the
+// pool for partial results in use, and takes the path for that case.
+#ifndef ATTN_POOL
+#define ATTN_POOL 1
 #endif
 // ATTN_LDS_PREFETCH: how many MFMAs ahead of its consumer an LDS operand fragment is read (shipped: 3).
 #ifndef ATTN_LDS_PREFETCH
@@ -1125,6 +1130,10 @@ void attn_fwd_kernel(const Params p)
 // private 16 KiB of LDS, and the eight partial results are merged through LDS at the end:
 //     M = max_w m_w,  f_w = 2^(m_w - M),  O = sum_w f_w acc_w / sum_w f_w lr_w,  LSE = ln2 (M + log2 sum_w f_w l_w).
 // No barrier inside the key loop, no workspace in device memory.
+//
+// When the items are fewer than the compute units, each item is shared by `splits` workgroups, which
+// take contiguous ranges of its key blocks.  They leave (acc, m, l, lr) in device memory and the one that arrives last
+// merges them, in the order of the ranges, whatever the order of arrival, so that the result does not depend on it.
 struct SplitParams {
     const __bf16 *q, *k, *v;
     __bf16 *o;
@@ -1134,9 +1143,76 @@ struct SplitParams {
     int chunks;             // G / pack
     int tile_pos;           // query positions per work item = 32 / pack
     int ntile;              // ceil(Sq / tile_pos)
-    Div d_ntile, d_chunks, d_hkv;   // exact division by ntile, chunks, Hkv
+    int nrest;              // B * Hkv * chunks; items = ntile * nrest
+    int splits;             // workgroups that share an item
+    int units;              // POOL_UNIT_BYTES units of device memory the launch needs, 0 if splits == 1
+    int reserve;            // 1: this launch is one workgroup that takes the units, for the launch behind it
+    Div d_nrs, d_splits, d_chunks, d_hkv;   // exact division by nrest * splits, splits, chunks, Hkv
     float c;                // scale * log2(e)
 };
+// Device memory for partial results: a part of the code object, so it exists once per device, needs no
+// allocation and no host-side bookkeeping, and goes when the library is unloaded.  A launch takes a run of
+// units and gives it back, both on the device: a one-workgroup launch in front finds a free run and
+// leaves its number in the first LSE element of every item, which is the launch's own memory and is overwritten by the
+// result only after all workgroups of the item have read it.  Launches on any number of streams, from
+// any thread and replayed from graphs thus never share units; if no run is free (the pool serves at
+// least POOL_UNITS / SPLIT_MAX_UNITS launches at a time), the first workgroup of each item takes all of its keys and
+// the others leave, which is slower but needs no memory.
+constexpr int POOL_UNITS = 64;
+constexpr uint32_t POOL_UNIT_BYTES = 1u << 20;
+constexpr uint32_t POOL_NONE = 0xffffffffu;
+__device__ unsigned long long g_pool_taken;         // bit u: unit u belongs to a launch in flight
+__device__ __attribute__((aligned(4096))) unsigned char g_pool[POOL_UNITS * POOL_UNIT_BYTES];
+constexpr int SPLIT_MAX_ITEMS = 256;                // of a launch with splits > 1 (one thread each in the reserving workgroup)
+constexpr int SPLIT_MAX_WGS = 512;                  // items * splits of such a launch
+constexpr int SPLIT_PART_BYTES = 32 * HD * 4 + 3 * 32 * 4;          // one partial result: accumulator, m, l, lr
+constexpr uint32_t SPLIT_HEADER_BYTES = 4096;       // at the start of a run: [0] finished items, [1 + item] workgroups that arrived
+constexpr int SPLIT_MAX_UNITS = (SPLIT_HEADER_BYTES + SPLIT_MAX_WGS * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES;
+static_assert((1 + SPLIT_MAX_ITEMS) * 4 <= SPLIT_HEADER_BYTES && SPLIT_MAX_ITEMS <= NTHREADS, "header holds a counter per item");
+static_assert(SPLIT_MAX_UNITS <= POOL_UNITS / 4, "several launches fit the pool");
+// The one lane that takes a run of n units: first free run, or POOL_NONE.
+__device__ inline uint32_t pool_take(int n)
+{
+    if (!ATTN_POOL) return POOL_NONE;
+    const unsigned long long run = (1ull << n) - 1;     // n < 64
+    unsigned long long taken = 0;       // (a guess that is usually right: one round trip to memory)
+    int tries = 0;
+    for (int u = 0; u + n <= POOL_UNITS;) {
+        if (taken & (run << u)) { ++u; continue; }
+        if (__hip_atomic_compare_exchange_strong(&g_pool_taken, &taken, taken | (run << u), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT))
+            return (uint32_t)u;
+        // the mask is another one, `taken` holds it now: look at u again, but not more than POOL_UNITS times in all
+        if (++tries == POOL_UNITS) break;
+    }
+    return POOL_NONE;
+}
+// Partial results pass between workgroups of one launch that may sit on different XCDs, each with an L2 of its
+// own.  They are written and read at agent scope element by element (sc1: through the L2 to memory that all
+// XCDs share), and a wait for the stores stands before the counter that announces them.  An agent-scope release
+// fence instead writes back an XCD's whole L2 for every workgroup: measured 0.17 us each, one after the other
+// (512 workgroups: 80 us).
+__device__ inline void pool_store4(unsigned char *at, float a, float b, float c, float d)
+{
+    typedef unsigned long long u64;
+    const u64 lo = (u64)__float_as_uint(a) | (u64)__float_as_uint(b) << 32, hi = (u64)__float_as_uint(c) | (u64)__float_as_uint(d) << 32;
+    __hip_atomic_store((u64 *)at, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store((u64 *)at + 1, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void pool_load4(const unsigned char *at, float *x)
+{
+    typedef unsigned long long u64;
+    const u64 lo = __hip_atomic_load((const u64 *)at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const u64 hi = __hip_atomic_load((const u64 *)at + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    x[0] = __uint_as_float((uint32_t)lo); x[1] = __uint_as_float((uint32_t)(lo >> 32));
+    x[2] = __uint_as_float((uint32_t)hi); x[3] = __uint_as_float((uint32_t)(hi >> 32));
+}
+__device__ inline void pool_store(float *at, float a) { __hip_atomic_store(at, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline float pool_load(const float *at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void pool_give(uint32_t u, int n)
+{
+    __hip_atomic_fetch_and(&g_pool_taken, ~(((1ull << n) - 1) << u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 constexpr int SPLIT_KEYS = 32;                                  // keys per block of the split kernel
 constexpr int SPLIT_TILE_BYTES = SPLIT_KEYS * ROW_BYTES;        // 8 KiB: one K or V block
 constexpr int SPLIT_WAVE_BYTES = 2 * SPLIT_TILE_BYTES;          // per wavefront: its K block, then its V block
@@ -1156,11 +1232,36 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hh = lane >> 5;
-    const int item = blockIdx.x;
+    // blockIdx.x -> (tile, rest, part), parts fastest and tiles slowest, last tile first: under the causal mask
+    // the long items start first, and where nrest * splits is a multiple of 8 the workgroups that read
+    // the same keys are on one XCD.
+    const int bid = blockIdx.x;
 #ifdef ATTN_CLOCKS
-    if (item == 0 && tid == 0) { g_clocks[2] = wall_clock64(); g_clocks[0] = __builtin_readcyclecounter(); }
+    if (bid == 0 && tid == 0) { g_clocks[2] = wall_clock64(); g_clocks[0] = __builtin_readcyclecounter(); }
 #endif
-    const int rest = fast_div(item, p.d_ntile), tile = item - rest * p.ntile;
+    // first element of an item's LSE
+    auto item_lse = [&](int rest, int q0) __attribute__((always_inline)) -> size_t {
+        const int bh = fast_div(rest, p.d_chunks), chunk = rest - bh * p.chunks;
+        const int b = fast_div(bh, p.d_hkv), hkv = bh - b * p.Hkv;
+        return ((size_t)b * p.Hq + hkv * p.G + chunk * p.pack) * p.Sq + q0;
+    };
+    if (p.reserve) {
+        uint32_t *shared = (uint32_t *)smem;
+        if (tid == 0) shared[0] = pool_take(p.units);
+        __syncthreads();
+        const uint32_t unit = shared[0];
+        const int items = p.nrest * p.ntile;
+        if (unit != POOL_NONE) {
+            uint32_t *header = (uint32_t *)(g_pool + (size_t)unit * POOL_UNIT_BYTES);
+            if (tid <= items) header[tid] = 0;
+        }
+        if (tid < items)
+            ((uint32_t *)p.lse)[item_lse(tid % p.nrest, tid / p.nrest * p.tile_pos)] = unit;
+        return;
+    }
+    const int tile_r = fast_div(bid, p.d_nrs), rest_s = bid - tile_r * (p.nrest * p.splits);
+    const int rest = fast_div(rest_s, p.d_splits), part = rest_s - rest * p.splits;
+    const int tile = p.ntile - 1 - tile_r;
     const int bh = fast_div(rest, p.d_chunks), chunk = rest - bh * p.chunks;
     const int b = fast_div(bh, p.d_hkv), hkv = bh - b * p.Hkv;
     const int q0 = tile * p.tile_pos;
@@ -1171,7 +1272,22 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
     // keys 0 .. klast are valid for some row of the tile
     int klast = p.Skv - 1;
     if (CAUSAL) klast = min(klast, min(q0 + p.tile_pos - 1, p.Sq - 1) + off);
-    const int nb = klast < 0 ? 0 : klast / SPLIT_KEYS + 1;
+    int nb = klast < 0 ? 0 : klast / SPLIT_KEYS + 1;
+    // this workgroup's blocks: part, of `splits` ranges of equal length (the last ones may be shorter or empty)
+    int first = 0;
+    uint32_t unit = POOL_NONE;
+    if (p.splits > 1) {
+        // (read as a constant: nothing writes it until every workgroup of the item has read it)
+        unit = ((const __attribute__((address_space(4))) uint32_t *)(uintptr_t)p.lse)[item_lse(rest, q0)];
+        asm volatile("" : "+s"(unit));      // read once, here
+        if (unit != POOL_NONE) {
+            const int len = fast_div(nb + p.splits - 1, p.d_splits);
+            first = min(nb, part * len);
+            nb = min(nb, first + len);
+        } else if (part != 0) {
+            return;
+        }
+    }
     const size_t kv_row_bytes = (size_t)p.Hkv * HD * 2;
     const unsigned char *kg = (const unsigned char *)(p.k + ((size_t)b * p.Skv * p.Hkv + hkv) * HD);
     const unsigned char *vg = (const unsigned char *)(p.v + ((size_t)b * p.Skv * p.Hkv + hkv) * HD);
@@ -1219,7 +1335,7 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
         const uint32_t o = (uint32_t)(drow * p.Hq + dhead) * (uint32_t)(HD * 2) + ((unit ^ (r & 15)) << 4);
         lds_dma16(qg, o, lds0 + SPLIT_Q_BASE + wave * 1024);
     }
-    int t = wave;
+    int t = first + wave;
     if (t < nb) {
         request(t, false);
         request(t, true);
@@ -1254,7 +1370,7 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
     for (int s = 0; s < 8; ++s)
         qf[s] = *(const LDS_AS bf16x8 *)(lds + SPLIT_Q_BASE + l32 * ROW_BYTES + (((2 * s + hh) ^ (l32 & 15)) << 4));
 
-    // Blocks wave, wave + 8, ...: K(t) and V(t) were requested above (this wavefront's first block); K(t + 8) goes out as soon as the
+    // Blocks first + wave, first + wave + 8, ...: K(t) and V(t) were requested above (this wavefront's first block); K(t + 8) goes out as soon as the
     // score MFMAs have read K(t), V(t + 8) as soon as the PV MFMAs have read V(t), so that a wait is "all
     // but the newest eight requests have landed" while there is a next block and "all" at the last one.
     for (; t < nb; t += NWAVES) {
@@ -1383,6 +1499,81 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
                 o8[4 + j] += f * hi[j];
             }
         }
+        if (unit != POOL_NONE) {
+            // Leave this part's result; every thread of the merging workgroup reads what the same thread of
+            // the others wrote, so the accumulators lie in thread order.
+            unsigned char *run = g_pool + (size_t)unit * POOL_UNIT_BYTES;
+            uint32_t *header = (uint32_t *)run;
+            const int item = tile * p.nrest + rest;
+            unsigned char *mine = run + SPLIT_HEADER_BYTES + (size_t)item * p.splits * SPLIT_PART_BYTES;
+            const bool valid = qpos < p.Sq;
+            {
+                unsigned char *out = mine + (size_t)part * SPLIT_PART_BYTES;
+                if (valid) {
+                    pool_store4(out + ((2 * wave) * 64 + lane) * 16, o8[0], o8[1], o8[2], o8[3]);
+                    pool_store4(out + ((2 * wave + 1) * 64 + lane) * 16, o8[4], o8[5], o8[6], o8[7]);
+                }
+                if (wave == 0 && hh == 0) {
+                    float *st = (float *)(out + 32 * HD * 4);
+                    pool_store(st + l32, M);
+                    pool_store(st + 32 + l32, L);
+                    pool_store(st + 64 + l32, LR);
+                }
+            }
+            __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);        // this thread's stores have arrived
+            __syncthreads();                // (also: everyone is done with the state area)
+            uint32_t *shared = (uint32_t *)(smem + SPLIT_STATE_BASE);
+            if (tid == 0)
+                shared[0] = __hip_atomic_fetch_add(&header[1 + item], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            if (shared[0] != (uint32_t)p.splits - 1) return;
+            // eight parts at a time, all of their loads in flight together
+            M = -INFINITY;
+            L = LR = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) o8[j] = 0.0f;
+            constexpr int BATCH = 8;
+            for (int s0 = 0; s0 < p.splits; s0 += BATCH) {
+                float ms[BATCH], ls[BATCH], rs[BATCH], x[BATCH][8];
+#pragma unroll
+                for (int i = 0; i < BATCH; ++i) {
+                    const bool there = s0 + i < p.splits;
+                    const unsigned char *in = mine + (size_t)(s0 + i) * SPLIT_PART_BYTES;
+                    const float *st = (const float *)(in + 32 * HD * 4);
+                    ms[i] = there ? pool_load(st + l32) : -INFINITY;
+                    ls[i] = there ? pool_load(st + 32 + l32) : 0.0f;
+                    rs[i] = there ? pool_load(st + 64 + l32) : 0.0f;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) x[i][j] = 0.0f;
+                    if (there && valid) {
+                        pool_load4(in + ((2 * wave) * 64 + lane) * 16, x[i]);
+                        pool_load4(in + ((2 * wave + 1) * 64 + lane) * 16, x[i] + 4);
+                    }
+                }
+                float mn = M;
+#pragma unroll
+                for (int i = 0; i < BATCH; ++i) mn = fmaxf(mn, ms[i]);
+                const float keep = (M == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(M - mn);
+                M = mn;
+                L *= keep;
+                LR *= keep;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) o8[j] *= keep;
+#pragma unroll
+                for (int i = 0; i < BATCH; ++i) {
+                    const float f = (ms[i] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(ms[i] - M);
+                    L += f * ls[i];
+                    LR += f * rs[i];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) o8[j] += f * x[i][j];
+                }
+            }
+            __syncthreads();                // everything of this item is read
+            if (tid == 0) {
+                const uint32_t done = __hip_atomic_fetch_add(&header[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (done == (uint32_t)(p.nrest * p.ntile) - 1) pool_give(unit, p.units);
+            }
+        }
         const float inv = LR > 0.0f ? 1.0f / LR : 0.0f;
         if (qpos < p.Sq) {
             u32x4 ww = {pack_bf16(o8[0] * inv, o8[1] * inv), pack_bf16(o8[2] * inv, o8[3] * inv),
@@ -1395,8 +1586,23 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
         }
     }
 #ifdef ATTN_CLOCKS
-    if (item == 0 && tid == 0) { g_clocks[1] = __builtin_readcyclecounter(); g_clocks[3] = wall_clock64(); }
+    if (bid == 0 && tid == 0) { g_clocks[1] = __builtin_readcyclecounter(); g_clocks[3] = wall_clock64(); }
 #endif
+}
+
+// Workgroups that share one item of the split-key kernel, whose key sequence is `blocks` blocks of 32 keys.
+// One workgroup takes about 5 us + 1.3 us per 8 blocks as long as memory keeps up (measured, 8 items: 7.0 us at 16 blocks,
+// 15.0 at 64, 43 at 256, 189 at 1024); sharing an item adds about 4 us for the reserving launch and
+// 0.25 us per part to merge, so the sum is least at parts^2 = 0.65 blocks (measured, 8 items: 64 blocks 12.5 us
+// with 4 parts, 12.8 with 8; 256 blocks 17.4 with 8 or 16, 20.1 with 24; 1024 blocks 32.9 with 16, 36.2 with 32) and
+// not worth it below 40 blocks (32 blocks, 16 blocks: 10 and 7 us in one part, 11 in two).
+// More workgroups than compute units start a second round: 160 items in two parts 26.5 us, in one 16.2.
+int split_parts(int64_t items, int blocks, int ncu)
+{
+    if (items > SPLIT_MAX_ITEMS || blocks < 40) return 1;
+    int s = 1;
+    while ((s + 1) * items <= (ncu < SPLIT_MAX_WGS ? ncu : SPLIT_MAX_WGS) && 5 * (s + 1) * (s + 1) <= 2 * blocks) ++s;
+    return s;
 }
 
 }  // namespace
@@ -1470,11 +1676,15 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
     // a negative scale turns the running maximum of the scaled scores into c times the smallest raw score
     const bool neg = scale < 0.0f;
 
-    // Small problems: few 256-row items would leave most compute units idle; 32-row items whose keys
-    // are shared out among the wavefronts of a workgroup fill the device instead.
+    // Small problems: few 256-row items would leave most compute units idle, and items of few rows (the
+    // query heads of one group times the positions of the sequence) most of each item's rows; 32-row items whose keys
+    // are shared out among the wavefronts of a workgroup, and among workgroups, fill the device instead.
+    // Few rows, measured, 256-row / split-key kernel, us: 4 rows x 4000 keys, 128 items 77.9 / 42.4; 4 x 4096, 512 items
+    // 240.8 / 184.1 (1.07 GB of K and V); 4 x 500, 512 items 35.6 / 24.1; 1 x 8000, 256 items 232.9 / 175.2.
     const int split_tile_pos = 32 / sh.pack;
     const int64_t split_items = (int64_t)B * Hkv * sh.chunks * ((Sq + split_tile_pos - 1) / split_tile_pos);
-    const bool small = ATTN_SMALL_PATH == 2 || (ATTN_SMALL_PATH == 1 && total * 4 <= ncu);
+    const bool few_rows = (int64_t)Sq * sh.pack <= 64;
+    const bool small = ATTN_SMALL_PATH == 2 || (ATTN_SMALL_PATH == 1 && (total * 4 <= ncu || few_rows));
     if (small && split_items < INT32_MAX) {
         SplitParams sp = {};
         sp.q = p.q; sp.k = p.k; sp.v = p.v; sp.o = p.o; sp.lse = lse;
@@ -1482,19 +1692,32 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
         sp.pack = sh.pack; sp.pack_log2 = sh.pack_log2; sp.chunks = sh.chunks;
         sp.tile_pos = split_tile_pos;
         sp.ntile = (Sq + split_tile_pos - 1) / split_tile_pos;
-        sp.d_ntile = make_div((uint32_t)sp.ntile);
+        sp.nrest = (int)((int64_t)B * Hkv * sh.chunks);
+        sp.splits = split_parts(split_items, (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS, ncu);
+        sp.d_nrs = make_div((uint32_t)(sp.nrest * sp.splits));
+        sp.d_splits = make_div((uint32_t)sp.splits);
         sp.d_chunks = make_div((uint32_t)sp.chunks);
         sp.d_hkv = make_div((uint32_t)Hkv);
         sp.c = p.c;
-        const dim3 sgrid((unsigned)split_items), sblock(NTHREADS);
-        if (causal && neg)
-            hipLaunchKernelGGL((attn_fwd_split_kernel<true, true>), sgrid, sblock, SPLIT_LDS_BYTES, st, sp);
-        else if (causal)
-            hipLaunchKernelGGL((attn_fwd_split_kernel<true, false>), sgrid, sblock, SPLIT_LDS_BYTES, st, sp);
-        else if (neg)
-            hipLaunchKernelGGL((attn_fwd_split_kernel<false, true>), sgrid, sblock, SPLIT_LDS_BYTES, st, sp);
-        else
-            hipLaunchKernelGGL((attn_fwd_split_kernel<false, false>), sgrid, sblock, SPLIT_LDS_BYTES, st, sp);
+        auto launch = [&](unsigned wgs, int lds) {
+            const dim3 sgrid(wgs), sblock(NTHREADS);
+            if (causal && neg)
+                hipLaunchKernelGGL((attn_fwd_split_kernel<true, true>), sgrid, sblock, lds, st, sp);
+            else if (causal)
+                hipLaunchKernelGGL((attn_fwd_split_kernel<true, false>), sgrid, sblock, lds, st, sp);
+            else if (neg)
+                hipLaunchKernelGGL((attn_fwd_split_kernel<false, true>), sgrid, sblock, lds, st, sp);
+            else
+                hipLaunchKernelGGL((attn_fwd_split_kernel<false, false>), sgrid, sblock, lds, st, sp);
+        };
+        if (sp.splits > 1) {
+            sp.units = (int)((SPLIT_HEADER_BYTES + split_items * sp.splits * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
+            sp.reserve = 1;
+            launch(1, 1024);
+            if (hipGetLastError() != hipSuccess) return ATTN_E_LAUNCH;
+            sp.reserve = 0;
+        }
+        launch((unsigned)(split_items * sp.splits), SPLIT_LDS_BYTES);
         return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_E_LAUNCH;
     }
 
