@@ -1160,7 +1160,17 @@ struct SplitParams {
 // the others leave, which is slower but needs no memory.
 constexpr int POOL_UNITS = 64;
 constexpr uint32_t POOL_UNIT_BYTES = 1u << 20;
-constexpr uint32_t POOL_NONE = 0xffffffffu;
+constexpr uint32_t POOL_NONE = 0xffu;
+// How the number (or POOL_NONE) stands in an LSE element: as a NaN whose low half is no result's.  (A NaN of a
+// result has the default payload or one that came in with a BF16 value, whose low 16 bits are zero.)  Where no run was
+// free, a late workgroup may find the item's result there instead, already stored by the first one, and has to
+// take anything but the mark for "none".
+constexpr uint32_t POOL_MARK = 0xffe5a500u;
+static_assert(POOL_UNITS <= POOL_NONE, "a unit's number fits the low byte of the mark");
+__host__ __device__ inline uint32_t pool_mark(uint32_t unit) { return POOL_MARK | unit; }
+__host__ __device__ inline uint32_t pool_unmark(uint32_t word) {
+    return (word ^ POOL_MARK) < POOL_UNITS ? (word ^ POOL_MARK) : POOL_NONE;
+}
 __device__ unsigned long long g_pool_taken;         // bit u: unit u belongs to a launch in flight
 __device__ __attribute__((aligned(4096))) unsigned char g_pool[POOL_UNITS * POOL_UNIT_BYTES];
 constexpr int SPLIT_MAX_ITEMS = 256;                // of a launch with splits > 1 (one thread each in the reserving workgroup)
@@ -1256,7 +1266,7 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
             if (tid <= items) header[tid] = 0;
         }
         if (tid < items)
-            ((uint32_t *)p.lse)[item_lse(tid % p.nrest, tid / p.nrest * p.tile_pos)] = unit;
+            ((uint32_t *)p.lse)[item_lse(tid % p.nrest, tid / p.nrest * p.tile_pos)] = pool_mark(unit);
         return;
     }
     const int tile_r = fast_div(bid, p.d_nrs), rest_s = bid - tile_r * (p.nrest * p.splits);
@@ -1277,9 +1287,10 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
     int first = 0;
     uint32_t unit = POOL_NONE;
     if (p.splits > 1) {
-        // (read as a constant: nothing writes it until every workgroup of the item has read it)
+        // (read as a constant: where units were taken, nothing writes it until every workgroup of the item has read it)
         unit = ((const __attribute__((address_space(4))) uint32_t *)(uintptr_t)p.lse)[item_lse(rest, q0)];
         asm volatile("" : "+s"(unit));      // read once, here
+        unit = pool_unmark(unit);
         if (unit != POOL_NONE) {
             const int len = fast_div(nb + p.splits - 1, p.d_splits);
             first = min(nb, part * len);

@@ -43,20 +43,22 @@ def test_hard_scores():
     U.check_full(q, k, v, True, SCALE, what="empty rows")
 
 
-def _launch(x, out, stream):
+def _launch(x, out, stream, entry=None):
     q, k, v = x
     (B, Sq, Hq, D), (_, Skv, Hkv, _) = q.shape, k.shape
-    rc = A.attn_fwd(q, k, v, out[0], out[1], B, Hq, Hkv, Sq, Skv, D, True, SCALE, stream.cuda_stream)
+    rc = (A.attn_fwd if entry is None else lambda *a: P.variant_attn_fwd(entry, *a))(q, k, v, out[0], out[1], B, Hq, Hkv, Sq, Skv, D, True, SCALE, stream.cuda_stream)
     assert rc == 0, A.attn_strerror(rc)
 
 
-def test_many_streams_at_once_and_graph_replay():
-    """Launches in flight together do not touch each other's partial results, and give their units back."""
+@pytest.mark.parametrize("entry", [None, "no_pool"])
+def test_many_streams_at_once_and_graph_replay(entry):
+    """Launches in flight together do not touch each other's partial results, and give their units back.  Without units
+    (no_pool) a workgroup that starts after its item's result is stored finds that result, and nothing to do."""
     xs = [tuple(t.cuda() for t in _inputs(n)) for n in (4, 5, 7, 9)] * 2
     outs = [(torch.empty_like(x[0]), torch.empty((x[0].shape[0], x[0].shape[2], x[0].shape[1]), device="cuda")) for x in xs]
     ref = []
     for x, o in zip(xs, outs):
-        _launch(x, o, torch.cuda.current_stream())
+        _launch(x, o, torch.cuda.current_stream(), entry)
         torch.cuda.synchronize()
         ref.append([t.clone() for t in o])
     streams = [torch.cuda.Stream() for _ in xs]
@@ -64,7 +66,7 @@ def test_many_streams_at_once_and_graph_replay():
     for x, o, s in zip(xs, outs, streams):
         g = torch.cuda.CUDAGraph()
         with torch.cuda.graph(g, stream=s):
-            _launch(x, o, s)
+            _launch(x, o, s, entry)
         graphs.append(g)
     for rep in range(40):           # (a run of units that stayed taken would use the pool up)
         for o in outs:
@@ -73,7 +75,7 @@ def test_many_streams_at_once_and_graph_replay():
         torch.cuda.synchronize()
         for x, o, s, g in zip(xs, outs, streams, graphs):
             with torch.cuda.stream(s):
-                g.replay() if rep % 2 else _launch(x, o, s)
+                g.replay() if rep % 2 else _launch(x, o, s, entry)
         torch.cuda.synchronize()
         for n, (o, r) in enumerate(zip(outs, ref)):
             assert torch.equal(o[0], r[0]) and torch.equal(o[1], r[1]), (rep, n)
