@@ -62,7 +62,8 @@ enum {
  * units or hold at most 64 rows each, one with one workgroup per
  * 32 query rows that share a K/V head (p heads x 32/p positions), whose
  * wavefronts share the item's keys and merge their partial results through LDS.
- * Where these are fewer than the compute units and the key sequence is long,
+ * Where these are fewer than the compute units and the key sequence is long, or
+ * where whole 256-row items would leave compute units without work for long,
  * several workgroups share an item's keys; the launch is then preceded by one of a
  * single workgroup, which takes the device memory that the partial results pass
  * through.  Any number of threads and streams may do so at a time: a launch

@@ -36,6 +36,11 @@ VARIANTS = {
     "always_small_path": ["-DATTN_SMALL_PATH=2"],
     # the split-key kernel without its pool for partial results (what a launch does that finds the pool in use)
     "no_pool": ["-DATTN_POOL=0"],
+    # the 256-row kernel with whole items only / with items shared among workgroups wherever the device memory for it
+    # serves / the same, finding that memory in use
+    "whole_items": ["-DATTN_SHARE=0"],
+    "always_share": ["-DATTN_SHARE=2", "-DATTN_SMALL_PATH=0"],
+    "always_share_no_pool": ["-DATTN_SHARE=2", "-DATTN_SMALL_PATH=0", "-DATTN_POOL=0"],
     "lds_prefetch_1": ["-DATTN_LDS_PREFETCH=1"],
     "lds_prefetch_5": ["-DATTN_LDS_PREFETCH=5"],
     # the shipped kernel plus clock stamps of its first workgroup (exports attn_clocks_read as well)

@@ -44,6 +44,12 @@
 // SIMD the issue of vector instructions, not the matrix pipe alone, is what
 // an iteration's length follows.
 //
+// Where whole items would leave compute units without work for long (fewer items than compute units, a last
+// round with few of them), the kernel's shared form cuts the line of all items' key blocks into
+// stretches of equal length, one for each workgroup; an item that a cut falls into is added up from its parts
+// (512 rows against 16384 keys, 32 heads on 8, causal: 203 -> 127 us; one sequence of 16384, 4 heads, causal:
+// 324 -> 248).
+//
 // A second kernel at the end of this file serves small problems (few query
 // rows, however many keys): 32-row work items whose key blocks are shared out
 // among the wavefronts of a workgroup and whose partial results are merged
@@ -51,6 +57,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <math.h>
+#include <float.h>
 #include <type_traits>
 #include <atomic>
 
@@ -87,6 +94,11 @@
 // pool for partial results in use, and takes the path for that case.
 #ifndef ATTN_POOL
 #define ATTN_POOL 1
+#endif
+// ATTN_SHARE: which launches of the 256-row kernel share items among workgroups: 1 (shipped) those that it makes
+// shorter; 0 none; 2 all that the device memory for it can serve.
+#ifndef ATTN_SHARE
+#define ATTN_SHARE 1
 #endif
 // ATTN_LDS_PREFETCH: how many MFMAs ahead of its consumer an LDS operand fragment is read (shipped: 3).
 #ifndef ATTN_LDS_PREFETCH
@@ -188,6 +200,22 @@ struct Sched {
     int per_win;    // window * nsub
     Div d_ntile, d_per_win, d_window;
 };
+// How the work items are shared (SHARED kernels only).  The items stand in a line, (group, tile) with tiles
+// fastest, each as long as its key blocks plus `extra`, and workgroup w takes what lies between cut(w) and
+// cut(w + 1), cut(w) = w * total / wgs, moved to an item's end or start where it would leave a part of fewer than
+// SHARE_MIN_PART blocks.
+struct Share {
+    int total;      // length of the line; total * wgs < 2^31
+    int wgs;        // workgroups of the launch (a multiple of 8); total / wgs >= extra + 2 SHARE_MIN_PART - 1, so that each has a part
+    int groups;     // B * Hkv * chunks
+    int group_len;  // total / groups
+    int extra;      // what an item costs beside its blocks, in blocks
+    int units;      // POOL_UNIT_BYTES units of device memory
+};
+constexpr int SHARE_MIN_PART = 2;
+// Beside its blocks an item costs about 8400 cycles (a block: 2560), and under the causal mask four masked blocks
+// of 1300 cycles more each, not all of which the cut falls on.
+constexpr int SHARE_EXTRA = 3, SHARE_EXTRA_CAUSAL = 5;
 // Tensor shape and head packing (read by the per-item code only).
 struct Shape {
     int Sq, Hq;
@@ -209,6 +237,7 @@ struct Params {
     float *lse;
     Shape shape;
     Sched sched;
+    Share share;
 };
 
 // "Extreme" below is the raw score that maximises score * c: the largest one for c >= 0, the smallest
@@ -309,10 +338,112 @@ __device__ __forceinline__ unsigned long long phase_now() {
 #define ATTN_PHASE_COUNT(k) do { } while (0)
 #endif
 
-template <bool CAUSAL, bool NEG>
+// Device memory for partial results: a part of the code object, so it exists once per device, needs no
+// allocation and no host-side bookkeeping, and goes when the library is unloaded.  A launch takes a run of
+// units and gives it back, both on the device: a one-workgroup launch in front finds a free run and
+// leaves its number in the first LSE element of every item, which is the launch's own memory and is overwritten by the
+// result only after all workgroups of the item have read it.  The 256-row kernel's shared form takes 18 units or fewer.  Launches on any number of streams, from
+// any thread and replayed from graphs thus never share units; if no run is free (the pool serves at
+// least POOL_UNITS / SHARE_MAX_UNITS launches at a time), the first workgroup of each item takes all of its keys and
+// the others leave, which is slower but needs no memory.
+constexpr int POOL_UNITS = 64;
+constexpr uint32_t POOL_UNIT_BYTES = 4u << 20;
+constexpr uint32_t POOL_NONE = 0xffu;
+// How the number (or POOL_NONE) stands in an LSE element: as a NaN whose low half is no result's.  (A NaN of a
+// result has the default payload or one that came in with a BF16 value, whose low 16 bits are zero.)  Where no run was
+// free, a late workgroup may find the item's result there instead, already stored by the first one, and has to
+// take anything but the mark for "none".
+constexpr uint32_t POOL_MARK = 0xffe5a500u;
+static_assert(POOL_UNITS <= POOL_NONE, "a unit's number fits the low byte of the mark");
+__host__ __device__ inline uint32_t pool_mark(uint32_t unit) { return POOL_MARK | unit; }
+__host__ __device__ inline uint32_t pool_unmark(uint32_t word) {
+    return (word ^ POOL_MARK) < POOL_UNITS ? (word ^ POOL_MARK) : POOL_NONE;
+}
+__device__ unsigned long long g_pool_taken;         // bit u: unit u belongs to a launch in flight
+__device__ __attribute__((aligned(4096))) unsigned char g_pool[POOL_UNITS * POOL_UNIT_BYTES];
+constexpr int SPLIT_MAX_ITEMS = 256;                // of a launch with splits > 1
+constexpr int SPLIT_MAX_WGS = 512;                  // items * splits of such a launch
+constexpr int SPLIT_PART_BYTES = 32 * HD * 4 + 3 * 32 * 4;          // one partial result: accumulator, m, l, lr
+constexpr uint32_t SPLIT_HEADER_BYTES = 4096;       // at the start of a run: [0] finished items, [1 + item] workgroups that arrived
+constexpr int SPLIT_MAX_UNITS = (SPLIT_HEADER_BYTES + SPLIT_MAX_WGS * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES;
+static_assert((1 + SPLIT_MAX_ITEMS) * 4 <= SPLIT_HEADER_BYTES, "header holds a counter per item");
+static_assert(SPLIT_MAX_UNITS <= POOL_UNITS / 4, "several launches fit the pool");
+// 256-row kernel: a wavefront's part is its accumulator, then m, l, lr, as 17 16-byte pieces per lane.
+constexpr uint32_t SHARE_WAVE_BYTES = 17 * 64 * 16;
+constexpr uint32_t SHARE_SLOT_BYTES = NWAVES * SHARE_WAVE_BYTES;    // 136 KiB: one part of an item
+constexpr uint32_t SHARE_HEADER_BYTES = 64 * 1024;  // [0] workgroups that left, [1 + 8 item + wave] parts that arrived
+constexpr int SHARE_MAX_ITEMS = 2047;
+constexpr int SHARE_MAX_WGS = 256;                  // two slots each at most: one that starts with its item, one that does not
+constexpr int SHARE_MAX_UNITS = (SHARE_HEADER_BYTES + 2 * SHARE_MAX_WGS * SHARE_SLOT_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES;
+static_assert((1 + SHARE_MAX_ITEMS * NWAVES) * 4 <= SHARE_HEADER_BYTES, "header holds a counter per item and wavefront");
+static_assert(SHARE_MAX_UNITS <= POOL_UNITS / 3, "several launches fit the pool");
+// The one lane that takes a run of n units: first free run, or POOL_NONE.
+__device__ inline uint32_t pool_take(int n)
+{
+    if (!ATTN_POOL) return POOL_NONE;
+    const unsigned long long run = (1ull << n) - 1;     // n < 64
+    unsigned long long taken = 0;       // (a guess that is usually right: one round trip to memory)
+    int tries = 0;
+    for (int u = 0; u + n <= POOL_UNITS;) {
+        if (taken & (run << u)) { ++u; continue; }
+        if (__hip_atomic_compare_exchange_strong(&g_pool_taken, &taken, taken | (run << u), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT))
+            return (uint32_t)u;
+        // the mask is another one, `taken` holds it now: look at u again, but not more than POOL_UNITS times in all
+        if (++tries == POOL_UNITS) break;
+    }
+    return POOL_NONE;
+}
+// Partial results pass between workgroups of one launch that may sit on different XCDs, each with an L2 of its
+// own.  They are written and read at agent scope element by element (sc1: through the L2 to memory that all
+// XCDs share), and a wait for the stores stands before the counter that announces them.  An agent-scope release
+// fence instead writes back an XCD's whole L2 for every workgroup: measured 0.17 us each, one after the other
+// (512 workgroups: 80 us).
+__device__ inline void pool_store4(unsigned char *at, float a, float b, float c, float d)
+{
+    typedef unsigned long long u64;
+    const u64 lo = (u64)__float_as_uint(a) | (u64)__float_as_uint(b) << 32, hi = (u64)__float_as_uint(c) | (u64)__float_as_uint(d) << 32;
+    __hip_atomic_store((u64 *)at, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store((u64 *)at + 1, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void pool_load4(const unsigned char *at, float *x)
+{
+    typedef unsigned long long u64;
+    const u64 lo = __hip_atomic_load((const u64 *)at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const u64 hi = __hip_atomic_load((const u64 *)at + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    x[0] = __uint_as_float((uint32_t)lo); x[1] = __uint_as_float((uint32_t)(lo >> 32));
+    x[2] = __uint_as_float((uint32_t)hi); x[3] = __uint_as_float((uint32_t)(hi >> 32));
+}
+// The same at 16 bytes per lane, as buffer accesses with the sc1 bit (agent scope; bounds-checked by the descriptor).
+constexpr int POOL_SC1 = 16;
+__device__ inline __amdgpu_buffer_rsrc_t pool_rsrc(uint32_t unit, int units)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(g_pool + (size_t)unit * POOL_UNIT_BYTES, 0, units * (int)POOL_UNIT_BYTES, 0x00020000);
+}
+__device__ inline void pool_store16(__amdgpu_buffer_rsrc_t rs, uint32_t lane_at, uint32_t at, float a, float b, float c, float d)
+{
+    const u32x4 x = {__float_as_uint(a), __float_as_uint(b), __float_as_uint(c), __float_as_uint(d)};
+    __builtin_amdgcn_raw_buffer_store_b128(x, rs, lane_at, at, POOL_SC1);
+}
+__device__ inline u32x4 pool_load16(__amdgpu_buffer_rsrc_t rs, uint32_t lane_at, uint32_t at)
+{
+    return __builtin_amdgcn_raw_buffer_load_b128(rs, lane_at, at, POOL_SC1);
+}
+__device__ inline void pool_store(float *at, float a) { __hip_atomic_store(at, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline float pool_load(const float *at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void pool_give(uint32_t u, int n)
+{
+    __hip_atomic_fetch_and(&g_pool_taken, ~(((1ull << n) - 1) << u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The forms of the 256-row kernel: whole items for a scale >= 0 and < 0, shared items for both (Q is negated as it is
+// loaded; in the kernel of whole items the branch for that costs 0.2 % of a causal launch).
+enum { FORM_POS, FORM_NEG, FORM_SHARED };
+template <bool CAUSAL, int FORM>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(ATTN_WAVES_PER_SIMD, ATTN_WAVES_PER_SIMD)))
 void attn_fwd_kernel(const Params p)
 {
+    constexpr bool NEG = FORM == FORM_NEG, SHARED = FORM == FORM_SHARED;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
     // Launch constants that only the per-item code needs are read from the kernel argument block where
@@ -342,6 +473,7 @@ void attn_fwd_kernel(const Params p)
 #ifdef ATTN_CLOCKS
     if (bid == 0 && tid == 0) { g_clocks[2] = wall_clock64(); g_clocks[0] = __builtin_readcyclecounter(); }
 #endif
+    const float c = SHARED ? fabsf(p.c) : p.c;
     const int off = p.Skv - cold().shape.Sq;                    // causal: key j valid iff j <= i + off
     const int nfull = p.Skv / BN;                               // tiles below this index are full
     const bool all_full = (p.Skv % BN) == 0;
@@ -375,6 +507,64 @@ void attn_fwd_kernel(const Params p)
         tile = item - grp * sc.ntile;
         return item < sc.total;
     };
+    // SHARED: this workgroup's stretch of the line, and whether items are shared at all (false: no pool units were
+    // free; then the workgroup whose stretch holds an item's start takes all of it)
+    int cut_lo = 0, cut_hi = 0;
+    bool pooled = true;
+    uint32_t unit = POOL_NONE;
+    auto load_share = [&]() __attribute__((always_inline)) -> Share {
+        Share sr;
+        __builtin_memcpy(&sr, &cold().share, sizeof(Share));
+        return sr;
+    };
+    auto blocks_of = [&](const Shape &sh, int tile) __attribute__((always_inline)) -> int {
+        int n = (p.Skv + BN - 1) / BN;
+        if (CAUSAL) {
+            const int klast = min(tile * sh.tile_pos + sh.tile_pos, sh.Sq) - 1 + off;
+            n = klast < 0 ? 0 : min(n, klast / BN + 1);
+        }
+        return n;
+    };
+    // SHARED: first item from (grp, tile), which stands at `at` in the line, that this workgroup has a part of
+    auto find_part = [&](int &grp, int &tile, int &at) __attribute__((always_inline)) -> bool {
+        const Share sr = load_share();
+        const Shape sh = load_shape();
+        const int ntile = cold().sched.ntile;
+        while (grp < sr.groups) {
+            const int n = blocks_of(sh, tile);
+            const int first_cut = at + sr.extra + SHARE_MIN_PART, last_cut = at + sr.extra + n - SHARE_MIN_PART;
+            if (cut_hi < first_cut) return false;
+            if (cut_lo < first_cut || (pooled && cut_lo <= last_cut)) return true;
+            at += n + sr.extra;
+            if (++tile == ntile) { tile = 0; ++grp; }
+        }
+        return false;
+    };
+    // SHARED: the item that `x` of the line lies in
+    auto locate = [&](int x, int &grp, int &tile, int &at) __attribute__((always_inline)) {
+        const Share sr = load_share();
+        const Shape sh = load_shape();
+        const int ntile = cold().sched.ntile;
+        grp = __builtin_amdgcn_readfirstlane((unsigned)x / (unsigned)sr.group_len);
+        at = grp * sr.group_len;
+        for (tile = 0; ; tile += 64) {      // 64 tiles at a time; their lengths add up to group_len
+            const int len = tile + lane < ntile ? blocks_of(sh, tile + lane) + sr.extra : 0;
+            int sum = len;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int o = __shfl_up(sum, d);
+                if (lane >= d) sum += o;
+            }
+            const unsigned long long beyond = __builtin_amdgcn_ballot_w64(at + sum > x);
+            if (beyond != 0 || tile + 64 >= ntile) {
+                const int k = beyond != 0 ? __builtin_ctzll(beyond) : ntile - 1 - tile;
+                at += __builtin_amdgcn_readlane(sum - len, k);
+                tile += k;
+                return;
+            }
+            at += __builtin_amdgcn_readlane(sum, 63);
+        }
+    };
     // first round >= r in which this workgroup has a real entry; false when its list is exhausted
     auto find_item = [&](int &r, int &grp, int &tile) __attribute__((always_inline)) -> bool {
         const Sched sc = load_sched();
@@ -388,26 +578,36 @@ void attn_fwd_kernel(const Params p)
     struct Geo {
         int b, head, q0;                 // batch entry, query head and first query row of this wavefront
         int nblk;                        // key blocks of the workgroup (one barrier each)
+        int j0, at, item, blocks;        // SHARED: first of them, the item's place in the line, its number and all its blocks
         const unsigned char *kg, *vg;    // first K / V row of the item's batch entry and K/V head
     };
     const size_t kv_row_bytes = (size_t)p.Hkv * HD * 2;
     const size_t tile_gbytes = (size_t)BN * kv_row_bytes;
-    auto geometry = [&](int grp, int tile) __attribute__((always_inline)) -> Geo {
+    auto geometry = [&](int grp, int tile, int at) __attribute__((always_inline)) -> Geo {
         const Shape sh = load_shape();
         Geo g;
+        g.j0 = g.at = g.item = g.blocks = 0;
         const int bh = fast_div(grp, sh.d_chunks);
         const int chunk = grp - bh * sh.chunks;
         g.b = fast_div(bh, sh.d_hkv);
         const int hkv = bh - g.b * p.Hkv;
         g.head = hkv * sh.G + chunk * sh.pack + (wave & (sh.pack - 1));
         g.q0 = tile * sh.tile_pos + (wave >> sh.pack_log2) * 32;
-        g.nblk = (p.Skv + BN - 1) / BN;
-        if (CAUSAL) {
-            const int klast = min(tile * sh.tile_pos + sh.tile_pos, sh.Sq) - 1 + off;
-            g.nblk = klast < 0 ? 0 : min(g.nblk, klast / BN + 1);
-        }
+        g.nblk = blocks_of(sh, tile);
         g.kg = (const unsigned char *)(p.k + ((size_t)g.b * p.Skv * p.Hkv + hkv) * HD);
         g.vg = (const unsigned char *)(p.v + ((size_t)g.b * p.Skv * p.Hkv + hkv) * HD);
+        if (SHARED) {
+            const int first = at + cold().share.extra;      // block 0's place in the line
+            int j1 = g.nblk;
+            if (pooled && cut_hi <= first + j1 - SHARE_MIN_PART) j1 = cut_hi - first;
+            if (pooled && cut_lo >= first + SHARE_MIN_PART) g.j0 = __builtin_amdgcn_readfirstlane(cut_lo - first);
+            g.blocks = __builtin_amdgcn_readfirstlane(g.nblk);
+            g.nblk = j1 - g.j0;
+            g.at = __builtin_amdgcn_readfirstlane(at);
+            g.item = __builtin_amdgcn_readfirstlane(grp * cold().sched.ntile + tile);
+            g.kg += g.j0 * tile_gbytes;
+            g.vg += g.j0 * tile_gbytes;
+        }
         // all of it is wave-uniform: say so, so that it lives in scalar registers
         g.b = __builtin_amdgcn_readfirstlane(g.b);
         g.head = __builtin_amdgcn_readfirstlane(g.head);
@@ -423,16 +623,22 @@ void attn_fwd_kernel(const Params p)
     int nblk = 0;       // key blocks of the workgroup
     int n_w = 0;        // of those, the blocks that hold a key valid for some row of this wavefront
     int n_unm = 0;      // of those, the leading blocks that need no mask at all
+    int part_j0 = 0;    // SHARED: first block of the part in work; block numbers and key indices count from there
+    auto keys = [&]() __attribute__((always_inline)) -> int { return SHARED ? p.Skv - part_j0 * BN : p.Skv; };
+    auto offset = [&]() __attribute__((always_inline)) -> int { return SHARED ? off - part_j0 * BN : off; };
     const unsigned char *kg = nullptr, *vg = nullptr;
+    int nx_keys = 0;                    // SHARED: keys from its first block on
     bool warm_next = false;             // the item after this one exists and its first tiles are requested by this one
     int nx_nblk = 0;
     const unsigned char *nx_kg = nullptr, *nx_vg = nullptr;
     int ring0 = 0;                      // LDS stage of block 0 of the item in work
     auto enter = [&](const Geo &g) __attribute__((always_inline)) {
         b = g.b; head = g.head; q0 = g.q0; nblk = g.nblk; kg = g.kg; vg = g.vg;
-        n_unm = p.Skv / BN;
+        if (SHARED) part_j0 = g.j0;
+        n_unm = keys() / BN;
         n_w = nblk;
         if (CAUSAL) {
+            const int off = offset();
             const int klast_w = q0 + 31 + off;          // last key valid for the last row of the wave
             n_w = klast_w < 0 ? 0 : min(nblk, klast_w / BN + 1);
             const int kfirst_w = q0 + off + 1;          // number of keys valid for every row of the wave
@@ -453,12 +659,19 @@ void attn_fwd_kernel(const Params p)
     float lr;              // the same sum over the BF16-rounded probabilities that multiply V: O is
                            // normalised by this one, so that a rounding error in a dominant weight
                            // cancels between numerator and denominator
+    auto negate_q = [&]() __attribute__((always_inline)) {
+        if (SHARED && p.c < 0.0f) {
+#pragma unroll
+            for (int s = 0; s < 8; ++s) qf[s] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, qf[s]) ^ 0x80008000u);
+        }
+    };
     auto load_q = [&](const Geo &g) __attribute__((always_inline)) {
         const int Sq = cold().shape.Sq, Hq = cold().shape.Hq;
         const int qrow = min(g.q0 + l32, Sq - 1);
         const __bf16 *qp = cold().q + ((size_t)((size_t)g.b * Sq + qrow) * Hq + g.head) * HD + 8 * hh;
 #pragma unroll
         for (int s = 0; s < 8; ++s) qf[s] = *(const bf16x8 *)(qp + 16 * s);
+        negate_q();
     };
     // The same through LDS: requested (wave-private region, the K swizzle) when the item before
     // starts, fetched into registers when that one's last block is done.
@@ -510,11 +723,13 @@ void attn_fwd_kernel(const Params p)
     // end) a block of the next item if that one is being warmed up; otherwise, and past the end of
     // the next item too, the last block is read again into the (dead) stage the request would have
     // used, so that the number of loads in flight is the same in every iteration.
-    auto tile_ptr = [&](int blk_req, bool is_v, int &blk) __attribute__((always_inline)) -> const unsigned char * {
+    auto tile_ptr = [&](int blk_req, bool is_v, int &blk, int &left) __attribute__((always_inline)) -> const unsigned char * {
         const unsigned char *g = is_v ? vg : kg;
+        left = keys();      // keys from the item's first block on
         blk = min(blk_req, nblk - 1);
         if (blk_req >= nblk && warm_next) {
             g = is_v ? nx_vg : nx_kg;
+            if (SHARED) left = nx_keys;
             blk = min(blk_req - nblk, nx_nblk - 1);
         }
         return g + (size_t)blk * tile_gbytes;
@@ -522,10 +737,10 @@ void attn_fwd_kernel(const Params p)
     // General form of a tile request: rows past the end of a partial tile re-read the last row (they
     // are masked later).
     auto issue_tile = [&](int blk_req, bool is_v) __attribute__((always_inline)) {
-        int blk;
-        const unsigned char *g = tile_ptr(blk_req, is_v, blk);
+        int blk, left;
+        const unsigned char *g = tile_ptr(blk_req, is_v, blk, left);
         const uint32_t lbase = lds_wave + (is_v ? V_BASE : 0) + stage_off(blk_req);
-        const bool partial = (blk + 1) * BN > p.Skv;
+        const bool partial = (blk + 1) * BN > left;
 #pragma unroll
         for (int i = 0; i < LPT; ++i) {
             uint32_t o = is_v ? voff[i] : koff[i];
@@ -533,7 +748,7 @@ void attn_fwd_kernel(const Params p)
                 int ln = lane;
                 PIN(ln);        // formed here, not kept in a register across the block loop
                 const int row = (wave * LPT + i) * 4 + (ln >> 4);
-                const int rl = min(row, p.Skv - 1 - blk * BN);
+                const int rl = min(row, left - 1 - blk * BN);
                 o = o - (uint32_t)(row * kv_row_bytes) + (uint32_t)(rl * kv_row_bytes);
             }
             lds_dma16(g, o, lbase + i * 1024);
@@ -669,8 +884,8 @@ void attn_fwd_kernel(const Params p)
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int r = 0; r < 16; r += 2) {
-                const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], p.c, -m));
-                const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r + 1], p.c, -m));
+                const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], c, -m));
+                const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r + 1], c, -m));
                 ls0 += e0;
                 ls1 += e1;
                 pb[t][r >> 1] = pack_bf16(e0, e1);
@@ -686,7 +901,7 @@ void attn_fwd_kernel(const Params p)
 #pragma unroll
         for (int i = 3; i < 31; i += 2) mx = ext3<NEG>(mx, s[i >> 4][i & 15], s[(i + 1) >> 4][(i + 1) & 15]);
         mx = ext3<NEG>(mx, s[1][15], s[1][15]);
-        return lane32_ext<NEG>(mx) * p.c;
+        return lane32_ext<NEG>(mx) * c;
     };
     auto raise_reference = [&](f32x16 (&s)[2]) __attribute__((always_inline)) {
         const float mx = block_maximum(s);
@@ -699,8 +914,8 @@ void attn_fwd_kernel(const Params p)
     auto softmax_masked = [&](f32x16 (&s)[2], int blk) __attribute__((always_inline)) {
         int ln = lane;
         PIN(ln);                // lane-derived values are formed here, not kept across the block loop
-        int lim = p.Skv - 1;
-        if (CAUSAL) lim = min(lim, q0 + (ln & 31) + off);
+        int lim = keys() - 1;
+        if (CAUSAL) lim = min(lim, q0 + (ln & 31) + offset());
         const int kidx = blk * BN + 4 * (ln >> 5);
         constexpr float NONE = NEG ? INFINITY : -INFINITY;      // extreme of no score at all
         float mx = NONE;
@@ -712,7 +927,7 @@ void attn_fwd_kernel(const Params p)
                 mx = ext2<NEG>(mx, key <= lim ? s[t][r] : NONE);
             }
         mx = lane32_ext<NEG>(mx);
-        mx = (mx == NONE) ? -INFINITY : mx * p.c;
+        mx = (mx == NONE) ? -INFINITY : mx * c;
         if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
             const float mn = fmaxf(m, mx);
             rescale(mn, (mn == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - mn));
@@ -724,8 +939,8 @@ void attn_fwd_kernel(const Params p)
 #pragma unroll
             for (int r = 0; r < 16; r += 2) {
                 const int key = kidx + 32 * t + 8 * (r >> 2) + (r & 3);
-                float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], p.c, -mu));
-                float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r + 1], p.c, -mu));
+                float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], c, -mu));
+                float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r + 1], c, -mu));
                 e0 = (key <= lim) ? e0 : 0.0f;
                 e1 = (key + 1 <= lim) ? e1 : 0.0f;
                 ls += e0 + e1;
@@ -764,8 +979,8 @@ void attn_fwd_kernel(const Params p)
         if (MASKED) {
             int ln = lane;
             PIN(ln);
-            int lim = p.Skv - 1;
-            if (CAUSAL) lim = min(lim, q0 + (ln & 31) + off);
+            int lim = keys() - 1;
+            if (CAUSAL) lim = min(lim, q0 + (ln & 31) + offset());
             room = lim - blk * BN - 4 * (ln >> 5);
         }
         // Variants 1..3 look for the block's maximum first (the classic running-maximum form); their
@@ -782,7 +997,7 @@ void attn_fwd_kernel(const Params p)
         }
         mfma_block(snxt, s0, s2, [&](int slot) __attribute__((always_inline)) {
             // element `slot` of the 32 scores of this lane: exp now, row-sum add one slot later
-            ev[slot] = __builtin_amdgcn_exp2f(__builtin_fmaf(scur[slot >> 4][slot & 15], p.c, -mref));
+            ev[slot] = __builtin_amdgcn_exp2f(__builtin_fmaf(scur[slot >> 4][slot & 15], c, -mref));
             if (MASKED) {
                 const int r = slot & 15;
                 ev[slot] = (32 * (slot >> 4) + 8 * (r >> 2) + (r & 3) <= room) ? ev[slot] : 0.0f;
@@ -853,12 +1068,156 @@ void attn_fwd_kernel(const Params p)
             fused_iteration(std::true_type{}, scur, snxt, stage_off(j), 0, stage_off(j + 2), nullptr, nullptr, j + 1);
     };
 
+    // ---- SHARED: the end of a part.  A wavefront needs nothing but the same wavefront's parts of the item, so there is
+    // no barrier here.  It leaves its part and counts itself, and the one that completes the count adds all parts up in
+    // the order of the keys, so that the result does not depend on the order of arrival.  Of two parts, the common
+    // case in a line longer than the launch is wide, the second to arrive keeps its own in registers: the counter's
+    // low half counts arrivals, the high half parts that are in memory (1 x 1111, 32 heads on 8, causal: 29.9 us, both parts
+    // through memory 32.4; with more parts the extra round trip costs more than it saves: 700 x 20000, 16 heads, 142 us
+    // against 123).  False if the item's rows are another's to finish.
+    auto share_parts = [&](const Geo &g) __attribute__((always_inline)) -> bool {
+        const Share sr = load_share();
+        const uint32_t wgs = (uint32_t)sr.wgs, total = (uint32_t)sr.total;
+        const uint32_t first = (uint32_t)(g.at + sr.extra);
+        // the cuts inside the item: SHARE_MIN_PART <= cut - first <= blocks - SHARE_MIN_PART
+        const int lo = (int)(((first + SHARE_MIN_PART) * wgs + total - 1) / total);
+        const int hi = (int)(((first + (uint32_t)g.blocks - SHARE_MIN_PART + 1) * wgs + total - 1) / total) - 1;
+        if (g.blocks < 2 * SHARE_MIN_PART || hi < lo) return true;
+        const int parts = __builtin_amdgcn_readfirstlane(hi - lo + 2);
+        uint32_t *arrived = (uint32_t *)(g_pool + (size_t)unit * POOL_UNIT_BYTES) + 1 + g.item * NWAVES + wave;
+        const __amdgpu_buffer_rsrc_t rs = pool_rsrc(unit, sr.units);
+        // slot of part i: that of the workgroup, and for part 0 one of a second set, by item or by workgroup, whichever are fewer
+        const int items = sr.groups * cold().sched.ntile;
+        const int slot0 = __builtin_amdgcn_readfirstlane((int)wgs + (items < (int)wgs ? g.item : lo - 1));
+        const int w = xcd * (int)(wgs >> 3) + slot;
+        int ln = lane;
+        PIN(ln);
+        const uint32_t lane_at = ln * 16;
+        auto slot_of = [&](int i) __attribute__((always_inline)) -> uint32_t {
+            return SHARE_HEADER_BYTES + wave * SHARE_WAVE_BYTES + (uint32_t)(i == 0 ? slot0 : lo - 1 + i) * SHARE_SLOT_BYTES;
+        };
+        const int mine = w - (lo - 1);
+        auto leave = [&]() __attribute__((always_inline)) {
+            const uint32_t out = slot_of(mine);
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                pool_store16(rs, lane_at, out + i * 1024, acc[i >> 2][4 * (i & 3)], acc[i >> 2][4 * (i & 3) + 1],
+                             acc[i >> 2][4 * (i & 3) + 2], acc[i >> 2][4 * (i & 3) + 3]);
+            pool_store16(rs, lane_at, out + 16 * 1024, m, l, lr, 0.0f);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // they have arrived
+        };
+        auto count = [&](uint32_t by) __attribute__((always_inline)) -> uint32_t {
+            uint32_t n = 0;
+            if (ln == 0) n = __hip_atomic_fetch_add(arrived, by, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return __builtin_amdgcn_readfirstlane(n);
+        };
+        if (parts == 2) {
+            uint32_t seen = count(1);
+            if ((seen & 0xffff) == 0) {
+                leave();
+                count(0x10000);
+                return false;
+            }
+            // The other has come here before and needs nothing to go on: the wait is for its stores, if they are under way.
+            while ((seen >> 16) == 0) {
+                __builtin_amdgcn_s_sleep(1);
+                seen = __builtin_amdgcn_readfirstlane(__hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            }
+            asm volatile("" ::: "memory");
+            const uint32_t in = slot_of(1 - mine);
+            const u32x4 st = pool_load16(rs, lane_at, in + 16 * 1024);
+            u32x4 x[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) x[k] = pool_load16(rs, lane_at, in + k * 1024);
+            const float mo = __uint_as_float(st[0]), M = fmaxf(m, mo);      // (neither is minus infinity)
+            const float f = __builtin_amdgcn_exp2f(m - M), fo = __builtin_amdgcn_exp2f(mo - M);
+            m = M;
+            if (mine == 0) {
+                l = __builtin_fmaf(fo, __uint_as_float(st[1]), f * l);
+                lr = __builtin_fmaf(fo, __uint_as_float(st[2]), f * lr);
+#pragma unroll
+                for (int k = 0; k < 64; ++k)
+                    acc[k >> 4][k & 15] = __builtin_fmaf(fo, __uint_as_float(x[k >> 2][k & 3]), f * acc[k >> 4][k & 15]);
+            } else {
+                l = __builtin_fmaf(f, l, fo * __uint_as_float(st[1]));
+                lr = __builtin_fmaf(f, lr, fo * __uint_as_float(st[2]));
+#pragma unroll
+                for (int k = 0; k < 64; ++k)
+                    acc[k >> 4][k & 15] = __builtin_fmaf(f, acc[k >> 4][k & 15], fo * __uint_as_float(x[k >> 2][k & 3]));
+            }
+            return true;
+        }
+        leave();
+        if (count(1) != (uint32_t)parts - 1) return false;
+        asm volatile("" ::: "memory");
+        // Part after part in halves of 32 accumulator elements, the next half always in flight.
+        reset_state();
+        u32x4 st, xa[8], xb[8];
+        uint32_t in = slot_of(0);
+        st = pool_load16(rs, lane_at, in + 16 * 1024);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) xa[k] = pool_load16(rs, lane_at, in + k * 1024);
+#pragma nounroll
+        for (int i = 0; i < parts; ++i) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) xb[k] = pool_load16(rs, lane_at, in + (8 + k) * 1024);
+            const float mi = __uint_as_float(st[0]), mn = fmaxf(m, mi);
+            const float keep = (m == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(m - mn);
+            const float f = __builtin_amdgcn_exp2f(mi - mn);
+            m = mn;
+            l = l * keep + f * __uint_as_float(st[1]);
+            lr = lr * keep + f * __uint_as_float(st[2]);
+#pragma unroll
+            for (int k = 0; k < 32; ++k)
+                acc[k >> 4][k & 15] = acc[k >> 4][k & 15] * keep + f * __uint_as_float(xa[k >> 2][k & 3]);
+            in = slot_of(min(i + 1, parts - 1));        // (the last part again, unused, at the end)
+            st = pool_load16(rs, lane_at, in + 16 * 1024);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) xa[k] = pool_load16(rs, lane_at, in + k * 1024);
+#pragma unroll
+            for (int k = 0; k < 32; ++k)
+                acc[2 + (k >> 4)][k & 15] = acc[2 + (k >> 4)][k & 15] * keep + f * __uint_as_float(xb[k >> 2][k & 3]);
+        }
+        asm volatile("" ::: "memory");
+        return true;
+    };
+
     // ---- the workgroup's items, one after the other
-    int r = 0, grp = 0, tile = 0;
-    bool have = find_item(r, grp, tile);
+    int r = 0, grp = 0, tile = 0, at = 0;
+    bool have;
+    if (SHARED) {
+        const Share sr = load_share();
+        const uint32_t w = xcd * (sr.wgs >> 3) + slot;      // neighbours in the line are on one XCD
+        cut_lo = (int)(w * (uint32_t)sr.total / (uint32_t)sr.wgs);
+        cut_hi = w + 1 == (uint32_t)sr.wgs ? INT32_MAX : (int)((w + 1) * (uint32_t)sr.total / (uint32_t)sr.wgs);
+        // (an item shorter than SHARE_MIN_PART may begin before cut_lo and still be this workgroup's)
+        int grp0, tile0, at0;
+        locate(max(cut_lo - SHARE_MIN_PART, 0), grp0, tile0, at0);
+        grp = grp0; tile = tile0; at = at0;
+        have = find_part(grp, tile, at);
+        if (have) {
+            // the pool units, from the LSE element of the item's first row (nothing writes a result there until this
+            // workgroup has handed in its part)
+            const Shape sh = load_shape();
+            const int bh = fast_div(grp, sh.d_chunks), b = fast_div(bh, sh.d_hkv);
+            const int head = (bh - b * p.Hkv) * sh.G + (grp - bh * sh.chunks) * sh.pack;
+            unit = ((const __attribute__((address_space(4))) uint32_t *)(uintptr_t)cold().lse)
+                [((size_t)b * sh.Hq + head) * sh.Sq + tile * sh.tile_pos];
+            asm volatile("" : "+s"(unit));      // read once, here
+            unit = pool_unmark(unit);
+            pooled = unit != POOL_NONE;
+            if (!pooled) {
+                grp = grp0; tile = tile0; at = at0;
+                have = find_part(grp, tile, at);
+            }
+        }
+        wg_barrier();       // every wavefront has read it before one of them stores a result
+    } else {
+        have = find_item(r, grp, tile);
+    }
     Geo cur = {};
     if (have) {
-        cur = geometry(grp, tile);
+        cur = geometry(grp, tile, at);
         load_q(cur);
     }
     bool warm = false;          // the first tiles of the item about to start were requested by the item before it
@@ -879,12 +1238,20 @@ void attn_fwd_kernel(const Params p)
         // the item after this one
         Geo nxt = cur;
         int r2 = r + 1;
-        const bool have2 = find_item(r2, grp, tile);
-        if (have2) nxt = geometry(grp, tile);
+        bool have2;
+        if (SHARED) {
+            at += cur.blocks + cold().share.extra;
+            if (++tile == cold().sched.ntile) { tile = 0; ++grp; }
+            have2 = find_part(grp, tile, at);
+        } else {
+            have2 = find_item(r2, grp, tile);
+        }
+        if (have2) nxt = geometry(grp, tile, at);
         // Its tiles K'(0..2), V'(0) ride on this item's last iterations (requests K(j+4), V(j+2) of
         // iterations j >= nblk-4), which takes four iterations to host them.
         warm_next = ATTN_ITEM_OVERLAP && have2 && nblk >= 2 + REQ_AHEAD && nxt.nblk > 0;
         nx_nblk = nxt.nblk; nx_kg = nxt.kg; nx_vg = nxt.vg;
+        if (SHARED) nx_keys = p.Skv - nxt.j0 * BN;
         // Its Q goes into this wavefront's LDS region now (the epilogue of the item before is done with
         // it) and into registers when this item's last block is done; being the oldest request of the
         // item, it never holds up a wait for tiles.
@@ -912,11 +1279,15 @@ void attn_fwd_kernel(const Params p)
             // P(0).  A first block without masked keys (every one but a causal item's diagonal start or a
             // short tail) takes its maximum as the reference and has nothing to rescale yet; the masked
             // path also handles an empty first block.
+            // In a shared item a row's scores may be minus infinity in all of a part's first block, and finite in another
+            // part; any finite reference will do until this part sees a finite one.
             if (n_unm > 0) {
                 m = block_maximum(sa);
+                if (SHARED) m = fmaxf(m, -FLT_MAX);
                 l = probabilities(sa, lr);
             } else {
                 softmax_masked(sa, 0);
+                if (SHARED) m = fmaxf(m, -FLT_MAX);
             }
             ATTN_PHASE(2);
             // K(2), V(0) landed: a warm item waited for them before the epilogue of the item before, and
@@ -936,16 +1307,18 @@ void attn_fwd_kernel(const Params p)
             ATTN_PHASE(3);
             // Iterations j < fast_end take the fast path: S(j+1) needs no mask, and the tiles requested are
             // full ones (past the last block: of the next item, or the last block again).
-            int fast_end = all_full ? n_unm - 1 : min(n_unm - 1, nfull - (2 + REQ_AHEAD));
+            int fast_end = all_full ? n_unm - 1 : min(n_unm - 1, (SHARED ? keys() / BN : nfull) - (2 + REQ_AHEAD));
+            // (a next part may begin so near the end that the partial tile is among its first three)
+            if (SHARED && !all_full && warm_next && nx_keys < 3 * BN) fast_end = min(fast_end, nblk - (2 + REQ_AHEAD));
             // Request addresses of the fast loop.  K and V have the same shape, so V's address is K's of
             // two iterations earlier plus the distance between the tensors; K's moves on by one tile per
             // iteration, except at the item's last block (on to block 0 of the next item, or stay) and,
             // if there is no next item, after it (stay).
             const ptrdiff_t dv = (const unsigned char *)p.v - (const unsigned char *)p.k;
-            int unused;
-            const unsigned char *kp = uniform_ptr(tile_ptr(2 + REQ_AHEAD, false, unused));
-            const unsigned char *vp = uniform_ptr(tile_ptr(REQ_AHEAD, true, unused));
-            const unsigned char *vp1 = uniform_ptr(tile_ptr(1 + REQ_AHEAD, true, unused));
+            int unused, unused2;
+            const unsigned char *kp = uniform_ptr(tile_ptr(2 + REQ_AHEAD, false, unused, unused2));
+            const unsigned char *vp = uniform_ptr(tile_ptr(REQ_AHEAD, true, unused, unused2));
+            const unsigned char *vp1 = uniform_ptr(tile_ptr(1 + REQ_AHEAD, true, unused, unused2));
             int kleft = nblk - 1 - (2 + REQ_AHEAD);      // whole-tile steps left before K's request reaches the last block
             const ptrdiff_t kjump = warm_next ? nx_kg - (kg + (size_t)(nblk - 1) * tile_gbytes) : 0;
             const ptrdiff_t kafter = warm_next ? (ptrdiff_t)tile_gbytes : 0;
@@ -1042,62 +1415,68 @@ void attn_fwd_kernel(const Params p)
         __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
         ATTN_PHASE(9);
 
+        bool last_part = true;
+        if (SHARED && unit != POOL_NONE) last_part = share_parts(cur);
         // ---- Q of the next item into registers, from this wavefront's LDS region
-        if (ATTN_ITEM_OVERLAP && have2) {
+        // (SHARED: also if there is none, so that the old values are not kept through the above)
+        if (ATTN_ITEM_OVERLAP && (SHARED || have2)) {
 #pragma unroll
             for (int s = 0; s < 8; ++s)
                 qf[s] = *(const LDS_AS bf16x8 *)(lds + Q_BASE + wave * Q_WAVE_BYTES + kaddr[s]);
         }
-        // ---- epilogue: O = acc / lr (BF16), LSE = ln2 * (m + log2 l).  A lane holds one query's values
-        // in pieces of 8 bytes; they go through the same LDS region (32 rows of 256 bytes, 16-byte units
-        // swizzled by the row), so that each store instruction writes whole rows.
-        const float lt = lane32_sum(l);
-        const float lrt = lane32_sum(lr);
-        const float inv = lrt > 0.0f ? 1.0f / lrt : 0.0f;
-        {
-            const int ob = Q_BASE + wave * Q_WAVE_BYTES;
-            int ln = lane;
-            PIN(ln);        // per-lane offsets are formed here, not kept in registers across the block loop
-            const int orow = ln >> 4, ounit = ln & 15, l32 = ln & 31, hh = ln >> 5;
+        if (ATTN_ITEM_OVERLAP && have2) negate_q();
+        if (last_part) {
+            // ---- epilogue: O = acc / lr (BF16), LSE = ln2 * (m + log2 l).  A lane holds one query's values
+            // in pieces of 8 bytes; they go through the same LDS region (32 rows of 256 bytes, 16-byte units
+            // swizzled by the row), so that each store instruction writes whole rows.
+            const float lt = lane32_sum(l);
+            const float lrt = lane32_sum(lr);
+            const float inv = lrt > 0.0f ? 1.0f / lrt : 0.0f;
+            {
+                const int ob = Q_BASE + wave * Q_WAVE_BYTES;
+                int ln = lane;
+                PIN(ln);        // per-lane offsets are formed here, not kept in registers across the block loop
+                const int orow = ln >> 4, ounit = ln & 15, l32 = ln & 31, hh = ln >> 5;
 #pragma unroll
-            for (int dt = 0; dt < 4; ++dt)
+                for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-                for (int rg = 0; rg < 4; ++rg) {
-                    u32x2 ww = {pack_bf16(acc[dt][4 * rg] * inv, acc[dt][4 * rg + 1] * inv),
-                                pack_bf16(acc[dt][4 * rg + 2] * inv, acc[dt][4 * rg + 3] * inv)};
-                    *(LDS_AS u32x2 *)(lds + ob + l32 * ROW_BYTES + (((4 * dt + rg) ^ (l32 & 15)) << 4) + 8 * hh) = ww;
+                    for (int rg = 0; rg < 4; ++rg) {
+                        u32x2 ww = {pack_bf16(acc[dt][4 * rg] * inv, acc[dt][4 * rg + 1] * inv),
+                                    pack_bf16(acc[dt][4 * rg + 2] * inv, acc[dt][4 * rg + 3] * inv)};
+                        *(LDS_AS u32x2 *)(lds + ob + l32 * ROW_BYTES + (((4 * dt + rg) ^ (l32 & 15)) << 4) + 8 * hh) = ww;
+                    }
+                const int Sq = cold().shape.Sq, Hq = cold().shape.Hq;
+                const size_t o_row_bytes = (size_t)Hq * HD * 2;
+                unsigned char *og = (unsigned char *)(cold().o + ((size_t)((size_t)b * Sq + q0) * Hq + head) * HD);
+                const int rows = Sq - q0;               // rows of this wavefront that exist
+                // (the row pitch is below 2^23 bytes, so the lane's first offset fits 32 bits; the rest are additions)
+                unsigned char *gp = og + ((uint32_t)orow * (uint32_t)o_row_bytes + 16u * (uint32_t)ounit);
+                const size_t gstep = 4 * o_row_bytes;
+                if (rows >= 32) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int row = 4 * i + orow;
+                        const u32x4 val = *(const LDS_AS u32x4 *)(lds + ob + row * ROW_BYTES + ((ounit ^ (row & 15)) << 4));
+                        *(u32x4 *)gp = val;
+                        gp += gstep;
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int row = 4 * i + orow;
+                        const u32x4 val = *(const LDS_AS u32x4 *)(lds + ob + row * ROW_BYTES + ((ounit ^ (row & 15)) << 4));
+                        if (row < rows) *(u32x4 *)gp = val;
+                        gp += gstep;
+                    }
                 }
-            const int Sq = cold().shape.Sq, Hq = cold().shape.Hq;
-            const size_t o_row_bytes = (size_t)Hq * HD * 2;
-            unsigned char *og = (unsigned char *)(cold().o + ((size_t)((size_t)b * Sq + q0) * Hq + head) * HD);
-            const int rows = Sq - q0;               // rows of this wavefront that exist
-            // (the row pitch is below 2^23 bytes, so the lane's first offset fits 32 bits; the rest are additions)
-            unsigned char *gp = og + ((uint32_t)orow * (uint32_t)o_row_bytes + 16u * (uint32_t)ounit);
-            const size_t gstep = 4 * o_row_bytes;
-            if (rows >= 32) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int row = 4 * i + orow;
-                    const u32x4 val = *(const LDS_AS u32x4 *)(lds + ob + row * ROW_BYTES + ((ounit ^ (row & 15)) << 4));
-                    *(u32x4 *)gp = val;
-                    gp += gstep;
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int row = 4 * i + orow;
-                    const u32x4 val = *(const LDS_AS u32x4 *)(lds + ob + row * ROW_BYTES + ((ounit ^ (row & 15)) << 4));
-                    if (row < rows) *(u32x4 *)gp = val;
-                    gp += gstep;
+                if (l32 < rows && hh == 0) {
+                    const float lse = lt > 0.0f ? (m + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f : -INFINITY;
+                    cold().lse[((size_t)b * Hq + head) * Sq + q0 + l32] = lse;
                 }
             }
-            if (l32 < rows && hh == 0) {
-                const float lse = lt > 0.0f ? (m + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f : -INFINITY;
-                cold().lse[((size_t)b * Hq + head) * Sq + q0 + l32] = lse;
-            }
-        }
 
-        if (!ATTN_ITEM_OVERLAP && have2) load_q(nxt);
+        }
+        if (!ATTN_ITEM_OVERLAP && (SHARED || have2)) load_q(nxt);
 #if defined(ATTN_CLOCKS) && ATTN_CLOCKS >= 2
         ATTN_PHASE(10);
         if (bid == 0 && item_no == 1 && (tid == 0 || tid == NTHREADS - 64)) {
@@ -1114,6 +1493,17 @@ void attn_fwd_kernel(const Params p)
         have = have2;
         r = r2;
         cur = nxt;
+    }
+    if (SHARED && unit != POOL_NONE) {
+        // Every workgroup has a part of some item and so knows the units; the last one to leave gives them back.  (One count
+        // per workgroup: 8 per item, all on one address, took 16 us of a launch of 512 items.)
+        wg_barrier();
+        if (tid == 0) {
+            const Share sr = load_share();
+            uint32_t *left = (uint32_t *)(g_pool + (size_t)unit * POOL_UNIT_BYTES);
+            const uint32_t n = __hip_atomic_fetch_add(left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (n == (uint32_t)sr.wgs - 1) pool_give(unit, sr.units);
+        }
     }
 #ifdef ATTN_CLOCKS
     if (bid == 0 && tid == 0) { g_clocks[1] = __builtin_readcyclecounter(); g_clocks[3] = wall_clock64(); }
@@ -1146,83 +1536,11 @@ struct SplitParams {
     int nrest;              // B * Hkv * chunks; items = ntile * nrest
     int splits;             // workgroups that share an item
     int units;              // POOL_UNIT_BYTES units of device memory the launch needs, 0 if splits == 1
-    int reserve;            // 1: this launch is one workgroup that takes the units, for the launch behind it
+    int reserve;            // > 0: this launch is one workgroup that takes the units for the launch behind it, and clears
+                            // this many counters per item (the item geometry is that launch's)
     Div d_nrs, d_splits, d_chunks, d_hkv;   // exact division by nrest * splits, splits, chunks, Hkv
     float c;                // scale * log2(e)
 };
-// Device memory for partial results: a part of the code object, so it exists once per device, needs no
-// allocation and no host-side bookkeeping, and goes when the library is unloaded.  A launch takes a run of
-// units and gives it back, both on the device: a one-workgroup launch in front finds a free run and
-// leaves its number in the first LSE element of every item, which is the launch's own memory and is overwritten by the
-// result only after all workgroups of the item have read it.  Launches on any number of streams, from
-// any thread and replayed from graphs thus never share units; if no run is free (the pool serves at
-// least POOL_UNITS / SPLIT_MAX_UNITS launches at a time), the first workgroup of each item takes all of its keys and
-// the others leave, which is slower but needs no memory.
-constexpr int POOL_UNITS = 64;
-constexpr uint32_t POOL_UNIT_BYTES = 1u << 20;
-constexpr uint32_t POOL_NONE = 0xffu;
-// How the number (or POOL_NONE) stands in an LSE element: as a NaN whose low half is no result's.  (A NaN of a
-// result has the default payload or one that came in with a BF16 value, whose low 16 bits are zero.)  Where no run was
-// free, a late workgroup may find the item's result there instead, already stored by the first one, and has to
-// take anything but the mark for "none".
-constexpr uint32_t POOL_MARK = 0xffe5a500u;
-static_assert(POOL_UNITS <= POOL_NONE, "a unit's number fits the low byte of the mark");
-__host__ __device__ inline uint32_t pool_mark(uint32_t unit) { return POOL_MARK | unit; }
-__host__ __device__ inline uint32_t pool_unmark(uint32_t word) {
-    return (word ^ POOL_MARK) < POOL_UNITS ? (word ^ POOL_MARK) : POOL_NONE;
-}
-__device__ unsigned long long g_pool_taken;         // bit u: unit u belongs to a launch in flight
-__device__ __attribute__((aligned(4096))) unsigned char g_pool[POOL_UNITS * POOL_UNIT_BYTES];
-constexpr int SPLIT_MAX_ITEMS = 256;                // of a launch with splits > 1 (one thread each in the reserving workgroup)
-constexpr int SPLIT_MAX_WGS = 512;                  // items * splits of such a launch
-constexpr int SPLIT_PART_BYTES = 32 * HD * 4 + 3 * 32 * 4;          // one partial result: accumulator, m, l, lr
-constexpr uint32_t SPLIT_HEADER_BYTES = 4096;       // at the start of a run: [0] finished items, [1 + item] workgroups that arrived
-constexpr int SPLIT_MAX_UNITS = (SPLIT_HEADER_BYTES + SPLIT_MAX_WGS * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES;
-static_assert((1 + SPLIT_MAX_ITEMS) * 4 <= SPLIT_HEADER_BYTES && SPLIT_MAX_ITEMS <= NTHREADS, "header holds a counter per item");
-static_assert(SPLIT_MAX_UNITS <= POOL_UNITS / 4, "several launches fit the pool");
-// The one lane that takes a run of n units: first free run, or POOL_NONE.
-__device__ inline uint32_t pool_take(int n)
-{
-    if (!ATTN_POOL) return POOL_NONE;
-    const unsigned long long run = (1ull << n) - 1;     // n < 64
-    unsigned long long taken = 0;       // (a guess that is usually right: one round trip to memory)
-    int tries = 0;
-    for (int u = 0; u + n <= POOL_UNITS;) {
-        if (taken & (run << u)) { ++u; continue; }
-        if (__hip_atomic_compare_exchange_strong(&g_pool_taken, &taken, taken | (run << u), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT))
-            return (uint32_t)u;
-        // the mask is another one, `taken` holds it now: look at u again, but not more than POOL_UNITS times in all
-        if (++tries == POOL_UNITS) break;
-    }
-    return POOL_NONE;
-}
-// Partial results pass between workgroups of one launch that may sit on different XCDs, each with an L2 of its
-// own.  They are written and read at agent scope element by element (sc1: through the L2 to memory that all
-// XCDs share), and a wait for the stores stands before the counter that announces them.  An agent-scope release
-// fence instead writes back an XCD's whole L2 for every workgroup: measured 0.17 us each, one after the other
-// (512 workgroups: 80 us).
-__device__ inline void pool_store4(unsigned char *at, float a, float b, float c, float d)
-{
-    typedef unsigned long long u64;
-    const u64 lo = (u64)__float_as_uint(a) | (u64)__float_as_uint(b) << 32, hi = (u64)__float_as_uint(c) | (u64)__float_as_uint(d) << 32;
-    __hip_atomic_store((u64 *)at, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store((u64 *)at + 1, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline void pool_load4(const unsigned char *at, float *x)
-{
-    typedef unsigned long long u64;
-    const u64 lo = __hip_atomic_load((const u64 *)at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const u64 hi = __hip_atomic_load((const u64 *)at + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    x[0] = __uint_as_float((uint32_t)lo); x[1] = __uint_as_float((uint32_t)(lo >> 32));
-    x[2] = __uint_as_float((uint32_t)hi); x[3] = __uint_as_float((uint32_t)(hi >> 32));
-}
-__device__ inline void pool_store(float *at, float a) { __hip_atomic_store(at, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline float pool_load(const float *at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline void pool_give(uint32_t u, int n)
-{
-    __hip_atomic_fetch_and(&g_pool_taken, ~(((1ull << n) - 1) << u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 constexpr int SPLIT_KEYS = 32;                                  // keys per block of the split kernel
 constexpr int SPLIT_TILE_BYTES = SPLIT_KEYS * ROW_BYTES;        // 8 KiB: one K or V block
 constexpr int SPLIT_WAVE_BYTES = 2 * SPLIT_TILE_BYTES;          // per wavefront: its K block, then its V block
@@ -1233,7 +1551,7 @@ static_assert(SPLIT_Q_BASE % 1024 == 0 && NWAVES * 4 == 32, "each wavefront requ
 static_assert(SPLIT_WAVE_BYTES == 32 * HD * 4, "a wavefront's partial accumulator takes the place of its two blocks");
 static_assert(SPLIT_LDS_BYTES <= LDS_BYTES, "the split kernel is launched with the same dynamic LDS size");
 
-template <bool CAUSAL, bool NEG>
+template <bool CAUSAL>
 __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitParams p)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -1263,10 +1581,10 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
         const int items = p.nrest * p.ntile;
         if (unit != POOL_NONE) {
             uint32_t *header = (uint32_t *)(g_pool + (size_t)unit * POOL_UNIT_BYTES);
-            if (tid <= items) header[tid] = 0;
+            for (int i = tid; i <= items * p.reserve; i += NTHREADS) header[i] = 0;
         }
-        if (tid < items)
-            ((uint32_t *)p.lse)[item_lse(tid % p.nrest, tid / p.nrest * p.tile_pos)] = pool_mark(unit);
+        for (int i = tid; i < items; i += NTHREADS)
+            ((uint32_t *)p.lse)[item_lse(i % p.nrest, i / p.nrest * p.tile_pos)] = pool_mark(unit);
         return;
     }
     const int tile_r = fast_div(bid, p.d_nrs), rest_s = bid - tile_r * (p.nrest * p.splits);
@@ -1380,6 +1698,12 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
 #pragma unroll
     for (int s = 0; s < 8; ++s)
         qf[s] = *(const LDS_AS bf16x8 *)(lds + SPLIT_Q_BASE + l32 * ROW_BYTES + (((2 * s + hh) ^ (l32 & 15)) << 4));
+    // a negative scale: the negated Q (exact) with the scale's absolute value
+    const float c = fabsf(p.c);
+    if (p.c < 0.0f) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) qf[s] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, qf[s]) ^ 0x80008000u);
+    }
 
     // Blocks first + wave, first + wave + 8, ...: K(t) and V(t) were requested above (this wavefront's first block); K(t + 8) goes out as soon as the
     // score MFMAs have read K(t), V(t + 8) as soon as the PV MFMAs have read V(t), so that a wait is "all
@@ -1402,15 +1726,14 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
         int lim = p.Skv - 1;
         if (CAUSAL) lim = min(lim, qpos + off);
         const int kidx = t * SPLIT_KEYS + 4 * hh;
-        constexpr float NONE = NEG ? INFINITY : -INFINITY;
-        float mx = NONE;
+        float mx = -INFINITY;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int key = kidx + 8 * (r >> 2) + (r & 3);
-            mx = ext2<NEG>(mx, key <= lim ? s[r] : NONE);
+            mx = fmaxf(mx, key <= lim ? s[r] : -INFINITY);
         }
-        mx = lane32_ext<NEG>(mx);
-        mx = (mx == NONE) ? -INFINITY : mx * p.c;
+        mx = lane32_ext<false>(mx);
+        mx = (mx == -INFINITY) ? -INFINITY : mx * c;
         if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
             const float mn = fmaxf(m, mx);
             const float alpha = (mn == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - mn);
@@ -1428,8 +1751,8 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
 #pragma unroll
         for (int r = 0; r < 16; r += 2) {
             const int key = kidx + 8 * (r >> 2) + (r & 3);
-            float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], p.c, -mu));
-            float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r + 1], p.c, -mu));
+            float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -mu));
+            float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r + 1], c, -mu));
             e0 = (key <= lim) ? e0 : 0.0f;
             e1 = (key + 1 <= lim) ? e1 : 0.0f;
             ls += e0 + e1;
@@ -1601,6 +1924,37 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
 #endif
 }
 
+// Key blocks of 64 of a 256-row item, as the kernel counts them.
+int item_blocks(const Params &p, bool causal, int tile)
+{
+    const int n = (p.Skv + BN - 1) / BN;
+    if (!causal) return n;
+    const int end = tile * p.shape.tile_pos + p.shape.tile_pos;
+    const int klast = (end < p.shape.Sq ? end : p.shape.Sq) - 1 + p.Skv - p.shape.Sq;
+    return klast < 0 ? 0 : klast / BN + 1 < n ? klast / BN + 1 : n;
+}
+// What the longest workgroup of a launch of whole items takes, in blocks with `extra` for each item; the XCDs are dealt
+// alike, and none more than the first.
+int whole_items_length(const Params &p, bool causal, int extra)
+{
+    const Sched &sc = p.sched;
+    if (!causal) return (sc.per_xcd + sc.slots - 1) / sc.slots * (item_blocks(p, false, 0) + extra);
+    int longest = 0;
+    for (int slot = 0; slot < sc.slots; ++slot) {
+        int sum = 0;
+        for (int r = 0; r * sc.slots < sc.per_xcd; ++r) {
+            const int j = r * sc.slots + ((r & 1) ? sc.slots - 1 - slot : slot);
+            if (j >= sc.per_xcd) continue;
+            const int w = j / sc.per_win, i = j - w * sc.per_win;
+            const int kw = sc.window < sc.sgx - w * sc.window ? sc.window : sc.sgx - w * sc.window;
+            const int tile_r = i / kw * sc.split + ((w * sc.window + i % kw) & (sc.split - 1));
+            if (tile_r < sc.ntile) sum += item_blocks(p, true, sc.ntile - 1 - tile_r) + extra;
+        }
+        longest = sum > longest ? sum : longest;
+    }
+    return longest;
+}
+
 // Workgroups that share one item of the split-key kernel, whose key sequence is `blocks` blocks of 32 keys.
 // One workgroup takes about 5 us + 1.3 us per 8 blocks as long as memory keeps up (measured, 8 items: 7.0 us at 16 blocks,
 // 15.0 at 64, 43 at 256, 189 at 1024); sharing an item adds about 4 us for the reserving launch and
@@ -1614,6 +1968,38 @@ int split_parts(int64_t items, int blocks, int ncu)
     int s = 1;
     while ((s + 1) * items <= (ncu < SPLIT_MAX_WGS ? ncu : SPLIT_MAX_WGS) && 5 * (s + 1) * (s + 1) <= 2 * blocks) ++s;
     return s;
+}
+
+// Estimates, in ns, of the three ways to run a launch; they only choose among them.  Measured (us, whole items or split-key
+// kernel / shared): 128 items x 32 blocks 42.5 / 42.5, 192 x 24 45.3 / 55.0, 400 x 19 68.7 / 75.4, 576 x 47 229.6 / 208.1, 128 x 128
+// 150 / 124; causal: 128 items, 2048 x 2048 43.5 / 37.0; 256, 16384 x 16384 324 / 248; 384, 3000 x 3000 82.0 / 86.1; 640, 5000 x 5000
+// 220 / 203; 512, 32768 x 32768 889 / 899; split-key: 64 items, 512 x 16384 234 / 140; 48, 700 x 20000 224 / 123; 64, 4096 x 4096 (not
+// causal) 60.7 / 49.7; 32, 200 x 8000 48.8 / 52.6; 8, 64 x 30000 57.3 / 87.9.
+//
+// Shared: the chip is full and at the clock that goes with it; 17 us for the launch in front and the parts, 1 us for each
+// part of an item beyond the second.
+int64_t shared_ns(const Params &p, int64_t items)
+{
+    const Share &sr = p.share;
+    const int64_t more = sr.wgs / items > 1 ? sr.wgs / items - 2 : 0;
+    return 17000 + 1650 * (int64_t)sr.total / sr.wgs + 1000 * more;
+}
+// Whole items: a block takes 1.15 us where half of the chip idles and leaves its power to the other half, 1.55 where three
+// quarters are busy.
+int64_t whole_items_ns(const Params &p, bool causal)
+{
+    const Share &sr = p.share;
+    const int64_t longest = whole_items_length(p, causal, sr.extra);
+    const int64_t busy = 1000 * (int64_t)sr.total / (sr.wgs * longest);     // per mille
+    const int64_t over = busy < 500 ? 0 : busy > 750 ? 250 : busy - 500;
+    return (1150 + over * 400 / 250) * longest;
+}
+// Split-key kernel: as at split_parts.
+int64_t split_ns(int64_t items, int64_t blocks, int ncu)
+{
+    const int parts = split_parts(items, (int)blocks, ncu);
+    const int64_t rounds = (items * parts + ncu - 1) / ncu;
+    return (5000 + 163 * blocks / parts) * rounds + (parts > 1 ? 4000 + 250 * parts : 0);
 }
 
 }  // namespace
@@ -1663,77 +2049,29 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
     if (!cus[dev].load(std::memory_order_acquire)) {
         int n = 0;
         if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0 ||
-            hipFuncSetAttribute((const void *)attn_fwd_kernel<true, false>,
+            hipFuncSetAttribute((const void *)attn_fwd_kernel<true, FORM_POS>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess ||
-            hipFuncSetAttribute((const void *)attn_fwd_kernel<false, false>,
+            hipFuncSetAttribute((const void *)attn_fwd_kernel<true, FORM_NEG>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess ||
-            hipFuncSetAttribute((const void *)attn_fwd_kernel<true, true>,
+            hipFuncSetAttribute((const void *)attn_fwd_kernel<true, FORM_SHARED>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess ||
-            hipFuncSetAttribute((const void *)attn_fwd_kernel<false, true>,
+            hipFuncSetAttribute((const void *)attn_fwd_kernel<false, FORM_POS>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess ||
-            hipFuncSetAttribute((const void *)attn_fwd_split_kernel<true, false>,
+            hipFuncSetAttribute((const void *)attn_fwd_kernel<false, FORM_NEG>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess ||
+            hipFuncSetAttribute((const void *)attn_fwd_kernel<false, FORM_SHARED>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess ||
+            hipFuncSetAttribute((const void *)attn_fwd_split_kernel<true>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, SPLIT_LDS_BYTES) != hipSuccess ||
-            hipFuncSetAttribute((const void *)attn_fwd_split_kernel<false, false>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, SPLIT_LDS_BYTES) != hipSuccess ||
-            hipFuncSetAttribute((const void *)attn_fwd_split_kernel<true, true>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, SPLIT_LDS_BYTES) != hipSuccess ||
-            hipFuncSetAttribute((const void *)attn_fwd_split_kernel<false, true>,
+            hipFuncSetAttribute((const void *)attn_fwd_split_kernel<false>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, SPLIT_LDS_BYTES) != hipSuccess)
             return ATTN_E_LAUNCH;
         cus[dev].store(n, std::memory_order_release);
     }
     const int ncu = cus[dev].load(std::memory_order_relaxed);
-    hipStream_t st = (hipStream_t)stream;
-    // a negative scale turns the running maximum of the scaled scores into c times the smallest raw score
-    const bool neg = scale < 0.0f;
-
-    // Small problems: few 256-row items would leave most compute units idle, and items of few rows (the
-    // query heads of one group times the positions of the sequence) most of each item's rows; 32-row items whose keys
-    // are shared out among the wavefronts of a workgroup, and among workgroups, fill the device instead.
-    // Few rows, measured, 256-row / split-key kernel, us: 4 rows x 4000 keys, 128 items 77.9 / 42.4; 4 x 4096, 512 items
-    // 240.8 / 184.1 (1.07 GB of K and V); 4 x 500, 512 items 35.6 / 24.1; 1 x 8000, 256 items 232.9 / 175.2.
-    const int split_tile_pos = 32 / sh.pack;
-    const int64_t split_items = (int64_t)B * Hkv * sh.chunks * ((Sq + split_tile_pos - 1) / split_tile_pos);
-    const bool few_rows = (int64_t)Sq * sh.pack <= 64;
-    const bool small = ATTN_SMALL_PATH == 2 || (ATTN_SMALL_PATH == 1 && (total * 4 <= ncu || few_rows));
-    if (small && split_items < INT32_MAX) {
-        SplitParams sp = {};
-        sp.q = p.q; sp.k = p.k; sp.v = p.v; sp.o = p.o; sp.lse = lse;
-        sp.Hq = Hq; sp.Hkv = Hkv; sp.Sq = Sq; sp.Skv = Skv; sp.G = sh.G;
-        sp.pack = sh.pack; sp.pack_log2 = sh.pack_log2; sp.chunks = sh.chunks;
-        sp.tile_pos = split_tile_pos;
-        sp.ntile = (Sq + split_tile_pos - 1) / split_tile_pos;
-        sp.nrest = (int)((int64_t)B * Hkv * sh.chunks);
-        sp.splits = split_parts(split_items, (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS, ncu);
-        sp.d_nrs = make_div((uint32_t)(sp.nrest * sp.splits));
-        sp.d_splits = make_div((uint32_t)sp.splits);
-        sp.d_chunks = make_div((uint32_t)sp.chunks);
-        sp.d_hkv = make_div((uint32_t)Hkv);
-        sp.c = p.c;
-        auto launch = [&](unsigned wgs, int lds) {
-            const dim3 sgrid(wgs), sblock(NTHREADS);
-            if (causal && neg)
-                hipLaunchKernelGGL((attn_fwd_split_kernel<true, true>), sgrid, sblock, lds, st, sp);
-            else if (causal)
-                hipLaunchKernelGGL((attn_fwd_split_kernel<true, false>), sgrid, sblock, lds, st, sp);
-            else if (neg)
-                hipLaunchKernelGGL((attn_fwd_split_kernel<false, true>), sgrid, sblock, lds, st, sp);
-            else
-                hipLaunchKernelGGL((attn_fwd_split_kernel<false, false>), sgrid, sblock, lds, st, sp);
-        };
-        if (sp.splits > 1) {
-            sp.units = (int)((SPLIT_HEADER_BYTES + split_items * sp.splits * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
-            sp.reserve = 1;
-            launch(1, 1024);
-            if (hipGetLastError() != hipSuccess) return ATTN_E_LAUNCH;
-            sp.reserve = 0;
-        }
-        launch((unsigned)(split_items * sp.splits), SPLIT_LDS_BYTES);
-        return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_E_LAUNCH;
-    }
-
-    // One workgroup per CU (a workgroup takes all of a CU's registers and LDS), each working through a list.
     const int cu_slots = ncu >= 8 ? ncu / 8 : 1;
+    hipStream_t st = (hipStream_t)stream;
+    // One workgroup per CU (a workgroup takes all of a CU's registers and LDS), each working through a list.
     sc.per_xcd = (int)((total + 7) / 8);
     sc.split = sc.nsub = sc.sgx = sc.window = 1;
     sc.split_log2 = 0;
@@ -1750,15 +2088,106 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
     sc.d_per_win = make_div((uint32_t)sc.per_win);
     sc.d_window = make_div((uint32_t)sc.window);
     sc.slots = sc.per_xcd < cu_slots ? sc.per_xcd : cu_slots;
-    const dim3 grid((unsigned)(sc.slots * 8)), block(NTHREADS);
+
+    const int split_tile_pos = 32 / sh.pack;
+    const int64_t split_items = (int64_t)B * Hkv * sh.chunks * ((Sq + split_tile_pos - 1) / split_tile_pos);
+    // The same work as a line cut into equal stretches.  From 4 items per compute unit on, whole items leave at most a fifth of the chip idle at the
+    // end, and sharing has not been faster.  (5 %: what the estimates are worth.)
+    Share &sr = p.share;
+    sr.wgs = 8 * cu_slots;
+    sr.groups = (int)((int64_t)B * Hkv * sh.chunks);
+    sr.extra = causal ? SHARE_EXTRA_CAUSAL : SHARE_EXTRA;
+    bool share = false;
+    if (ATTN_SHARE != 0 && total <= (ATTN_SHARE == 2 ? SHARE_MAX_ITEMS : 4 * ncu) && total <= SHARE_MAX_ITEMS && sr.wgs <= SHARE_MAX_WGS) {
+        int64_t len = 0;
+        for (int t = 0; t < sc.ntile; ++t) len += item_blocks(p, causal, t) + sr.extra;
+        const int64_t line = len * sr.groups;
+        if (line * sr.wgs < INT32_MAX && line >= 8 * (sr.extra + 2 * SHARE_MIN_PART - 1)) {
+            sr.group_len = (int)len;
+            sr.total = (int)line;
+            const int most = sr.total / (sr.extra + 2 * SHARE_MIN_PART - 1) / 8 * 8;
+            if (sr.wgs > most) sr.wgs = most;
+            const int64_t slots = sr.wgs + (total < sr.wgs ? total : sr.wgs);
+            sr.units = (int)((SHARE_HEADER_BYTES + slots * SHARE_SLOT_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
+            const int64_t blocks32 = (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS;
+            const int64_t whole = total * 4 <= ncu && ATTN_SMALL_PATH == 1 ? split_ns(split_items, blocks32, ncu)
+                                                                           : whole_items_ns(p, causal != 0);
+            share = ATTN_SHARE == 2 || shared_ns(p, total) * 105 < whole * 100;
+        }
+    }
+
+    // a negative scale turns the running maximum of the scaled scores into c times the smallest raw score
+    const bool neg = scale < 0.0f;
+
+    // Small problems: few 256-row items would leave most compute units idle, and items of few rows (the
+    // query heads of one group times the positions of the sequence) most of each item's rows; 32-row items whose keys
+    // are shared out among the wavefronts of a workgroup, and among workgroups, fill the device instead.
+    // Few rows, measured, 256-row / split-key kernel, us: 4 rows x 4000 keys, 128 items 77.9 / 42.4; 4 x 4096, 512 items
+    // 240.8 / 184.1 (1.07 GB of K and V); 4 x 500, 512 items 35.6 / 24.1; 1 x 8000, 256 items 232.9 / 175.2.
+    const bool few_rows = (int64_t)Sq * sh.pack <= 64;
+    const bool small = ATTN_SMALL_PATH == 2 || (ATTN_SMALL_PATH == 1 && ((total * 4 <= ncu && !share) || few_rows));
+    auto launch_split = [&](const SplitParams &sp, unsigned wgs, int lds) {
+        const dim3 sgrid(wgs), sblock(NTHREADS);
+        if (causal)
+            hipLaunchKernelGGL(attn_fwd_split_kernel<true>, sgrid, sblock, lds, st, sp);
+        else
+            hipLaunchKernelGGL(attn_fwd_split_kernel<false>, sgrid, sblock, lds, st, sp);
+    };
+    if (small && split_items < INT32_MAX) {
+        SplitParams sp = {};
+        sp.q = p.q; sp.k = p.k; sp.v = p.v; sp.o = p.o; sp.lse = lse;
+        sp.Hq = Hq; sp.Hkv = Hkv; sp.Sq = Sq; sp.Skv = Skv; sp.G = sh.G;
+        sp.pack = sh.pack; sp.pack_log2 = sh.pack_log2; sp.chunks = sh.chunks;
+        sp.tile_pos = split_tile_pos;
+        sp.ntile = (Sq + split_tile_pos - 1) / split_tile_pos;
+        sp.nrest = (int)((int64_t)B * Hkv * sh.chunks);
+        sp.splits = split_parts(split_items, (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS, ncu);
+        sp.d_nrs = make_div((uint32_t)(sp.nrest * sp.splits));
+        sp.d_splits = make_div((uint32_t)sp.splits);
+        sp.d_chunks = make_div((uint32_t)sp.chunks);
+        sp.d_hkv = make_div((uint32_t)Hkv);
+        sp.c = p.c;
+        if (sp.splits > 1) {
+            sp.units = (int)((SPLIT_HEADER_BYTES + split_items * sp.splits * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
+            sp.reserve = 1;
+            launch_split(sp, 1, 1024);
+            if (hipGetLastError() != hipSuccess) return ATTN_E_LAUNCH;
+            sp.reserve = 0;
+        }
+        launch_split(sp, (unsigned)(split_items * sp.splits), SPLIT_LDS_BYTES);
+        return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_E_LAUNCH;
+    }
+
+    const dim3 block(NTHREADS);
+    if (share) {
+        SplitParams sp = {};
+        sp.lse = lse;
+        sp.Hq = Hq; sp.Hkv = Hkv; sp.Sq = Sq; sp.G = sh.G;
+        sp.pack = sh.pack; sp.chunks = sh.chunks;
+        sp.tile_pos = sh.tile_pos;
+        sp.ntile = sc.ntile;
+        sp.nrest = sr.groups;
+        sp.d_chunks = sh.d_chunks;
+        sp.d_hkv = sh.d_hkv;
+        sp.units = sr.units;
+        sp.reserve = NWAVES;
+        launch_split(sp, 1, 1024);
+        if (hipGetLastError() != hipSuccess) return ATTN_E_LAUNCH;
+        if (causal)
+            hipLaunchKernelGGL((attn_fwd_kernel<true, FORM_SHARED>), dim3(sr.wgs), block, LDS_BYTES, st, p);
+        else
+            hipLaunchKernelGGL((attn_fwd_kernel<false, FORM_SHARED>), dim3(sr.wgs), block, LDS_BYTES, st, p);
+        return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_E_LAUNCH;
+    }
+    const dim3 grid((unsigned)(sc.slots * 8));
     if (causal && neg)
-        hipLaunchKernelGGL((attn_fwd_kernel<true, true>), grid, block, LDS_BYTES, st, p);
+        hipLaunchKernelGGL((attn_fwd_kernel<true, FORM_NEG>), grid, block, LDS_BYTES, st, p);
     else if (causal)
-        hipLaunchKernelGGL((attn_fwd_kernel<true, false>), grid, block, LDS_BYTES, st, p);
+        hipLaunchKernelGGL((attn_fwd_kernel<true, FORM_POS>), grid, block, LDS_BYTES, st, p);
     else if (neg)
-        hipLaunchKernelGGL((attn_fwd_kernel<false, true>), grid, block, LDS_BYTES, st, p);
+        hipLaunchKernelGGL((attn_fwd_kernel<false, FORM_NEG>), grid, block, LDS_BYTES, st, p);
     else
-        hipLaunchKernelGGL((attn_fwd_kernel<false, false>), grid, block, LDS_BYTES, st, p);
+        hipLaunchKernelGGL((attn_fwd_kernel<false, FORM_POS>), grid, block, LDS_BYTES, st, p);
     return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_E_LAUNCH;
 }
 
