@@ -86,22 +86,32 @@ def attention(q, k, v, causal=False, scale=None):
     Returns (O BF16 [B,Sq,Hq,D], LSE FP32 [B,Hq,Sq]).
     """
     import torch
+    from torch._C import _cuda_getCurrentRawStream
     if not (q.is_cuda and k.is_cuda and v.is_cuda):
         raise ValueError("attention() needs device tensors; there is no CPU path")
+    bf16 = torch.bfloat16
     for t in (q, k, v):
-        if t.dtype != torch.bfloat16 or not t.is_contiguous() or t.dim() != 4:
+        if t.dtype != bf16 or not t.is_contiguous() or t.dim() != 4:
             raise ValueError("q, k, v must be contiguous 4-d BF16 tensors [B, S, H, D]")
     B, Sq, Hq, D = q.shape
-    Bk, Skv, Hkv, Dk = k.shape
-    if (Bk, Dk) != (B, D) or v.shape != k.shape:
+    kv_shape = k.shape
+    Bk, Skv, Hkv, Dk = kv_shape
+    if (Bk, Dk) != (B, D) or v.shape != kv_shape:
         raise ValueError("inconsistent q/k/v shapes")
     if scale is None:
         scale = D ** -0.5
     o = torch.empty_like(q)
     lse = torch.empty((B, Hq, Sq), dtype=torch.float32, device=q.device)
-    with torch.cuda.device(q.device):
-        rc = attn_fwd(q, k, v, o, lse, B, Hq, Hkv, Sq, Skv, D, causal, scale,
-                      torch.cuda.current_stream().cuda_stream)
+    # The raw stream handle, and no change of device where q's is the current one: the Stream object and the device
+    # context of the general form cost more than the launch itself.
+    index = q.get_device()
+    args = (q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), B, Hq, Hkv, Sq, Skv, D,
+            1 if causal else 0, float(scale), _cuda_getCurrentRawStream(index))
+    if index == torch.cuda.current_device():
+        rc = load().attn_fwd(*args)
+    else:
+        with torch.cuda.device(index):
+            rc = load().attn_fwd(*args)
     if rc != ATTN_OK:
         raise AttnError(rc)
     return o, lse
