@@ -1,0 +1,298 @@
+// Which kernel a call of attn_fwd() goes to and how its work is cut up: plain host arithmetic on sizes, without a device
+// and without HIP, so that it can be compiled and checked on its own.
+#ifndef PAPER_2603_24517_ATTN_ROUTE_H
+#define PAPER_2603_24517_ATTN_ROUTE_H
+
+#include <stdint.h>
+
+#include "../../include/attn.h"
+
+// ATTN_SMALL_PATH: which launches go to the split-key kernel for small problems (at the end of this
+// file): 1 (shipped) those whose 256-row work items would occupy at most a quarter of the compute
+// units and those of few query rows; 0 none; 2 all.
+#ifndef ATTN_SMALL_PATH
+#define ATTN_SMALL_PATH 1
+#endif
+// ATTN_SHARE: which launches of the 256-row kernel share items among workgroups: 1 (shipped) those that it makes
+// shorter; 0 none; 2 all that the device memory for it can serve.
+#ifndef ATTN_SHARE
+#define ATTN_SHARE 1
+#endif
+
+namespace attn {
+
+constexpr int HD = 128;              // head dimension
+constexpr int BN = 64;               // keys per K/V block
+constexpr int NWAVES = 8;            // wavefronts per workgroup; one workgroup fills a CU (registers and LDS)
+constexpr int NTHREADS = NWAVES * 64;
+constexpr int WG_ROWS = NWAVES * 32; // query rows per workgroup
+constexpr int SPLIT_KEYS = 32;                                  // keys per block of the split kernel
+
+// Exact n / d for 0 <= n < 2^31 as a multiply-high, an add and a shift.
+struct Div { uint32_t mul, shift; };
+inline Div make_div(uint32_t d) {
+    Div r;
+    r.shift = 0;
+    while ((1u << r.shift) < d) ++r.shift;
+    r.mul = (uint32_t)((((uint64_t)1 << 32) * (((uint64_t)1 << r.shift) - d)) / d + 1);
+    return r;
+}
+
+// How the work items are dealt out (read by the per-item code only).
+struct Sched {
+    int total;      // work items = B * Hkv * chunks * ntile
+    int per_xcd;    // entries in the work list of one XCD (non-causal: ceil(total / 8))
+    int slots;      // workgroups per XCD in this launch (one per CU); the grid is 8 * slots
+    int ntile;      // ceil(Sq / tile_pos)
+    // causal only: how the (group, tile) pairs are dealt to the XCDs (a group = one batch entry, K/V head and chunk)
+    int split;      // every group is cut into `split` sub-groups (a power of two), sub-group r holding the tiles t = r (mod split)
+    int split_log2;
+    int nsub;       // tiles per sub-group = ceil(ntile / split); the padding entries are skipped
+    int sgx;        // sub-groups per XCD = groups * split / 8
+    int window;     // sub-groups that one XCD works through together, longest tiles of all of them first
+    int per_win;    // window * nsub
+    Div d_ntile, d_per_win, d_window;
+};
+// How the work items are shared (SHARED kernels only).  The items stand in a line, (group, tile) with tiles
+// fastest, each as long as its key blocks plus `extra`, and workgroup w takes what lies between cut(w) and
+// cut(w + 1), cut(w) = w * total / wgs, moved to an item's end or start where it would leave a part of fewer than
+// SHARE_MIN_PART blocks.
+struct Share {
+    int total;      // length of the line; total * wgs < 2^31
+    int wgs;        // workgroups of the launch (a multiple of 8); total / wgs >= extra + 2 SHARE_MIN_PART - 1, so that each has a part
+    int groups;     // B * Hkv * chunks
+    int group_len;  // total / groups
+    int extra;      // what an item costs beside its blocks, in blocks
+    int units;      // POOL_UNIT_BYTES units of device memory
+};
+constexpr int SHARE_MIN_PART = 2;
+// Beside its blocks an item costs about 8400 cycles (a block: 2560), and under the causal mask four masked blocks
+// of 1300 cycles more each, not all of which the cut falls on.
+constexpr int SHARE_EXTRA = 3, SHARE_EXTRA_CAUSAL = 5;
+// Tensor shape and head packing (read by the per-item code only).
+struct Shape {
+    int Sq, Hq;
+    int G;          // Hq / Hkv
+    int pack;       // query heads of one K/V group served by one workgroup (1, 2, 4 or 8)
+    int pack_log2;
+    int tile_pos;   // query positions per workgroup = WG_ROWS / pack
+    int chunks;     // G / pack
+    Div d_chunks, d_hkv;
+};
+// How the split-key kernel's work is cut up.
+struct Split {
+    int tile_pos;           // query positions per work item = 32 / pack
+    int ntile;              // ceil(Sq / tile_pos)
+    int nrest;              // B * Hkv * chunks; items = ntile * nrest
+    int splits;             // workgroups that share an item
+    int units;              // POOL_UNIT_BYTES units of device memory, 0 if splits == 1
+};
+
+// Device memory for partial results (g_pool of the kernels): sizes of its units, and of what a launch keeps there.
+constexpr int POOL_UNITS = 64;
+constexpr uint32_t POOL_UNIT_BYTES = 4u << 20;
+constexpr int SPLIT_MAX_ITEMS = 256;                // of a launch with splits > 1
+constexpr int SPLIT_MAX_WGS = 512;                  // items * splits of such a launch
+constexpr int SPLIT_PART_BYTES = 32 * HD * 4 + 3 * 32 * 4;          // one partial result: accumulator, m, l, lr
+constexpr uint32_t SPLIT_HEADER_BYTES = 4096;       // at the start of a run: [0] finished items, [1 + item] workgroups that arrived
+constexpr int SPLIT_MAX_UNITS = (SPLIT_HEADER_BYTES + SPLIT_MAX_WGS * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES;
+static_assert((1 + SPLIT_MAX_ITEMS) * 4 <= SPLIT_HEADER_BYTES, "header holds a counter per item");
+static_assert(SPLIT_MAX_UNITS <= POOL_UNITS / 4, "several launches fit the pool");
+// 256-row kernel: a wavefront's part is its accumulator, then m, l, lr, as 17 16-byte pieces per lane.
+constexpr uint32_t SHARE_WAVE_BYTES = 17 * 64 * 16;
+constexpr uint32_t SHARE_SLOT_BYTES = NWAVES * SHARE_WAVE_BYTES;    // 136 KiB: one part of an item
+constexpr uint32_t SHARE_HEADER_BYTES = 64 * 1024;  // [0] workgroups that left, [1 + 8 item + wave] parts that arrived
+constexpr int SHARE_MAX_ITEMS = 2047;
+constexpr int SHARE_MAX_WGS = 256;                  // two slots each at most: one that starts with its item, one that does not
+constexpr int SHARE_MAX_UNITS = (SHARE_HEADER_BYTES + 2 * SHARE_MAX_WGS * SHARE_SLOT_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES;
+static_assert((1 + SHARE_MAX_ITEMS * NWAVES) * 4 <= SHARE_HEADER_BYTES, "header holds a counter per item and wavefront");
+static_assert(SHARE_MAX_UNITS <= POOL_UNITS / 3, "several launches fit the pool");
+
+enum RouteKind { ROUTE_WHOLE, ROUTE_SHARED, ROUTE_SPLIT };     // 256-row kernel, its shared form, split-key kernel
+struct Route {
+    RouteKind kind;
+    int Skv;
+    Shape shape;
+    Sched sched;
+    Share share;
+    Split split;
+};
+
+// Key blocks of 64 of a 256-row item, as the kernel counts them.
+inline int item_blocks(const Route &p, bool causal, int tile)
+{
+    const int n = (p.Skv + BN - 1) / BN;
+    if (!causal) return n;
+    const int end = tile * p.shape.tile_pos + p.shape.tile_pos;
+    const int klast = (end < p.shape.Sq ? end : p.shape.Sq) - 1 + p.Skv - p.shape.Sq;
+    return klast < 0 ? 0 : klast / BN + 1 < n ? klast / BN + 1 : n;
+}
+// What the longest workgroup of a launch of whole items takes, in blocks with `extra` for each item; the XCDs are dealt
+// alike, and none more than the first.
+inline int whole_items_length(const Route &p, bool causal, int extra)
+{
+    const Sched &sc = p.sched;
+    if (!causal) return (sc.per_xcd + sc.slots - 1) / sc.slots * (item_blocks(p, false, 0) + extra);
+    int longest = 0;
+    for (int slot = 0; slot < sc.slots; ++slot) {
+        int sum = 0;
+        for (int r = 0; r * sc.slots < sc.per_xcd; ++r) {
+            const int j = r * sc.slots + ((r & 1) ? sc.slots - 1 - slot : slot);
+            if (j >= sc.per_xcd) continue;
+            const int w = j / sc.per_win, i = j - w * sc.per_win;
+            const int kw = sc.window < sc.sgx - w * sc.window ? sc.window : sc.sgx - w * sc.window;
+            const int tile_r = i / kw * sc.split + ((w * sc.window + i % kw) & (sc.split - 1));
+            if (tile_r < sc.ntile) sum += item_blocks(p, true, sc.ntile - 1 - tile_r) + extra;
+        }
+        longest = sum > longest ? sum : longest;
+    }
+    return longest;
+}
+
+// Workgroups that share one item of the split-key kernel, whose key sequence is `blocks` blocks of 32 keys.
+// One workgroup takes about 5 us + 1.3 us per 8 blocks as long as memory keeps up (measured, 8 items: 7.0 us at 16 blocks,
+// 15.0 at 64, 43 at 256, 189 at 1024); sharing an item adds about 4 us for the reserving launch and
+// 0.25 us per part to merge, so the sum is least at parts^2 = 0.65 blocks (measured, 8 items: 64 blocks 12.5 us
+// with 4 parts, 12.8 with 8; 256 blocks 17.4 with 8 or 16, 20.1 with 24; 1024 blocks 32.9 with 16, 36.2 with 32) and
+// not worth it below 40 blocks (32 blocks, 16 blocks: 10 and 7 us in one part, 11 in two).
+// More workgroups than compute units start a second round: 160 items in two parts 26.5 us, in one 16.2.
+inline int split_parts(int64_t items, int blocks, int ncu)
+{
+    if (items > SPLIT_MAX_ITEMS || blocks < 40) return 1;
+    int s = 1;
+    while ((s + 1) * items <= (ncu < SPLIT_MAX_WGS ? ncu : SPLIT_MAX_WGS) && 5 * (s + 1) * (s + 1) <= 2 * blocks) ++s;
+    return s;
+}
+
+// Estimates, in ns, of the three ways to run a launch; they only choose among them.  Measured (us, whole items or split-key
+// kernel / shared): 128 items x 32 blocks 42.5 / 42.5, 192 x 24 45.3 / 55.0, 400 x 19 68.7 / 75.4, 576 x 47 229.6 / 208.1, 128 x 128
+// 150 / 124; causal: 128 items, 2048 x 2048 43.5 / 37.0; 256, 16384 x 16384 324 / 248; 384, 3000 x 3000 82.0 / 86.1; 640, 5000 x 5000
+// 220 / 203; 512, 32768 x 32768 889 / 899; split-key: 64 items, 512 x 16384 234 / 140; 48, 700 x 20000 224 / 123; 64, 4096 x 4096 (not
+// causal) 60.7 / 49.7; 32, 200 x 8000 48.8 / 52.6; 8, 64 x 30000 57.3 / 87.9.
+//
+// Shared: the chip is full and at the clock that goes with it; 17 us for the launch in front and the parts, 1 us for each
+// part of an item beyond the second.
+inline int64_t shared_ns(const Route &p, int64_t items)
+{
+    const Share &sr = p.share;
+    const int64_t more = sr.wgs / items > 1 ? sr.wgs / items - 2 : 0;
+    return 17000 + 1650 * (int64_t)sr.total / sr.wgs + 1000 * more;
+}
+// Whole items: a block takes 1.15 us where half of the chip idles and leaves its power to the other half, 1.55 where three
+// quarters are busy.
+inline int64_t whole_items_ns(const Route &p, bool causal)
+{
+    const Share &sr = p.share;
+    const int64_t longest = whole_items_length(p, causal, sr.extra);
+    const int64_t busy = 1000 * (int64_t)sr.total / (sr.wgs * longest);     // per mille
+    const int64_t over = busy < 500 ? 0 : busy > 750 ? 250 : busy - 500;
+    return (1150 + over * 400 / 250) * longest;
+}
+// Split-key kernel: as at split_parts.
+inline int64_t split_ns(int64_t items, int64_t blocks, int ncu)
+{
+    const int parts = split_parts(items, (int)blocks, ncu);
+    const int64_t rounds = (items * parts + ncu - 1) / ncu;
+    return (5000 + 163 * blocks / parts) * rounds + (parts > 1 ? 4000 + 250 * parts : 0);
+}
+
+// Sizes as attn_fwd() takes them, all positive: what the kernels' index arithmetic holds.  Returns a code of include/attn.h
+// (and, if that is ATTN_OK, the shape).
+inline int make_shape(int B, int Hq, int Hkv, int Sq, int Skv, Shape &sh, Sched &sc)
+{
+    // Key/query indices and the work-item count are 32-bit in the kernel (and below 2^31 for the divisions).
+    if ((int64_t)Sq + Skv + WG_ROWS + 8 * BN >= INT32_MAX) return ATTN_E_UNSUPPORTED;
+    // Byte offsets within one tile (rows x row pitch) are 32-bit in the kernel.
+    if (Hq > 32768 || Hkv > 32768) return ATTN_E_UNSUPPORTED;
+    sh.Sq = Sq; sh.Hq = Hq;
+    sh.G = Hq / Hkv;
+    sh.pack = (sh.G % 8 == 0) ? 8 : (sh.G % 4 == 0) ? 4 : (sh.G % 2 == 0) ? 2 : 1;
+    sh.pack_log2 = sh.pack == 8 ? 3 : sh.pack == 4 ? 2 : sh.pack == 2 ? 1 : 0;
+    sh.tile_pos = WG_ROWS / sh.pack;
+    sh.chunks = sh.G / sh.pack;
+    sh.d_chunks = make_div((uint32_t)sh.chunks);
+    sh.d_hkv = make_div((uint32_t)Hkv);
+    sc.ntile = (Sq + sh.tile_pos - 1) / sh.tile_pos;
+    const int64_t total = (int64_t)B * Hkv * sh.chunks * sc.ntile;
+    if (total + 8 >= INT32_MAX / 16) return ATTN_E_UNSUPPORTED;
+    sc.total = (int)total;
+    return ATTN_OK;
+}
+
+// The route of a call whose shape make_shape() has accepted, on a device of ncu compute units.
+inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
+{
+    Shape &sh = p.shape;
+    Sched &sc = p.sched;
+    const int Sq = sh.Sq;
+    const int64_t total = sc.total;
+    p.Skv = Skv;
+
+    const int cu_slots = ncu >= 8 ? ncu / 8 : 1;
+    // One workgroup per CU (a workgroup takes all of a CU's registers and LDS), each working through a list.
+    sc.per_xcd = (int)((total + 7) / 8);
+    sc.split = sc.nsub = sc.sgx = sc.window = 1;
+    sc.split_log2 = 0;
+    if (causal) {
+        const int64_t groups = (int64_t)B * Hkv * sh.chunks;
+        while ((groups * sc.split) % 8 != 0) { sc.split *= 2; ++sc.split_log2; }    // 1, 2, 4 or 8
+        sc.nsub = (sc.ntile + sc.split - 1) / sc.split;
+        sc.sgx = (int)(groups * sc.split / 8);
+        while (sc.window * 2 <= sc.sgx && sc.window * sc.nsub < cu_slots) sc.window *= 2;
+        sc.per_xcd = sc.sgx * sc.nsub;          // <= total + padding, far below 2^31 after the check above
+    }
+    sc.per_win = sc.window * sc.nsub;
+    sc.d_ntile = make_div((uint32_t)sc.ntile);
+    sc.d_per_win = make_div((uint32_t)sc.per_win);
+    sc.d_window = make_div((uint32_t)sc.window);
+    sc.slots = sc.per_xcd < cu_slots ? sc.per_xcd : cu_slots;
+
+    const int split_tile_pos = 32 / sh.pack;
+    const int64_t split_items = (int64_t)B * Hkv * sh.chunks * ((Sq + split_tile_pos - 1) / split_tile_pos);
+    // The same work as a line cut into equal stretches.  From 4 items per compute unit on, whole items leave at most a fifth of the chip idle at the
+    // end, and sharing has not been faster.  (5 %: what the estimates are worth.)
+    Share &sr = p.share;
+    sr.wgs = 8 * cu_slots;
+    sr.groups = (int)((int64_t)B * Hkv * sh.chunks);
+    sr.extra = causal ? SHARE_EXTRA_CAUSAL : SHARE_EXTRA;
+    bool share = false;
+    if (ATTN_SHARE != 0 && total <= (ATTN_SHARE == 2 ? SHARE_MAX_ITEMS : 4 * ncu) && total <= SHARE_MAX_ITEMS && sr.wgs <= SHARE_MAX_WGS) {
+        int64_t len = 0;
+        for (int t = 0; t < sc.ntile; ++t) len += item_blocks(p, causal, t) + sr.extra;
+        const int64_t line = len * sr.groups;
+        if (line * sr.wgs < INT32_MAX && line >= 8 * (sr.extra + 2 * SHARE_MIN_PART - 1)) {
+            sr.group_len = (int)len;
+            sr.total = (int)line;
+            const int most = sr.total / (sr.extra + 2 * SHARE_MIN_PART - 1) / 8 * 8;
+            if (sr.wgs > most) sr.wgs = most;
+            const int64_t slots = sr.wgs + (total < sr.wgs ? total : sr.wgs);
+            sr.units = (int)((SHARE_HEADER_BYTES + slots * SHARE_SLOT_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
+            const int64_t blocks32 = (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS;
+            const int64_t whole = total * 4 <= ncu && ATTN_SMALL_PATH == 1 ? split_ns(split_items, blocks32, ncu)
+                                                                           : whole_items_ns(p, causal != 0);
+            share = ATTN_SHARE == 2 || shared_ns(p, total) * 105 < whole * 100;
+        }
+    }
+
+    // Small problems: few 256-row items would leave most compute units idle, and items of few rows (the
+    // query heads of one group times the positions of the sequence) most of each item's rows; 32-row items whose keys
+    // are shared out among the wavefronts of a workgroup, and among workgroups, fill the device instead.
+    // Few rows, measured, 256-row / split-key kernel, us: 4 rows x 4000 keys, 128 items 77.9 / 42.4; 4 x 4096, 512 items
+    // 240.8 / 184.1 (1.07 GB of K and V); 4 x 500, 512 items 35.6 / 24.1; 1 x 8000, 256 items 232.9 / 175.2.
+    const bool few_rows = (int64_t)Sq * sh.pack <= 64;
+    const bool small = ATTN_SMALL_PATH == 2 || (ATTN_SMALL_PATH == 1 && ((total * 4 <= ncu && !share) || few_rows));
+    p.kind = share ? ROUTE_SHARED : ROUTE_WHOLE;
+    if (small && split_items < INT32_MAX) {
+        Split &sp = p.split;
+        p.kind = ROUTE_SPLIT;
+        sp.tile_pos = split_tile_pos;
+        sp.ntile = (Sq + split_tile_pos - 1) / split_tile_pos;
+        sp.nrest = sr.groups;
+        sp.splits = split_parts(split_items, (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS, ncu);
+        if (sp.splits > 1)
+            sp.units = (int)((SPLIT_HEADER_BYTES + split_items * sp.splits * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
+    }
+}
+
+}  // namespace attn
+#endif

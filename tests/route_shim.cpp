@@ -1,0 +1,16 @@
+// C entry over csrc/attn_route.h for tests/test_route_cpu.py.
+#include "../paper_2603_24517_amd/csrc/attn_route.h"
+
+extern "C" int route(int B, int Hq, int Hkv, int Sq, int Skv, int causal, int ncu, long long *out)
+{
+    attn::Route r = {};
+    const int rc = attn::make_shape(B, Hq, Hkv, Sq, Skv, r.shape, r.sched);
+    if (rc != ATTN_OK) return rc;
+    attn::make_route(B, Hkv, Skv, causal, ncu, r);
+    out[0] = r.kind;
+    out[1] = r.kind == attn::ROUTE_SPLIT ? (long long)r.split.nrest * r.split.ntile : r.sched.total;            // work items
+    out[2] = r.kind == attn::ROUTE_SPLIT ? out[1] * r.split.splits
+                                         : r.kind == attn::ROUTE_SHARED ? r.share.wgs : 8 * r.sched.slots;      // workgroups
+    out[3] = r.kind == attn::ROUTE_SPLIT ? r.split.units : r.kind == attn::ROUTE_SHARED ? r.share.units : 0;    // pool units
+    return ATTN_OK;
+}
