@@ -26,6 +26,7 @@ constexpr int BN = 64;               // keys per K/V block
 constexpr int NWAVES = 8;            // wavefronts per workgroup; one workgroup fills a CU (registers and LDS)
 constexpr int NTHREADS = NWAVES * 64;
 constexpr int WG_ROWS = NWAVES * 32; // query rows per workgroup
+constexpr int64_t MAX_WGS = UINT32_MAX / NTHREADS;      // a launch has fewer than 2^32 threads
 constexpr int SPLIT_KEYS = 32;                                  // keys per block of the split kernel
 
 // Exact n / d for 0 <= n < 2^31 as a multiply-high, an add and a shift.
@@ -282,13 +283,14 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
     const bool few_rows = (int64_t)Sq * sh.pack <= 64;
     const bool small = ATTN_SMALL_PATH == 2 || (ATTN_SMALL_PATH == 1 && ((total * 4 <= ncu && !share) || few_rows));
     p.kind = share ? ROUTE_SHARED : ROUTE_WHOLE;
-    if (small && split_items < INT32_MAX) {
+    const int splits = split_parts(split_items, (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS, ncu);
+    if (small && split_items * splits <= MAX_WGS) {
         Split &sp = p.split;
         p.kind = ROUTE_SPLIT;
         sp.tile_pos = split_tile_pos;
         sp.ntile = (Sq + split_tile_pos - 1) / split_tile_pos;
         sp.nrest = sr.groups;
-        sp.splits = split_parts(split_items, (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS, ncu);
+        sp.splits = splits;
         if (sp.splits > 1)
             sp.units = (int)((SPLIT_HEADER_BYTES + split_items * sp.splits * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
     }

@@ -36,3 +36,14 @@ def route(tmp_path_factory):
 ])
 def test_kind(route, shape, causal, kind):
     assert route(*shape, causal)["kind"] == kind
+
+
+def test_grid_of_few_row_calls_stays_launchable(route):
+    """HIP takes no grid of 2^32 threads or more: calls of more items than that allows, one workgroup of 512 threads
+    each, run in the 256-row kernel, whose grid follows the number of compute units."""
+    below, at = route(65535, 128, 128, 1, 1), route(65536, 128, 128, 1, 1)
+    assert (below["kind"], below["items"]) == (SPLIT, 2 ** 23 - 128)
+    assert (at["kind"], at["items"], at["wgs"]) == (WHOLE, 2 ** 23, NCU)
+    for shape in ((1048576, 32, 8, 1, 1), (2 ** 24, 4, 4, 1, 7), (2 ** 20, 64, 8, 3, 1)):
+        r = route(*shape)
+        assert r["wgs"] * 512 < 2 ** 32, (shape, r)
