@@ -154,12 +154,19 @@ inline int whole_items_length(const Route &p, bool causal, int extra)
 // One workgroup takes about 5 us + 1.3 us per 8 blocks as long as memory keeps up (measured, 8 items: 7.0 us at 16 blocks,
 // 15.0 at 64, 43 at 256, 189 at 1024); sharing an item adds about 4 us for the reserving launch and
 // 0.25 us per part to merge, so the sum is least at parts^2 = 0.65 blocks (measured, 8 items: 64 blocks 12.5 us
-// with 4 parts, 12.8 with 8; 256 blocks 17.4 with 8 or 16, 20.1 with 24; 1024 blocks 32.9 with 16, 36.2 with 32) and
-// not worth it below 40 blocks (32 blocks, 16 blocks: 10 and 7 us in one part, 11 in two).
+// with 4 parts, 12.8 with 8; 256 blocks 17.4 with 8 or 16, 20.1 with 24; 1024 blocks 32.9 with 16, 36.2 with 32).
 // More workgroups than compute units start a second round: 160 items in two parts 26.5 us, in one 16.2.
-inline int split_parts(int64_t items, int blocks, int ncu)
+//
+// From how many blocks on it pays depends on where K and V come from, which more workgroups read faster from HBM.  One
+// part / shared, us, K and V from HBM (from the last cache, where a repeated call finds them): 8 items of 40 blocks
+// 16.6 / 13.5 (10.9 / 12.0); 64 of 40 18.6 / 16.7 (12.9 / 15.6); 128 in two parts, of 40 blocks 20.7 / 22.5 (16.3 / 20.7), of 54
+// 27.2 / 27.0, of 66 32.0 / 30.9 (24.2 / 27.1).  Many tiles of a sequence read the same keys, which then come from a cache
+// either way: 13 tiles, 52 items of 54 blocks 14.5 / 15.2 (13.9 / 14.7), of 66 18.8 / 16.7 (15.5 / 15.3); 22 tiles, 88 items
+// of 66 18.1 / 18.3 (15.4 / 16.4), of 82 22.6 / 20.8.
+inline int split_parts(int64_t items, int ntile, int blocks, int ncu)
 {
-    if (items > SPLIT_MAX_ITEMS || blocks < 40) return 1;
+    const bool many = items * 4 > ncu;          // at most three parts
+    if (items > SPLIT_MAX_ITEMS || blocks < (ntile > 2 ? (many ? 82 : 66) : (many ? 54 : 40))) return 1;
     int s = 1;
     while ((s + 1) * items <= (ncu < SPLIT_MAX_WGS ? ncu : SPLIT_MAX_WGS) && 5 * (s + 1) * (s + 1) <= 2 * blocks) ++s;
     return s;
@@ -190,9 +197,9 @@ inline int64_t whole_items_ns(const Route &p, bool causal)
     return (1150 + over * 400 / 250) * longest;
 }
 // Split-key kernel: as at split_parts.
-inline int64_t split_ns(int64_t items, int64_t blocks, int ncu)
+inline int64_t split_ns(int64_t items, int ntile, int64_t blocks, int ncu)
 {
-    const int parts = split_parts(items, (int)blocks, ncu);
+    const int parts = split_parts(items, ntile, (int)blocks, ncu);
     const int64_t rounds = (items * parts + ncu - 1) / ncu;
     return (5000 + 163 * blocks / parts) * rounds + (parts > 1 ? 4000 + 250 * parts : 0);
 }
@@ -249,7 +256,8 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
     sc.slots = sc.per_xcd < cu_slots ? sc.per_xcd : cu_slots;
 
     const int split_tile_pos = 32 / sh.pack;
-    const int64_t split_items = (int64_t)B * Hkv * sh.chunks * ((Sq + split_tile_pos - 1) / split_tile_pos);
+    const int split_ntile = (Sq + split_tile_pos - 1) / split_tile_pos;
+    const int64_t split_items = (int64_t)B * Hkv * sh.chunks * split_ntile;
     // The same work as a line cut into equal stretches.  From 4 items per compute unit on, whole items leave at most a fifth of the chip idle at the
     // end, and sharing has not been faster.  (5 %: what the estimates are worth.)
     Share &sr = p.share;
@@ -269,7 +277,7 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
             const int64_t slots = sr.wgs + (total < sr.wgs ? total : sr.wgs);
             sr.units = (int)((SHARE_HEADER_BYTES + slots * SHARE_SLOT_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
             const int64_t blocks32 = (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS;
-            const int64_t whole = total * 4 <= ncu && ATTN_SMALL_PATH == 1 ? split_ns(split_items, blocks32, ncu)
+            const int64_t whole = total * 4 <= ncu && ATTN_SMALL_PATH == 1 ? split_ns(split_items, split_ntile, blocks32, ncu)
                                                                            : whole_items_ns(p, causal != 0);
             share = ATTN_SHARE == 2 || shared_ns(p, total) * 105 < whole * 100;
         }
@@ -283,12 +291,12 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
     const bool few_rows = (int64_t)Sq * sh.pack <= 64;
     const bool small = ATTN_SMALL_PATH == 2 || (ATTN_SMALL_PATH == 1 && ((total * 4 <= ncu && !share) || few_rows));
     p.kind = share ? ROUTE_SHARED : ROUTE_WHOLE;
-    const int splits = split_parts(split_items, (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS, ncu);
+    const int splits = split_parts(split_items, split_ntile, (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS, ncu);
     if (small && split_items * splits <= MAX_WGS) {
         Split &sp = p.split;
         p.kind = ROUTE_SPLIT;
         sp.tile_pos = split_tile_pos;
-        sp.ntile = (Sq + split_tile_pos - 1) / split_tile_pos;
+        sp.ntile = split_ntile;
         sp.nrest = sr.groups;
         sp.splits = splits;
         if (sp.splits > 1)

@@ -47,3 +47,14 @@ def test_grid_of_few_row_calls_stays_launchable(route):
     for shape in ((1048576, 32, 8, 1, 1), (2 ** 24, 4, 4, 1, 7), (2 ** 20, 64, 8, 3, 1)):
         r = route(*shape)
         assert r["wgs"] * 512 < 2 ** 32, (shape, r)
+
+
+@pytest.mark.parametrize("shape,shared", [
+    ((1, 32, 8, 1, 1280), True), ((2, 16, 16, 1, 1280), True), ((4, 16, 16, 1, 1280), True), ((1, 8, 8, 1, 1216), False),
+    ((8, 16, 16, 1, 1600), False), ((8, 16, 16, 1, 1800), True),            # 128 items of one tile
+    ((1, 32, 4, 51, 1700), False), ((1, 32, 4, 51, 2200), True),            # 13 tiles, 52 items
+    ((1, 4, 4, 700, 2400), False), ((1, 4, 4, 700, 2700), True),            # 22 tiles, 88 items
+])
+def test_split_key_items_are_shared_only_where_that_pays(route, shape, shared):
+    r = route(*shape)
+    assert r["kind"] == SPLIT and (r["units"] > 0) == shared == (r["wgs"] > r["items"]), r
