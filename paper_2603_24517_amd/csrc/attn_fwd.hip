@@ -281,7 +281,7 @@ __device__ __forceinline__ unsigned long long phase_now() {
 // leaves its number in the first LSE element of every item, which is the launch's own memory and is overwritten by the
 // result only after all workgroups of the item have read it.  The 256-row kernel's shared form takes 18 units or fewer.  Launches on any number of streams, from
 // any thread and replayed from graphs thus never share units; if no run is free (the pool serves at
-// least POOL_UNITS / SHARE_MAX_UNITS launches at a time), the first workgroup of each item takes all of its keys and
+// least POOL_UNITS / SHARE_MAX_UNITS launches at a time), the first workgroup of each item takes all of its parts and
 // the others leave, which is slower but needs no memory.
 constexpr uint32_t POOL_NONE = 0xffu;
 // How the number (or POOL_NONE) stands in an LSE element: as a NaN whose low half is no result's.  (A NaN of a
@@ -1438,11 +1438,13 @@ void attn_fwd_kernel(const Params p)
 // sums of its own (the same online softmax, paper section 2.2), staging its K and V blocks through a
 // private 16 KiB of LDS, and the eight partial results are merged through LDS at the end:
 //     M = max_w m_w,  f_w = 2^(m_w - M),  O = sum_w f_w acc_w / sum_w f_w lr_w,  LSE = ln2 (M + log2 sum_w f_w l_w).
-// No barrier inside the key loop, no workspace in device memory.
+// No barrier inside the key loop.
 //
 // When the items are fewer than the compute units, each item is shared by `splits` workgroups, which
 // take contiguous ranges of its key blocks.  They leave (acc, m, l, lr) in device memory and the one that arrives last
-// merges them, in the order of the ranges, whatever the order of arrival, so that the result does not depend on it.
+// merges them, in the order of the ranges, whatever the order of arrival, so that the result does not depend on it.  Nor does it
+// depend on the memory: where none is free, an item's first workgroup takes the same ranges one after the other and adds them up
+// the same way.
 struct SplitParams {
     const __bf16 *q, *k, *v;
     __bf16 *o;
@@ -1529,22 +1531,22 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
     const int qpos = q0 + (l32 >> p.pack_log2);
     // keys 0 .. klast are valid for some row of the tile
     const int klast = min(p.Skv - 1, min(q0 + p.tile_pos - 1, p.Sq - 1) + p.off);
-    int nb = klast < 0 ? 0 : klast / SPLIT_KEYS + 1;
-    // this workgroup's blocks: part, of `splits` ranges of equal length (the last ones may be shorter or empty)
-    int first = 0;
+    const int item_nb = klast < 0 ? 0 : klast / SPLIT_KEYS + 1;
+    int first = 0, nb = item_nb;        // this workgroup's blocks: first .. nb - 1
+    // SHARED: part i, of `splits` ranges of equal length (the last ones may be shorter or empty)
+    auto take_part = [&](int i) __attribute__((always_inline)) {
+        const int len = fast_div(item_nb + p.splits - 1, p.d_splits);
+        first = min(item_nb, i * len);
+        nb = min(item_nb, first + len);
+    };
     uint32_t unit = POOL_NONE;
     if (SHARED) {
         // (read as a constant: where units were taken, nothing writes it until every workgroup of the item has read it)
         unit = ((const __attribute__((address_space(4))) uint32_t *)(uintptr_t)p.lse)[item_lse(rest, q0)];
         asm volatile("" : "+s"(unit));      // read once, here
         unit = pool_unmark(unit);
-        if (unit != POOL_NONE) {
-            const int len = fast_div(nb + p.splits - 1, p.d_splits);
-            first = min(nb, part * len);
-            nb = min(nb, first + len);
-        } else if (part != 0) {
-            return;
-        }
+        if (unit == POOL_NONE && part != 0) return;
+        take_part(part);
     }
     const size_t kv_row_bytes = (size_t)p.Hkv * HD * 2;
     const unsigned char *kg = (const unsigned char *)(p.k + ((size_t)b * p.Skv * p.Hkv + hkv) * HD);
@@ -1569,9 +1571,11 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
 #pragma unroll
             for (int i = 0; i < 8; ++i) lds_dma16(g, is_v ? voff[i] : koff[i], dst + i * 1024);
         } else {
+            int ln = lane;
+            if (SHARED) PIN(ln);        // formed here, not kept in registers through all parts
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const int row = 4 * i + (lane >> 4);
+                const int row = 4 * i + (ln >> 4);
                 const uint32_t o = (is_v ? voff[i] : koff[i]) - (uint32_t)(row * kv_row_bytes) + (uint32_t)(min(row, last) * kv_row_bytes);
                 lds_dma16(g, o, dst + i * 1024);
             }
@@ -1600,11 +1604,50 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
     }
     __builtin_amdgcn_sched_barrier(0);
     f32x16 acc[4];
+    float m, l, lr;
+    auto reset_state = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+        for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
-    float m = -INFINITY, l = 0.0f, lr = 0.0f;
+            for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
+        m = -INFINITY;
+        l = lr = 0.0f;
+    };
+    reset_state();
+    // SHARED: what the parts of an item add up to, as far as they have been added, for the eight outputs of this thread.
+    // Four parts at a time (fewer rescalings than one by one), and the same operations in the same order wherever the parts
+    // come from, so that results do not depend on that.
+    constexpr int GROUP = 4;
+    struct Parts { float m[GROUP], l[GROUP], r[GROUP], x[GROUP][8]; };
+    float M = -INFINITY, L = 0.0f, LR = 0.0f, o8[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o8[j] = 0.0f;
+    auto no_part = [&](Parts &g, int i) __attribute__((always_inline)) {        // adds nothing
+        g.m[i] = -INFINITY;
+        g.l[i] = g.r[i] = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) g.x[i][j] = 0.0f;
+    };
+    auto add_parts = [&](const Parts &g) __attribute__((always_inline)) {
+        float mn = M;
+#pragma unroll
+        for (int i = 0; i < GROUP; ++i) mn = fmaxf(mn, g.m[i]);
+        const float keep = (M == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(M - mn);
+        M = mn;
+        L *= keep;
+        LR *= keep;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o8[j] *= keep;
+#pragma unroll
+        for (int i = 0; i < GROUP; ++i) {
+            const float f = (g.m[i] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(g.m[i] - mn);
+            L = __builtin_fmaf(f, g.l[i], L);
+            LR = __builtin_fmaf(f, g.r[i], LR);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) o8[j] = __builtin_fmaf(f, g.x[i][j], o8[j]);
+        }
+    };
+    Parts group;        // of a workgroup that takes all parts: those not added yet
     int kaddr[8];
 #pragma unroll
     for (int st = 0; st < 8; ++st) kaddr[st] = kbase + l32 * ROW_BYTES + (((2 * st + hh) ^ (l32 & 15)) << 4);
@@ -1634,133 +1677,166 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
         for (int s = 0; s < 8; ++s) qf[s] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, qf[s]) ^ 0x80008000u);
     }
 
-    // Blocks first + wave, first + wave + 8, ...: K(t) and V(t) were requested above (this wavefront's first block); K(t + 8) goes out as soon as the
-    // score MFMAs have read K(t), V(t + 8) as soon as the PV MFMAs have read V(t), so that a wait is "all
-    // but the newest eight requests have landed" while there is a next block and "all" at the last one.
-    for (; t < nb; t += NWAVES) {
-        const bool more = t + NWAVES < nb;
-        __builtin_amdgcn_s_waitcnt(wait_vmcnt(8));          // K(t) has landed
-        f32x16 s;
+    float mp, lp, rp, x[8];         // what the loop below leaves: this part's result for this thread's eight outputs
+    // (one turn; where items are shared and no units were free, one for each part)
+    for (;;) {
+        // Blocks first + wave, first + wave + 8, ...: K(t) and V(t) were requested above (this wavefront's first block); K(t + 8) goes out as soon as the
+        // score MFMAs have read K(t), V(t + 8) as soon as the PV MFMAs have read V(t), so that a wait is "all
+        // but the newest eight requests have landed" while there is a next block and "all" at the last one.
+        for (; t < nb; t += NWAVES) {
+            const bool more = t + NWAVES < nb;
+            __builtin_amdgcn_s_waitcnt(wait_vmcnt(8));          // K(t) has landed
+            f32x16 s;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+            for (int r = 0; r < 16; ++r) s[r] = 0.0f;
 #pragma unroll
-        for (int st = 0; st < 8; ++st) {
-            bf16x8 a = *(const LDS_AS bf16x8 *)(lds + kaddr[st]);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[st], s, 0, 0, 0);
+            for (int st = 0; st < 8; ++st) {
+                bf16x8 a = *(const LDS_AS bf16x8 *)(lds + kaddr[st]);
+                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[st], s, 0, 0, 0);
+            }
+            // (the MFMAs above hold K(t) in registers: the compiler has waited for the LDS reads)
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) request(t + NWAVES, false);
+            // exact online softmax of the block, masked per key
+            const int lim = min(p.Skv - 1, qpos + p.off);
+            const int kidx = t * SPLIT_KEYS + 4 * hh;
+            float mx = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int key = kidx + 8 * (r >> 2) + (r & 3);
+                mx = fmaxf(mx, key <= lim ? s[r] : -INFINITY);
+            }
+            mx = lane32_ext<false>(mx);
+            mx = (mx == -INFINITY) ? -INFINITY : mx * c;
+            if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
+                const float mn = fmaxf(m, mx);
+                const float alpha = (mn == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - mn);
+                m = mn;
+                l *= alpha;
+                lr *= alpha;
+#pragma unroll
+                for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[dt][r] *= alpha;
+            }
+            const float mu = (m == -INFINITY) ? 0.0f : m;
+            uint32_t pb[8];
+            float ls = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) {
+                const int key = kidx + 8 * (r >> 2) + (r & 3);
+                float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -mu));
+                float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r + 1], c, -mu));
+                e0 = (key <= lim) ? e0 : 0.0f;
+                e1 = (key + 1 <= lim) ? e1 : 0.0f;
+                ls += e0 + e1;
+                pb[r >> 1] = pack_bf16(e0, e1);
+                lr = add_bf16_pair(pb[r >> 1], lr);
+            }
+            l += ls;
+            // V(t) has landed: behind it in the queue are the requests of K(t + 8), if there is such a block
+            if (more) __builtin_amdgcn_s_waitcnt(wait_vmcnt(8)); else __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                u32x4 pw = {pb[4 * g], pb[4 * g + 1], pb[4 * g + 2], pb[4 * g + 3]};
+#pragma unroll
+                for (int dt = 0; dt < 4; ++dt) {
+                    const int ro = g * 16 * ROW_BYTES;
+                    s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4 *)(lds + vaddr[dt] + ro));
+                    s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4 *)(lds + vaddr[dt] + (ro + 8 * ROW_BYTES)));
+                    s16x8 av = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                    acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av),
+                                                                       __builtin_bit_cast(bf16x8, pw), acc[dt], 0, 0, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) request(t + NWAVES, true);
         }
-        // (the MFMAs above hold K(t) in registers: the compiler has waited for the LDS reads)
-        __builtin_amdgcn_sched_barrier(0);
-        if (more) request(t + NWAVES, false);
-        // exact online softmax of the block, masked per key
-        const int lim = min(p.Skv - 1, qpos + p.off);
-        const int kidx = t * SPLIT_KEYS + 4 * hh;
-        float mx = -INFINITY;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = kidx + 8 * (r >> 2) + (r & 3);
-            mx = fmaxf(mx, key <= lim ? s[r] : -INFINITY);
-        }
-        mx = lane32_ext<false>(mx);
-        mx = (mx == -INFINITY) ? -INFINITY : mx * c;
-        if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
-            const float mn = fmaxf(m, mx);
-            const float alpha = (mn == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - mn);
-            m = mn;
-            l *= alpha;
-            lr *= alpha;
+        // nothing of this wavefront's is still on its way into LDS (the last block waited for everything),
+        // and its MFMAs have read their operands
+        __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
+
+        // ---- merge.  Each wavefront leaves its accumulator as FP32 [query][d] in its own 16 KiB (its blocks
+        // are dead), the 16-byte units of a query's row swizzled by the query so that the 32 lanes of a
+        // store or load touch 32 different units, and its m, l, lr in the state area; wavefront w then
+        // combines d = 16 w .. 16 w + 15.
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        int l32 = lane & 31, hh = lane >> 5;
+        if (SHARED) { PIN(l32); PIN(hh); }      // what follows is formed here in every turn, not kept through the blocks
+        {
+            LDS_AS unsigned char *part = lds + wave * SPLIT_WAVE_BYTES + l32 * (HD * 4);
 #pragma unroll
             for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[dt][r] *= alpha;
-        }
-        const float mu = (m == -INFINITY) ? 0.0f : m;
-        uint32_t pb[8];
-        float ls = 0.0f;
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-            const int key = kidx + 8 * (r >> 2) + (r & 3);
-            float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -mu));
-            float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r + 1], c, -mu));
-            e0 = (key <= lim) ? e0 : 0.0f;
-            e1 = (key + 1 <= lim) ? e1 : 0.0f;
-            ls += e0 + e1;
-            pb[r >> 1] = pack_bf16(e0, e1);
-            lr = add_bf16_pair(pb[r >> 1], lr);
-        }
-        l += ls;
-        // V(t) has landed: behind it in the queue are the requests of K(t + 8), if there is such a block
-        if (more) __builtin_amdgcn_s_waitcnt(wait_vmcnt(8)); else __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            u32x4 pw = {pb[4 * g], pb[4 * g + 1], pb[4 * g + 2], pb[4 * g + 3]};
-#pragma unroll
-            for (int dt = 0; dt < 4; ++dt) {
-                const int ro = g * 16 * ROW_BYTES;
-                s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4 *)(lds + vaddr[dt] + ro));
-                s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4 *)(lds + vaddr[dt] + (ro + 8 * ROW_BYTES)));
-                s16x8 av = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av),
-                                                                   __builtin_bit_cast(bf16x8, pw), acc[dt], 0, 0, 0);
+                for (int rg = 0; rg < 4; ++rg) {
+                    const int u = 8 * dt + 2 * rg + hh;          // d = 4 u .. 4 u + 3
+                    const f32x4 val = {acc[dt][4 * rg], acc[dt][4 * rg + 1], acc[dt][4 * rg + 2], acc[dt][4 * rg + 3]};
+                    *(LDS_AS f32x4 *)(part + ((u ^ l32) << 4)) = val;
+                }
+            // every lane of a query holds the same m; l and lr are the lane's share: add the two halves
+            const float lt = lane32_sum(l), lrt = lane32_sum(lr);
+            LDS_AS float *state = (LDS_AS float *)(lds + SPLIT_STATE_BASE) + wave * 96;
+            if (hh == 0) {
+                state[l32] = m;
+                state[32 + l32] = lt;
+                state[64 + l32] = lrt;
             }
         }
-        __builtin_amdgcn_sched_barrier(0);
-        if (more) request(t + NWAVES, true);
+        __syncthreads();
+        mp = -INFINITY;
+        lp = rp = 0.0f;
+        {
+            const LDS_AS float *state = (const LDS_AS float *)(lds + SPLIT_STATE_BASE);
+            float mw[NWAVES];
+#pragma unroll
+            for (int w = 0; w < NWAVES; ++w) {
+                mw[w] = state[w * 96 + l32];
+                mp = fmaxf(mp, mw[w]);
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NWAVES; ++w) {
+                const float f = (mw[w] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(mw[w] - mp);
+                lp += f * state[w * 96 + 32 + l32];
+                rp += f * state[w * 96 + 64 + l32];
+                const LDS_AS unsigned char *part = lds + w * SPLIT_WAVE_BYTES + l32 * (HD * 4);
+                const int u = 4 * wave + 2 * hh;
+                const f32x4 lo = *(const LDS_AS f32x4 *)(part + ((u ^ l32) << 4));
+                const f32x4 hi = *(const LDS_AS f32x4 *)(part + (((u + 1) ^ l32) << 4));
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    x[j] += f * lo[j];
+                    x[4 + j] += f * hi[j];
+                }
+            }
+        }
+        if (!SHARED || unit != POOL_NONE) break;
+        // No units: all parts one after the other, added up like those that come from memory.
+        const int k = part % GROUP;
+#pragma unroll
+        for (int i = 0; i < GROUP; ++i) {
+            if (i == k) {
+                group.m[i] = mp; group.l[i] = lp; group.r[i] = rp;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) group.x[i][j] = x[j];
+            } else if (i > k) {
+                no_part(group, i);
+            }
+        }
+        ++part;
+        if (k == GROUP - 1 || part == p.splits) add_parts(group);
+        if (part == p.splits) break;
+        __syncthreads();            // the merge is done with the wavefronts' results, which lie where the blocks go
+        take_part(part);
+        t = first + wave;
+        if (t < nb) {
+            request(t, false);
+            request(t, true);
+        }
+        reset_state();
     }
-    // nothing of this wavefront's is still on its way into LDS (the last block waited for everything),
-    // and its MFMAs have read their operands
-    __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
-
-    // ---- merge.  Each wavefront leaves its accumulator as FP32 [query][d] in its own 16 KiB (its blocks
-    // are dead), the 16-byte units of a query's row swizzled by the query so that the 32 lanes of a
-    // store or load touch 32 different units, and its m, l, lr in the state area; wavefront w then
-    // combines d = 16 w .. 16 w + 15.
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
     {
-        LDS_AS unsigned char *part = lds + wave * SPLIT_WAVE_BYTES + l32 * (HD * 4);
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                const int u = 8 * dt + 2 * rg + hh;          // d = 4 u .. 4 u + 3
-                const f32x4 val = {acc[dt][4 * rg], acc[dt][4 * rg + 1], acc[dt][4 * rg + 2], acc[dt][4 * rg + 3]};
-                *(LDS_AS f32x4 *)(part + ((u ^ l32) << 4)) = val;
-            }
-        // every lane of a query holds the same m; l and lr are the lane's share: add the two halves
-        const float lt = lane32_sum(l), lrt = lane32_sum(lr);
-        LDS_AS float *state = (LDS_AS float *)(lds + SPLIT_STATE_BASE) + wave * 96;
-        if (hh == 0) {
-            state[l32] = m;
-            state[32 + l32] = lt;
-            state[64 + l32] = lrt;
-        }
-    }
-    __syncthreads();
-    {
-        const LDS_AS float *state = (const LDS_AS float *)(lds + SPLIT_STATE_BASE);
-        float mw[NWAVES], M = -INFINITY;
-#pragma unroll
-        for (int w = 0; w < NWAVES; ++w) {
-            mw[w] = state[w * 96 + l32];
-            M = fmaxf(M, mw[w]);
-        }
-        float L = 0.0f, LR = 0.0f, o8[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) o8[j] = 0.0f;
-#pragma unroll
-        for (int w = 0; w < NWAVES; ++w) {
-            const float f = (mw[w] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(mw[w] - M);
-            L += f * state[w * 96 + 32 + l32];
-            LR += f * state[w * 96 + 64 + l32];
-            const LDS_AS unsigned char *part = lds + w * SPLIT_WAVE_BYTES + l32 * (HD * 4);
-            const int u = 4 * wave + 2 * hh;
-            const f32x4 lo = *(const LDS_AS f32x4 *)(part + ((u ^ l32) << 4));
-            const f32x4 hi = *(const LDS_AS f32x4 *)(part + (((u + 1) ^ l32) << 4));
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                o8[j] += f * lo[j];
-                o8[4 + j] += f * hi[j];
-            }
-        }
         if (SHARED && unit != POOL_NONE) {
             // Leave this part's result; every thread of the merging workgroup reads what the same thread of
             // the others wrote, so the accumulators lie in thread order.
@@ -1772,14 +1848,14 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
             {
                 unsigned char *out = mine + (size_t)part * SPLIT_PART_BYTES;
                 if (valid) {
-                    pool_store4(out + ((2 * wave) * 64 + lane) * 16, o8[0], o8[1], o8[2], o8[3]);
-                    pool_store4(out + ((2 * wave + 1) * 64 + lane) * 16, o8[4], o8[5], o8[6], o8[7]);
+                    pool_store4(out + ((2 * wave) * 64 + lane) * 16, x[0], x[1], x[2], x[3]);
+                    pool_store4(out + ((2 * wave + 1) * 64 + lane) * 16, x[4], x[5], x[6], x[7]);
                 }
                 if (wave == 0 && hh == 0) {
                     float *st = (float *)(out + 32 * HD * 4);
-                    pool_store(st + l32, M);
-                    pool_store(st + 32 + l32, L);
-                    pool_store(st + 64 + l32, LR);
+                    pool_store(st + l32, mp);
+                    pool_store(st + 32 + l32, lp);
+                    pool_store(st + 64 + l32, rp);
                 }
             }
             __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);        // this thread's stores have arrived
@@ -1790,51 +1866,39 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
             __syncthreads();
             if (shared[0] != (uint32_t)p.splits - 1) return;
             // eight parts at a time, all of their loads in flight together
-            M = -INFINITY;
-            L = LR = 0.0f;
+            constexpr int BATCH = 2;
+            for (int s0 = 0; s0 < p.splits; s0 += BATCH * GROUP) {
+                Parts g[BATCH];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) o8[j] = 0.0f;
-            constexpr int BATCH = 8;
-            for (int s0 = 0; s0 < p.splits; s0 += BATCH) {
-                float ms[BATCH], ls[BATCH], rs[BATCH], x[BATCH][8];
-#pragma unroll
-                for (int i = 0; i < BATCH; ++i) {
+                for (int i = 0; i < BATCH * GROUP; ++i) {
                     const bool there = s0 + i < p.splits;
                     const unsigned char *in = mine + (size_t)(s0 + i) * SPLIT_PART_BYTES;
                     const float *st = (const float *)(in + 32 * HD * 4);
-                    ms[i] = there ? pool_load(st + l32) : -INFINITY;
-                    ls[i] = there ? pool_load(st + 32 + l32) : 0.0f;
-                    rs[i] = there ? pool_load(st + 64 + l32) : 0.0f;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) x[i][j] = 0.0f;
+                    Parts &gi = g[i / GROUP];
+                    no_part(gi, i % GROUP);
+                    if (there) {
+                        gi.m[i % GROUP] = pool_load(st + l32);
+                        gi.l[i % GROUP] = pool_load(st + 32 + l32);
+                        gi.r[i % GROUP] = pool_load(st + 64 + l32);
+                    }
                     if (there && valid) {
-                        pool_load4(in + ((2 * wave) * 64 + lane) * 16, x[i]);
-                        pool_load4(in + ((2 * wave + 1) * 64 + lane) * 16, x[i] + 4);
+                        pool_load4(in + ((2 * wave) * 64 + lane) * 16, gi.x[i % GROUP]);
+                        pool_load4(in + ((2 * wave + 1) * 64 + lane) * 16, gi.x[i % GROUP] + 4);
                     }
                 }
-                float mn = M;
 #pragma unroll
-                for (int i = 0; i < BATCH; ++i) mn = fmaxf(mn, ms[i]);
-                const float keep = (M == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(M - mn);
-                M = mn;
-                L *= keep;
-                LR *= keep;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) o8[j] *= keep;
-#pragma unroll
-                for (int i = 0; i < BATCH; ++i) {
-                    const float f = (ms[i] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(ms[i] - M);
-                    L += f * ls[i];
-                    LR += f * rs[i];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) o8[j] += f * x[i][j];
-                }
+                for (int k = 0; k < BATCH; ++k)
+                    if (s0 + k * GROUP < p.splits) add_parts(g[k]);
             }
             __syncthreads();                // everything of this item is read
             if (tid == 0) {
                 const uint32_t done = __hip_atomic_fetch_add(&header[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (done == (uint32_t)(p.nrest * p.ntile) - 1) pool_give(unit, p.units);
             }
+        } else if (!SHARED) {
+            M = mp; L = lp; LR = rp;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) o8[j] = x[j];
         }
         const float inv = LR > 0.0f ? 1.0f / LR : 0.0f;
         if (qpos < p.Sq) {
