@@ -67,8 +67,8 @@ enum {
  * several workgroups share an item's keys; the launch is then preceded by one of a
  * single workgroup, which takes the device memory that the partial results pass
  * through.  Any number of threads and streams may do so at a time: a launch
- * that finds the memory in use goes without it, which is slower, and rounds
- * differently in the last bits.  Nothing is allocated in any case.
+ * that finds the memory in use goes without it, which is slower and gives the
+ * same result bit for bit.  Nothing is allocated in any case.
  * The first call on a device queries the device once and sets function
  * attributes, so make one ordinary call on a device before recording attn_fwd
  * into a HIP graph (later calls are one or two kernel launches and nothing else, and

@@ -91,7 +91,7 @@ int attn_clocks_read(unsigned long long *out);
  *                7 their number, 8 the last iteration (PV only), 9 the wait for outstanding loads,
  *                10 the epilogue, 11 the whole item
  *   out[12..23]  the same for the last wavefront
- *   out  out  host, 24 x 64-bit (zero or stale if that workgroup had fewer than two items)
+ *   out  out  host, 24 x 64-bit (zero or stale if that workgroup had fewer than two items, or the launch shared its items)
  * A stamp per iteration lengthens the loop by about 1.5 %.
  * Returns 0, or a negative ATTN_E_* code of include/attn.h.
  */

@@ -260,7 +260,7 @@ __device__ unsigned long long g_clocks[10];
 // 1 the first two score blocks, 2 the first softmax, 3 the barrier and requests before the loop,
 // 4 iterations in which this wavefront took the fast path, 5 their number, 6 other iterations but the
 // last, 7 their number, 8 the last iteration, 9 the wait for outstanding loads, 10 the epilogue,
-// 11 the whole item
+// 11 the whole item.  Not stamped where items are shared: a part has no registers left for it.
 __device__ unsigned long long g_phases[2][12];
 __device__ __forceinline__ unsigned long long phase_now() {
     __builtin_amdgcn_sched_barrier(0);
@@ -268,8 +268,8 @@ __device__ __forceinline__ unsigned long long phase_now() {
     __builtin_amdgcn_sched_barrier(0);
     return t;
 }
-#define ATTN_PHASE(k) do { const unsigned long long now_ = phase_now(); ph[k] += now_ - ph_prev; ph_prev = now_; } while (0)
-#define ATTN_PHASE_COUNT(k) do { ++ph[k]; } while (0)
+#define ATTN_PHASE(k) do { if (!SHARED) { const unsigned long long now_ = phase_now(); ph[k] += now_ - ph_prev; ph_prev = now_; } } while (0)
+#define ATTN_PHASE_COUNT(k) do { if (!SHARED) ++ph[k]; } while (0)
 #else
 #define ATTN_PHASE(k) do { } while (0)
 #define ATTN_PHASE_COUNT(k) do { } while (0)
@@ -427,14 +427,21 @@ void attn_fwd_kernel(const Params p)
         return item < sc.total;
     };
     // SHARED: this workgroup's stretch of the line, and whether items are shared at all (false: no pool units were
-    // free; then the workgroup whose stretch holds an item's start takes all of it)
-    int cut_lo = 0, cut_hi = 0;
+    // free; then the workgroup whose stretch holds an item's start takes all of its parts, one after the other, the later ones
+    // in the place of the workgroups `ahead` of it, so that the result is the same to the last bit)
+    int cut_lo = 0, cut_hi = 0, ahead = 0;
     bool pooled = true;
     uint32_t unit = POOL_NONE;
     auto load_share = [&]() __attribute__((always_inline)) -> Share {
         Share sr;
         __builtin_memcpy(&sr, &cold().share, sizeof(Share));
         return sr;
+    };
+    auto set_cuts = [&]() __attribute__((always_inline)) {
+        const Share sr = load_share();
+        const uint32_t w = xcd * (sr.wgs >> 3) + slot + ahead;      // neighbours in the line are on one XCD
+        cut_lo = __builtin_amdgcn_readfirstlane((int)(w * (uint32_t)sr.total / (uint32_t)sr.wgs));
+        cut_hi = __builtin_amdgcn_readfirstlane(w + 1 == (uint32_t)sr.wgs ? INT32_MAX : (int)((w + 1) * (uint32_t)sr.total / (uint32_t)sr.wgs));
     };
     auto blocks_of = [&](const Shape &sh, int tile) __attribute__((always_inline)) -> int {
         int n = (p.Skv + BN - 1) / BN;
@@ -518,8 +525,8 @@ void attn_fwd_kernel(const Params p)
         if (SHARED) {
             const int first = at + cold().share.extra;      // block 0's place in the line
             int j1 = g.nblk;
-            if (pooled && cut_hi <= first + j1 - SHARE_MIN_PART) j1 = cut_hi - first;
-            if (pooled && cut_lo >= first + SHARE_MIN_PART) g.j0 = __builtin_amdgcn_readfirstlane(cut_lo - first);
+            if (cut_hi <= first + j1 - SHARE_MIN_PART) j1 = cut_hi - first;
+            if (cut_lo >= first + SHARE_MIN_PART) g.j0 = __builtin_amdgcn_readfirstlane(cut_lo - first);
             g.blocks = __builtin_amdgcn_readfirstlane(g.nblk);
             g.nblk = j1 - g.j0;
             g.at = __builtin_amdgcn_readfirstlane(at);
@@ -546,7 +553,6 @@ void attn_fwd_kernel(const Params p)
     auto keys = [&]() __attribute__((always_inline)) -> int { return SHARED ? p.Skv - part_j0 * BN : p.Skv; };
     auto offset = [&]() __attribute__((always_inline)) -> int { return SHARED ? off - part_j0 * BN : off; };
     const unsigned char *kg = nullptr, *vg = nullptr;
-    int nx_keys = 0;                    // SHARED: keys from its first block on
     bool warm_next = false;             // the item after this one exists and its first tiles are requested by this one
     int nx_nblk = 0;
     const unsigned char *nx_kg = nullptr, *nx_vg = nullptr;
@@ -648,7 +654,7 @@ void attn_fwd_kernel(const Params p)
         blk = min(blk_req, nblk - 1);
         if (blk_req >= nblk && warm_next) {
             g = is_v ? nx_vg : nx_kg;
-            if (SHARED) left = nx_keys;
+            left = p.Skv;       // (SHARED: only the first part of a stretch begins inside an item)
             blk = min(blk_req - nblk, nx_nblk - 1);
         }
         return g + (size_t)blk * tile_gbytes;
@@ -691,6 +697,27 @@ void attn_fwd_kernel(const Params p)
         }
     }
 
+    // SHARED: all of these once more, so that no registers hold them while parts are added up
+    auto read_addresses = [&]() __attribute__((always_inline)) {
+        int lane = tid & 63;
+        PIN(lane);
+        const int l32 = lane & 31, hh = lane >> 5, i16 = lane & 15, g = (lane >> 4) & 1;
+#pragma unroll
+        for (int i = 0; i < LPT; ++i) {
+            const int row = (wave * LPT + i) * 4 + (lane >> 4);
+            koff[i] = (uint32_t)(row * kv_row_bytes) + ((i16 ^ (row & 15)) << 4);
+            voff[i] = (uint32_t)(row * kv_row_bytes) + ((i16 ^ ((row & 3) << 2)) << 4);
+        }
+#pragma unroll
+        for (int st = 0; st < 8; ++st) kaddr[st] = l32 * ROW_BYTES + (((2 * st + hh) ^ (l32 & 15)) << 4);
+        const int row = 4 * hh + (i16 >> 2);
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) {
+            const int d = 32 * dt + 16 * g + 4 * (i16 & 3);
+            vaddr[dt] = V_BASE + row * ROW_BYTES + ((((d >> 3) ^ ((row & 3) << 2))) << 4) + (d & 7) * 2;
+        }
+    };
+
     // ---- building blocks
     // S^T = K(stage kb) Q^T alone (prologue).
     auto qk_only = [&](f32x16 (&s)[2], int kb) __attribute__((always_inline)) {
@@ -712,7 +739,7 @@ void attn_fwd_kernel(const Params p)
     // the MFMA of slot i.  `between(slot)` is called after each MFMA and carries the caller's vector
     // work for that slot (it must not touch pb entries the remaining PV MFMAs still read).
     auto mfma_block = [&](f32x16 (&snxt)[2], int vb, int kb, auto between) __attribute__((always_inline)) {
-        constexpr int PREFETCH = MAT_PREFETCH;
+        constexpr int PREFETCH = SHARED && MAT_PREFETCH > 3 ? 3 : MAT_PREFETCH;     // (SHARED: no registers for more)
         bf16x8 frag[32];
         int va[4], ka[8];      // stage offsets folded into the per-lane bases: every read is base + immediate
 #pragma unroll
@@ -762,7 +789,7 @@ void attn_fwd_kernel(const Params p)
     };
     // O^T += V^T P^T alone: the last iteration of an item, when no further scores are wanted.
     auto pv_only = [&](int vb) __attribute__((always_inline)) {
-        constexpr int PREFETCH = MAT_PREFETCH;
+        constexpr int PREFETCH = SHARED && MAT_PREFETCH > 3 ? 3 : MAT_PREFETCH;     // (SHARED: no registers for more)
         bf16x8 frag[16];
         int va[4];
 #pragma unroll
@@ -989,7 +1016,8 @@ void attn_fwd_kernel(const Params p)
 
     // ---- SHARED: the end of a part.  A wavefront needs nothing but the same wavefront's parts of the item, so there is
     // no barrier here.  It leaves its part and counts itself, and the one that completes the count adds all parts up in
-    // the order of the keys, so that the result does not depend on the order of arrival.  Of two parts, the common
+    // the order of the keys, so that the result does not depend on the order of arrival (nor on whether parts pass through the
+    // pool at all: add_up below does the same sums).  Of two parts, the common
     // case in a line longer than the launch is wide, the second to arrive keeps its own in registers: the counter's
     // low half counts arrivals, the high half parts that are in memory (1 x 1111, 32 heads on 8, causal: 29.9 us, both parts
     // through memory 32.4; with more parts the extra round trip costs more than it saves: 700 x 20000, 16 heads, 142 us
@@ -1001,7 +1029,6 @@ void attn_fwd_kernel(const Params p)
         // the cuts inside the item: SHARE_MIN_PART <= cut - first <= blocks - SHARE_MIN_PART
         const int lo = (int)(((first + SHARE_MIN_PART) * wgs + total - 1) / total);
         const int hi = (int)(((first + (uint32_t)g.blocks - SHARE_MIN_PART + 1) * wgs + total - 1) / total) - 1;
-        if (g.blocks < 2 * SHARE_MIN_PART || hi < lo) return true;
         const int parts = __builtin_amdgcn_readfirstlane(hi - lo + 2);
         uint32_t *arrived = (uint32_t *)(g_pool + (size_t)unit * POOL_UNIT_BYTES) + 1 + g.item * NWAVES + wave;
         const __amdgpu_buffer_rsrc_t rs = pool_rsrc(unit, sr.units);
@@ -1084,31 +1111,69 @@ void attn_fwd_kernel(const Params p)
             const float keep = (m == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(m - mn);
             const float f = __builtin_amdgcn_exp2f(mi - mn);
             m = mn;
-            l = l * keep + f * __uint_as_float(st[1]);
-            lr = lr * keep + f * __uint_as_float(st[2]);
+            l = __builtin_fmaf(f, __uint_as_float(st[1]), keep * l);
+            lr = __builtin_fmaf(f, __uint_as_float(st[2]), keep * lr);
 #pragma unroll
             for (int k = 0; k < 32; ++k)
-                acc[k >> 4][k & 15] = acc[k >> 4][k & 15] * keep + f * __uint_as_float(xa[k >> 2][k & 3]);
+                acc[k >> 4][k & 15] = __builtin_fmaf(f, __uint_as_float(xa[k >> 2][k & 3]), keep * acc[k >> 4][k & 15]);
             in = slot_of(min(i + 1, parts - 1));        // (the last part again, unused, at the end)
             st = pool_load16(rs, lane_at, in + 16 * 1024);
 #pragma unroll
             for (int k = 0; k < 8; ++k) xa[k] = pool_load16(rs, lane_at, in + k * 1024);
 #pragma unroll
             for (int k = 0; k < 32; ++k)
-                acc[2 + (k >> 4)][k & 15] = acc[2 + (k >> 4)][k & 15] * keep + f * __uint_as_float(xb[k >> 2][k & 3]);
+                acc[2 + (k >> 4)][k & 15] = __builtin_fmaf(f, __uint_as_float(xb[k >> 2][k & 3]), keep * acc[2 + (k >> 4)][k & 15]);
         }
         asm volatile("" ::: "memory");
         return true;
+    };
+
+    // The same without the pool: the parts of an item follow each other in this workgroup, and what the earlier ones add up to
+    // waits meanwhile, half of the accumulator in the item's own rows of O, as many bytes, half in the LDS
+    // region that would hold the next item's Q, and three numbers in registers.
+    float mp = 0.0f, lp = 0.0f, lrp = 0.0f;
+    auto add_up = [&](const Geo &g, bool goes_on) __attribute__((always_inline)) -> bool {
+        const int Sq = cold().shape.Sq, o_row_bytes = cold().shape.Hq * HD * 2;
+        int ln = lane;
+        PIN(ln);
+        // (rows past the end have nowhere to wait, and no result: the descriptor ends with the last row)
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            cold().o + ((size_t)((size_t)b * Sq + q0) * cold().shape.Hq + head) * HD, 0, max(min(Sq - q0, 32), 0) * o_row_bytes, 0x00020000);
+        const uint32_t og = (uint32_t)(ln & 31) * (uint32_t)o_row_bytes + (ln >> 5) * (HD / 2 * 2);
+        LDS_AS u32x4 *ol = (LDS_AS u32x4 *)(lds + Q_BASE + wave * Q_WAVE_BYTES) + ln;
+        if (g.j0 > 0) {
+            const float M = fmaxf(mp, m);       // (neither is minus infinity)
+            const float keep = __builtin_amdgcn_exp2f(mp - M), f = __builtin_amdgcn_exp2f(m - M);
+            m = M;
+            l = __builtin_fmaf(f, l, keep * lp);
+            lr = __builtin_fmaf(f, lr, keep * lrp);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const u32x4 x = i >= 8 ? ol[64 * (i - 8)] : __builtin_amdgcn_raw_buffer_load_b128(rs, og, i * 16, 0);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int e = 4 * (i & 3) + k;
+                    acc[i >> 2][e] = __builtin_fmaf(f, acc[i >> 2][e], keep * __uint_as_float(x[k]));
+                }
+            }
+        }
+        if (!goes_on) return true;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const u32x4 x = {__float_as_uint(acc[i >> 2][4 * (i & 3)]), __float_as_uint(acc[i >> 2][4 * (i & 3) + 1]),
+                             __float_as_uint(acc[i >> 2][4 * (i & 3) + 2]), __float_as_uint(acc[i >> 2][4 * (i & 3) + 3])};
+            if (i >= 8) ol[64 * (i - 8)] = x;
+            else __builtin_amdgcn_raw_buffer_store_b128(x, rs, og, i * 16, 0);
+        }
+        mp = m; lp = l; lrp = lr;
+        return false;
     };
 
     // ---- the workgroup's items, one after the other
     int r = 0, grp = 0, tile = 0, at = 0;
     bool have;
     if (SHARED) {
-        const Share sr = load_share();
-        const uint32_t w = xcd * (sr.wgs >> 3) + slot;      // neighbours in the line are on one XCD
-        cut_lo = (int)(w * (uint32_t)sr.total / (uint32_t)sr.wgs);
-        cut_hi = w + 1 == (uint32_t)sr.wgs ? INT32_MAX : (int)((w + 1) * (uint32_t)sr.total / (uint32_t)sr.wgs);
+        set_cuts();
         // (an item shorter than SHARE_MIN_PART may begin before cut_lo and still be this workgroup's)
         int grp0, tile0, at0;
         locate(max(cut_lo - SHARE_MIN_PART, 0), grp0, tile0, at0);
@@ -1150,31 +1215,38 @@ void attn_fwd_kernel(const Params p)
 #if defined(ATTN_CLOCKS) && ATTN_CLOCKS >= 2
 #pragma unroll
         for (int k = 0; k < 11; ++k) ph[k] = 0;
-        ph_prev = ph_item = phase_now();
+        if (!SHARED) ph_prev = ph_item = phase_now();
 #endif
         enter(cur);
         reset_state();
         // the item after this one
         Geo nxt = cur;
         int r2 = r + 1;
-        bool have2;
+        bool have2, goes_on = false;        // goes_on: the next part of the same item is this workgroup's as well
         if (SHARED) {
-            at += cur.blocks + cold().share.extra;
-            if (++tile == cold().sched.ntile) { tile = 0; ++grp; }
-            have2 = find_part(grp, tile, at);
+            goes_on = !pooled && cut_hi <= cur.at + cold().share.extra + cur.blocks - SHARE_MIN_PART;
+            if (goes_on) {
+                ++ahead;
+                set_cuts();
+                have2 = true;
+            } else {
+                if (ahead != 0) { ahead = 0; set_cuts(); }
+                at += cur.blocks + cold().share.extra;
+                if (++tile == cold().sched.ntile) { tile = 0; ++grp; }
+                have2 = find_part(grp, tile, at);
+            }
         } else {
             have2 = find_item(r2, grp, tile);
         }
         if (have2) nxt = geometry(grp, tile, at);
         // Its tiles K'(0..2), V'(0) ride on this item's last iterations (requests K(j+4), V(j+2) of
         // iterations j >= nblk-4), which takes four iterations to host them.
-        warm_next = ATTN_ITEM_OVERLAP && have2 && nblk >= 2 + REQ_AHEAD && nxt.nblk > 0;
+        warm_next = ATTN_ITEM_OVERLAP && have2 && pooled && nblk >= 2 + REQ_AHEAD && nxt.nblk > 0;
         nx_nblk = nxt.nblk; nx_kg = nxt.kg; nx_vg = nxt.vg;
-        if (SHARED) nx_keys = p.Skv - nxt.j0 * BN;
         // Its Q goes into this wavefront's LDS region now (the epilogue of the item before is done with
         // it) and into registers when this item's last block is done; being the oldest request of the
         // item, it never holds up a wait for tiles.
-        if (ATTN_ITEM_OVERLAP && have2) request_q(nxt);
+        if (ATTN_ITEM_OVERLAP && have2 && pooled) request_q(nxt);
 
         if (nblk > 0) {
             // Iteration j reads K(j+2) and V(j) and requests K(j+4) and V(j+2) into the stages of K(j+1)
@@ -1226,9 +1298,7 @@ void attn_fwd_kernel(const Params p)
             ATTN_PHASE(3);
             // Iterations j < fast_end take the fast path: S(j+1) needs no mask, and the tiles requested are
             // full ones (past the last block: of the next item, or the last block again).
-            int fast_end = all_full ? n_unm - 1 : min(n_unm - 1, (SHARED ? keys() / BN : nfull) - (2 + REQ_AHEAD));
-            // (a next part may begin so near the end that the partial tile is among its first three)
-            if (SHARED && !all_full && warm_next && nx_keys < 3 * BN) fast_end = min(fast_end, nblk - (2 + REQ_AHEAD));
+            const int fast_end = all_full ? n_unm - 1 : min(n_unm - 1, (SHARED ? keys() / BN : nfull) - (2 + REQ_AHEAD));
             // Request addresses of the fast loop.  K and V have the same shape, so V's address is K's of
             // two iterations earlier plus the distance between the tensors; K's moves on by one tile per
             // iteration, except at the item's last block (on to block 0 of the next item, or stay) and,
@@ -1335,7 +1405,15 @@ void attn_fwd_kernel(const Params p)
         ATTN_PHASE(9);
 
         bool last_part = true;
-        if (SHARED && unit != POOL_NONE) last_part = share_parts(cur);
+        if (SHARED && (cur.j0 != 0 || cur.nblk != cur.blocks)) {        // a part, not a whole item
+            if (pooled) {
+                last_part = share_parts(cur);
+                mp = lp = lrp = 0.0f;       // (unused, and no register for them through the above)
+            } else {
+                last_part = add_up(cur, goes_on);
+            }
+            read_addresses();
+        }
         // ---- Q of the next item into registers, from this wavefront's LDS region
         // (SHARED: also if there is none, so that the old values are not kept through the above)
         if (ATTN_ITEM_OVERLAP && (SHARED || have2)) {
@@ -1395,10 +1473,10 @@ void attn_fwd_kernel(const Params p)
             }
 
         }
-        if (!ATTN_ITEM_OVERLAP && (SHARED || have2)) load_q(nxt);
+        if ((!ATTN_ITEM_OVERLAP || !pooled) && (SHARED || have2)) load_q(nxt);
 #if defined(ATTN_CLOCKS) && ATTN_CLOCKS >= 2
         ATTN_PHASE(10);
-        if (bid == 0 && item_no == 1 && (tid == 0 || tid == NTHREADS - 64)) {
+        if (!SHARED && bid == 0 && item_no == 1 && (tid == 0 || tid == NTHREADS - 64)) {
 #pragma unroll
             for (int k = 0; k < 11; ++k) g_phases[tid != 0][k] = ph[k];
             g_phases[tid != 0][11] = ph_prev - ph_item;

@@ -101,7 +101,7 @@ PHASES = ("setup", "first_two_score_blocks", "first_softmax", "barrier_and_first
 def phases_read():
     """Cycle sums per phase of the second work item of the first workgroup in the last launch of the `phases`
     variant: {"first_wavefront": {phase: cycles}, "last_wavefront": {...}}, or None if that workgroup had fewer
-    than two items (or took the split-key kernel).  Waits for the device."""
+    than two items (or took the split-key kernel, or shared its items).  Waits for the device."""
     out = (ctypes.c_ulonglong * 24)()
     rc = load_variant("phases").attn_phases_read(out)
     if rc != 0:

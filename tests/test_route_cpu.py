@@ -69,3 +69,10 @@ def test_few_rows_in_two_tiles_read_keys_twice(route, shape, kind):
     r = route(*shape)
     # (a call that the 256-row kernel gets may take either of its forms)
     assert r["kind"] == kind or {r["kind"], kind} == {WHOLE, SHARED}, r
+
+
+def test_calls_of_the_bits_test_are_shared(route):
+    import test_shared_bits_gpu as T
+    for shape in T.SHARED_CALLS:
+        for causal in (False, True):
+            assert route(*shape, causal)["kind"] == SHARED, (shape, causal)
