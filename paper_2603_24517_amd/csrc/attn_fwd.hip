@@ -1536,7 +1536,8 @@ struct SplitParams {
     int splits;             // workgroups that share an item
     int units;              // POOL_UNIT_BYTES units of device memory the launch needs, 0 if splits == 1
     int reserve;            // > 0: this launch is one workgroup that takes the units for the launch behind it, and clears
-                            // this many counters per item (the item geometry is that launch's)
+                            // this many counters per item (the item geometry is that launch's); < 0: one that gives them
+                            // back, because there was no launch behind it
     int tiles_inside;       // order of the items, see the kernel
     int inner;              // tiles_inside ? ntile : nrest * splits
     Div d_inner, d_splits, d_chunks, d_hkv;     // exact division by inner, splits, chunks, Hkv
@@ -1577,6 +1578,11 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
         const int b = fast_div(bh, p.d_hkv), hkv = bh - b * p.Hkv;
         return ((size_t)b * p.Hq + hkv * p.G + chunk * p.pack) * p.Sq + q0;
     };
+    if (SHARED && p.reserve < 0) {
+        const uint32_t unit = pool_unmark(((const uint32_t *)p.lse)[item_lse(0, 0)]);
+        if (tid == 0 && unit != POOL_NONE) pool_give(unit, p.units);
+        return;
+    }
     if (SHARED && p.reserve) {
         uint32_t *shared = (uint32_t *)smem;
         if (tid == 0) shared[0] = pool_take(p.units);
@@ -2054,9 +2060,6 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
     // a negative scale turns the running maximum of the scaled scores into c times the smallest raw score
     const bool neg = scale < 0.0f;
 
-    auto launch_shared_split = [&](const SplitParams &sp, unsigned wgs, int lds) {
-        hipLaunchKernelGGL(attn_fwd_split_kernel<true>, dim3(wgs), dim3(NTHREADS), lds, st, sp);
-    };
     SplitParams sp = {};
     sp.lse = lse;
     sp.Hq = Hq; sp.Hkv = Hkv; sp.Sq = Sq; sp.G = sh.G;
@@ -2076,44 +2079,35 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
         // (i + INT32_MAX - Sq - 64 is above every key for i >= 0 and within 32 bits for the i < Sq + 32 of a tile)
         sp.off = causal ? Skv - Sq : INT32_MAX - Sq - 64;
         sp.c = p.c;
-        const unsigned wgs = (unsigned)sp.nrest * sp.ntile * sp.splits;
-        if (sp.splits > 1) {
-            sp.reserve = 1;
-            launch_shared_split(sp, 1, 1024);
-            if (hipGetLastError() != hipSuccess) return ATTN_E_LAUNCH;
-            sp.reserve = 0;
-            launch_shared_split(sp, wgs, SPLIT_LDS_BYTES);
-        } else {
-            hipLaunchKernelGGL(attn_fwd_split_kernel<false>, dim3(wgs), dim3(NTHREADS), SPLIT_LDS_BYTES, st, sp);
-        }
-        return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_E_LAUNCH;
-    }
-
-    const dim3 block(NTHREADS);
-    if (r.kind == ROUTE_SHARED) {
+    } else {
         sp.tile_pos = sh.tile_pos;
         sp.ntile = r.sched.ntile;
         sp.nrest = r.share.groups;
         sp.units = r.share.units;
-        sp.reserve = NWAVES;
-        launch_shared_split(sp, 1, 1024);
-        if (hipGetLastError() != hipSuccess) return ATTN_E_LAUNCH;
-        if (causal)
-            hipLaunchKernelGGL((attn_fwd_kernel<true, FORM_SHARED>), dim3(r.share.wgs), block, LDS_BYTES, st, p);
-        else
-            hipLaunchKernelGGL((attn_fwd_kernel<false, FORM_SHARED>), dim3(r.share.wgs), block, LDS_BYTES, st, p);
-        return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_E_LAUNCH;
     }
-    const dim3 grid((unsigned)(r.sched.slots * 8));
-    if (causal && neg)
-        hipLaunchKernelGGL((attn_fwd_kernel<true, FORM_NEG>), grid, block, LDS_BYTES, st, p);
-    else if (causal)
-        hipLaunchKernelGGL((attn_fwd_kernel<true, FORM_POS>), grid, block, LDS_BYTES, st, p);
-    else if (neg)
-        hipLaunchKernelGGL((attn_fwd_kernel<false, FORM_NEG>), grid, block, LDS_BYTES, st, p);
-    else
-        hipLaunchKernelGGL((attn_fwd_kernel<false, FORM_POS>), grid, block, LDS_BYTES, st, p);
-    return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_E_LAUNCH;
+    // Each launch is judged by its own status: the runtime's record of the thread's last error may hold an earlier
+    // call's.  (One that fails is taken out of that record, as its report is the return value.)
+    auto launch = [&](const void *kernel, unsigned wgs, int lds, void *params) -> bool {
+        if (hipLaunchKernel(kernel, dim3(wgs), dim3(NTHREADS), &params, lds, st) == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
+    };
+    return enqueue(r, [&](Step step) -> bool {
+        if (step != STEP_MAIN) {
+            sp.reserve = step == STEP_GIVE ? -1 : r.kind == ROUTE_SHARED ? NWAVES : 1;
+            return launch((const void *)attn_fwd_split_kernel<true>, 1, 1024, &sp);
+        }
+        sp.reserve = 0;
+        if (r.kind == ROUTE_SPLIT)
+            return launch(sp.splits > 1 ? (const void *)attn_fwd_split_kernel<true> : (const void *)attn_fwd_split_kernel<false>,
+                          (unsigned)sp.nrest * sp.ntile * sp.splits, SPLIT_LDS_BYTES, &sp);
+        if (r.kind == ROUTE_SHARED)
+            return launch(causal ? (const void *)attn_fwd_kernel<true, FORM_SHARED> : (const void *)attn_fwd_kernel<false, FORM_SHARED>,
+                          r.share.wgs, LDS_BYTES, &p);
+        const void *whole = causal ? (neg ? (const void *)attn_fwd_kernel<true, FORM_NEG> : (const void *)attn_fwd_kernel<true, FORM_POS>)
+                                   : (neg ? (const void *)attn_fwd_kernel<false, FORM_NEG> : (const void *)attn_fwd_kernel<false, FORM_POS>);
+        return launch(whole, (unsigned)(r.sched.slots * 8), LDS_BYTES, &p);
+    });
 }
 
 const char *attn_strerror(int code)

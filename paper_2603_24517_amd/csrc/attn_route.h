@@ -309,5 +309,19 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
     }
 }
 
+// The launches of a call: where items are shared, one that takes the device memory for the parts stands in front of the one
+// that uses it and gives it back, and if that fails, another one gives the memory back (or, if none can be launched any more,
+// nothing does).  `go` enqueues a step and says whether the runtime took it.  Returns a code of include/attn.h.
+enum Step { STEP_TAKE, STEP_MAIN, STEP_GIVE };
+template <class Go>
+int enqueue(const Route &p, Go &&go)
+{
+    const bool takes = p.kind == ROUTE_SHARED || (p.kind == ROUTE_SPLIT && p.split.splits > 1);
+    if (takes && !go(STEP_TAKE)) return ATTN_E_LAUNCH;
+    if (go(STEP_MAIN)) return ATTN_OK;
+    if (takes) (void)go(STEP_GIVE);
+    return ATTN_E_LAUNCH;
+}
+
 }  // namespace attn
 #endif

@@ -14,3 +14,13 @@ extern "C" int route(int B, int Hq, int Hkv, int Sq, int Skv, int causal, int nc
     out[3] = r.kind == attn::ROUTE_SPLIT ? r.split.units : r.kind == attn::ROUTE_SHARED ? r.share.units : 0;    // pool units
     return ATTN_OK;
 }
+
+// The steps that are enqueued for a call if the runtime takes all but step `refused` (-1: all), as letters in `log`.
+extern "C" int steps(int B, int Hq, int Hkv, int Sq, int Skv, int causal, int ncu, int refused, char *log)
+{
+    attn::Route r = {};
+    const int rc = attn::make_shape(B, Hq, Hkv, Sq, Skv, r.shape, r.sched);
+    if (rc != ATTN_OK) return rc;
+    attn::make_route(B, Hkv, Skv, causal, ncu, r);
+    return attn::enqueue(r, [&](attn::Step s) { *log++ = "TMG"[s]; return s != refused; });
+}

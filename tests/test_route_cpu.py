@@ -14,12 +14,15 @@ NCU = 256
 
 
 @pytest.fixture(scope="module")
-def route(tmp_path_factory):
+def lib(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("route") / "route.so")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-o", so,
                     os.path.join(HERE, "route_shim.cpp")], check=True)
-    lib = ctypes.CDLL(so)
+    return ctypes.CDLL(so)
 
+
+@pytest.fixture(scope="module")
+def route(lib):
     def call(B, Hq, Hkv, Sq, Skv, causal=True, ncu=NCU):
         out = (ctypes.c_longlong * 4)()
         rc = lib.route(B, Hq, Hkv, Sq, Skv, int(causal), ncu, out)
@@ -76,3 +79,17 @@ def test_calls_of_the_bits_test_are_shared(route):
     for shape in T.SHARED_CALLS:
         for causal in (False, True):
             assert route(*shape, causal)["kind"] == SHARED, (shape, causal)
+
+
+@pytest.mark.parametrize("shape,takes", [((1, 32, 8, 1, 32768), True), ((1, 32, 8, 512, 16384), True),
+                                         ((1, 4, 4, 512, 512), False), ((8, 16, 16, 4096, 4096), False)])
+def test_memory_taken_for_a_launch_that_fails_is_given_back(lib, shape, takes):
+    def steps(refused):
+        log = ctypes.create_string_buffer(8)
+        rc = lib.steps(*shape, 1, NCU, refused, log)
+        return rc, log.value.decode()
+    TAKE, MAIN, GIVE = range(3)
+    assert steps(-1) == (A.ATTN_OK, "TM" if takes else "M")
+    assert steps(MAIN) == (A.ATTN_E_LAUNCH, "TMG" if takes else "M")
+    assert steps(TAKE) == ((A.ATTN_E_LAUNCH, "T") if takes else (A.ATTN_OK, "M"))
+    assert steps(GIVE)[0] == A.ATTN_OK

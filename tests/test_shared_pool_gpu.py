@@ -1,0 +1,69 @@
+"""The device memory that launches with shared items take and give back."""
+import ctypes
+import math
+
+import pytest
+import torch
+
+import paper_2603_24517_amd as A
+from paper_2603_24517_amd import probe as P
+import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+SCALE = 1.0 / math.sqrt(128)
+
+
+def _call(shape, entry=None, causal=False):
+    B, Hq, Hkv, Sq, Skv = shape
+    q, k, v = (t.cuda() for t in U.rand_qkv(*shape, seed=9700))
+    o, lse = torch.empty_like(q), torch.empty((B, Hq, Sq), device="cuda")
+    fwd = A.attn_fwd if entry is None else (lambda *a: P.variant_attn_fwd(entry, *a))
+    stream = torch.cuda.current_stream().cuda_stream
+    return (lambda: fwd(q, k, v, o, lse, B, Hq, Hkv, Sq, Skv, 128, causal, SCALE, stream)), o, lse
+
+
+@pytest.mark.parametrize("entry,shape", [(None, (1, 8, 8, 1, 65536)), ("always_share", (1, 1, 1, 256, 65536))],
+                         ids=["split_key_kernel", "256_row_kernel"])
+def test_units_are_given_back(entry, shape):
+    """Without units one workgroup takes all of an item, which for these items takes several times as long (measured: 10 and
+    more).  Were a launch's units lost, the pool of 64 would be used up after at most that many launches."""
+    call, _, _ = _call(shape, entry)
+
+    def ms(n=10):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(n):
+            assert call() == 0
+        e1.record()
+        torch.cuda.synchronize()
+        return e0.elapsed_time(e1) / n
+
+    first = min(ms() for _ in range(3))
+    for _ in range(500):
+        assert call() == 0
+    last = min(ms() for _ in range(3))
+    no_pool, _, _ = _call(shape, "no_pool" if entry is None else "always_share_no_pool")
+    call = no_pool
+    without = min(ms() for _ in range(3))
+    print(f"first {first:.4f} last {last:.4f} without units {without:.4f} ms", flush=True)
+    assert last < 2 * first and without > 4 * first
+
+
+def test_call_after_an_error_of_another_call():
+    """A HIP call that failed before, and whose error nobody has fetched, is no business of a launch: it runs, says so, and
+    leaves the record as it is."""
+    lib = A.load()          # (its dependencies hold the HIP runtime)
+    lib.hipSetDevice.argtypes, lib.hipGetLastError.argtypes = [ctypes.c_int], []
+    call, o, lse = _call((1, 32, 8, 1, 8192))
+    assert call() == 0
+    torch.cuda.synchronize()
+    ref = o.clone(), lse.clone()
+    for t in (o, lse):
+        t.fill_(float("nan"))
+    torch.cuda.synchronize()
+    error = lib.hipSetDevice(4096)
+    rc = [call() for _ in range(100)]
+    recorded = lib.hipGetLastError()
+    assert error != 0 and recorded == error and rc == [0] * 100, (error, recorded, rc)
+    torch.cuda.synchronize()
+    assert torch.equal(o, ref[0]) and torch.equal(lse, ref[1])
