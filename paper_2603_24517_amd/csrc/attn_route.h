@@ -288,12 +288,15 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
     // are shared out among the wavefronts of a workgroup, and among workgroups, fill the device instead.
     // Few rows, measured, 256-row / split-key kernel, us: 4 rows x 4000 keys, 128 items 77.9 / 42.4; 4 x 4096, 512 items
     // 248.3 / 191.7 (1.07 GB of K and V); 4 x 500, 512 items 35.6 / 24.1; 1 x 8000, 256 items 232.9 / 175.2.
-    // More than 32 of them are two tiles, which read the same keys.  That pays while all tiles run at once, and for up to
-    // half as many again if the keys are few enough for the second tile to find them in a cache: 64 rows x 5000, 256 tiles
-    // 93.2 / 70.1; 288 tiles, x 1500 40.1 / 36.1, x 5000 105.9 / 115.0, x 16000 292 / 386; 384 tiles, x 400 20.3 / 17.1, x 1500
-    // 47.0 / 44.9, x 5000 131.6 / 158.5; 512 tiles, x 1500 55.2 / 65.6; 56 rows x 4096, 1024 tiles 257 / 381.
+    // More than 32 of them are two tiles, which read the same keys.  That pays while all tiles run at once, and while the keys
+    // are few enough for the second tile to find them in a cache, where 256-row items leave much of a round empty: up to three
+    // quarters of the compute units' number of them, and from one to five quarters.  64 rows x 5000, 256 tiles 93.2 / 70.1; 288 tiles,
+    // x 1500 40.1 / 36.1, x 5000 105.9 / 115.0, x 16000 292 / 386; 384 tiles, x 400 20.3 / 17.1, x 1500 47.0 / 44.9, x 5000 131.6 / 158.5;
+    // 512 tiles, x 1500 55.2 / 65.6; 544 .. 640 tiles, x 250 24.8 / 20.3, x 1000 57.0 / 51.2, x 1500 78.5 / 73.0, x 2048 96.4 / 110.4; 768
+    // tiles, x 1000 58.0 / 59.5; 1024 tiles of 28 rows x 4096 257 / 381.
     const int64_t rows = (int64_t)Sq * sh.pack;
-    const bool few_rows = rows <= 32 || (rows <= 64 && (split_items <= ncu || (split_items * 2 <= 3 * ncu && Skv <= 2048)));
+    const bool few_rows = rows <= 32 || (rows <= 64 && (total * 2 <= ncu || (total * 4 <= 3 * ncu && Skv <= 2048) ||
+                                                        (total > ncu && total * 4 <= 5 * ncu && Skv <= 1536)));
     const bool small = ATTN_SMALL_PATH == 2 || (ATTN_SMALL_PATH == 1 && ((total * 4 <= ncu && !share) || few_rows));
     p.kind = share ? ROUTE_SHARED : ROUTE_WHOLE;
     const int splits = split_parts(split_items, split_ntile, (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS, ncu);
