@@ -8,8 +8,9 @@
  * heads follow the benchmark configurations of sections 4.1 and 4.3.
  *
  * All pointers are DEVICE pointers owned by the caller.  The library allocates
- * nothing, never synchronises and never throws; its code object brings 64 MiB
- * of device memory for partial results, which launches share out among
+ * nothing, never synchronises and never throws; its code object brings 256 MiB
+ * of device memory for partial results (once per device that the library is used
+ * on, whether or not a call needs it), which launches share out among
  * themselves on the device.
  */
 #ifndef PAPER_2603_24517_ATTN_H

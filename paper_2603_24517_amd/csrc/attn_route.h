@@ -293,7 +293,7 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
     // quarters of the compute units' number of them, and from one to five quarters.  64 rows x 5000, 256 tiles 93.2 / 70.1; 288 tiles,
     // x 1500 40.1 / 36.1, x 5000 105.9 / 115.0, x 16000 292 / 386; 384 tiles, x 400 20.3 / 17.1, x 1500 47.0 / 44.9, x 5000 131.6 / 158.5;
     // 512 tiles, x 1500 55.2 / 65.6; 544 .. 640 tiles, x 250 24.8 / 20.3, x 1000 57.0 / 51.2, x 1500 78.5 / 73.0, x 2048 96.4 / 110.4; 768
-    // tiles, x 1000 58.0 / 59.5; 1024 tiles of 28 rows x 4096 257 / 381.
+    // tiles, x 1000 58.0 / 59.5; 56 rows, 1024 tiles, x 4096 257 / 381.
     const int64_t rows = (int64_t)Sq * sh.pack;
     const bool few_rows = rows <= 32 || (rows <= 64 && (total * 2 <= ncu || (total * 4 <= 3 * ncu && Skv <= 2048) ||
                                                         (total > ncu && total * 4 <= 5 * ncu && Skv <= 1536)));

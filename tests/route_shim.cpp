@@ -24,3 +24,5 @@ extern "C" int steps(int B, int Hq, int Hkv, int Sq, int Skv, int causal, int nc
     attn::make_route(B, Hkv, Skv, causal, ncu, r);
     return attn::enqueue(r, [&](attn::Step s) { *log++ = "TMG"[s]; return s != refused; });
 }
+
+extern "C" long long pool_bytes() { return (long long)attn::POOL_UNITS * attn::POOL_UNIT_BYTES; }

@@ -2,6 +2,7 @@
 csrc/attn_route.h, compiled without HIP."""
 import ctypes
 import os
+import re
 import subprocess
 
 import pytest
@@ -94,3 +95,10 @@ def test_memory_taken_for_a_launch_that_fails_is_given_back(lib, shape, takes):
     assert steps(MAIN) == (A.ATTN_E_LAUNCH, "TMG" if takes else "M")
     assert steps(TAKE) == ((A.ATTN_E_LAUNCH, "T") if takes else (A.ATTN_OK, "M"))
     assert steps(GIVE)[0] == A.ATTN_OK
+
+
+def test_header_states_the_device_memory_of_the_code_object(lib):
+    lib.pool_bytes.restype = ctypes.c_longlong
+    text = open(os.path.join(os.path.dirname(HERE), "include", "attn.h")).read()
+    stated = re.search(r"(\d+) MiB\s+\*\s+of device memory", text)
+    assert stated and int(stated.group(1)) << 20 == lib.pool_bytes()
