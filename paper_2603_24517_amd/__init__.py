@@ -86,7 +86,6 @@ def attention(q, k, v, causal=False, scale=None):
     Returns (O BF16 [B,Sq,Hq,D], LSE FP32 [B,Hq,Sq]).
     """
     import torch
-    from torch._C import _cuda_getCurrentRawStream
     if not (q.is_cuda and k.is_cuda and v.is_cuda):
         raise ValueError("attention() needs device tensors; there is no CPU path")
     bf16 = torch.bfloat16
@@ -104,6 +103,7 @@ def attention(q, k, v, causal=False, scale=None):
     lse = torch.empty((B, Hq, Sq), dtype=torch.float32, device=q.device)
     # The raw stream handle, and no change of device where q's is the current one: the Stream object and the device
     # context of the general form cost more than the launch itself.
+    from torch._C import _cuda_getCurrentRawStream
     index = q.get_device()
     args = (q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), B, Hq, Hkv, Sq, Skv, D,
             1 if causal else 0, float(scale), _cuda_getCurrentRawStream(index))

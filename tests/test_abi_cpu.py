@@ -128,3 +128,12 @@ def test_row_sampler_terminates_and_is_stratified():
     assert {(b, h) for b, h, _ in rows.tolist()} == {(b, h) for b in range(w.B) for h in range(w.Hq)}
     assert {0, w.Sq - 1} <= set(rows[:, 2].tolist())
     assert (W.sample_rows(w, 4096) == rows).all()               # seeded
+
+
+def test_no_cpu_fallback_without_a_device_build_of_torch(monkeypatch):
+    """The argument checks come before anything that only a device build of torch has."""
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    x = torch.zeros(1, 8, 2, 128, dtype=torch.bfloat16)
+    with pytest.raises(ValueError):
+        A.attention(x, x, x)
