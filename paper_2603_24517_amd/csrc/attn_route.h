@@ -20,6 +20,7 @@
 #endif
 
 namespace attn {
+namespace {        // (nothing of it is exported by the library)
 
 constexpr int HD = 128;              // head dimension
 constexpr int BN = 64;               // keys per K/V block
@@ -326,5 +327,6 @@ int enqueue(const Route &p, Go &&go)
     return ATTN_E_LAUNCH;
 }
 
+}  // namespace
 }  // namespace attn
 #endif

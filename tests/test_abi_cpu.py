@@ -137,3 +137,11 @@ def test_no_cpu_fallback_without_a_device_build_of_torch(monkeypatch):
     x = torch.zeros(1, 8, 2, 128, dtype=torch.bfloat16)
     with pytest.raises(ValueError):
         A.attention(x, x, x)
+
+
+def test_attention_library_exports_no_internal_symbols():
+    import subprocess
+    out = subprocess.run(["nm", "-D", "--defined-only", A.LIB_PATH], check=True, capture_output=True, text=True).stdout
+    names = {ln.split()[-1] for ln in out.splitlines()}
+    # (__hip_cuid_<hash>: the compiler's mark of a translation unit with device code)
+    assert {n for n in names if not n.startswith("__hip_cuid_")} == {"attn_fwd", "attn_strerror", "attn_version"}
