@@ -4,8 +4,8 @@
     python -m paper_2603_24517_amd.build --all      that, the measurement-aid library (include/attn_probe.h)
                                                      and every variant of the attention kernel
 
-The variants are builds of the same source with one compile-time switch each (see the head of
-csrc/attn_fwd.hip); they exist to measure the shipped choices against their alternatives and are
+The variants are builds of the same source with one compile-time switch each (see the heads of
+csrc/attn_fwd.hip and csrc/attn_route.h); they exist to measure the shipped choices against their alternatives and are
 never loaded by the product path.
 """
 import os
@@ -34,7 +34,7 @@ VARIANTS = {
     # every launch through the 256-row kernel / every launch through the split-key kernel for small problems
     "no_small_path": ["-DATTN_SMALL_PATH=0"],
     "always_small_path": ["-DATTN_SMALL_PATH=2"],
-    # the split-key kernel without its pool for partial results (what a launch does that finds the pool in use)
+    # no device memory for partial results (what a launch does that finds it in use)
     "no_pool": ["-DATTN_POOL=0"],
     # the 256-row kernel with whole items only / with items shared among workgroups wherever the device memory for it
     # serves / the same, finding that memory in use

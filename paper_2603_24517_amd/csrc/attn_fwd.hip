@@ -47,8 +47,8 @@
 // Where whole items would leave compute units without work for long (fewer items than compute units, a last
 // round with few of them), the kernel's shared form cuts the line of all items' key blocks into
 // stretches of equal length, one for each workgroup; an item that a cut falls into is added up from its parts
-// (512 rows against 16384 keys, 32 heads on 8, causal: 203 -> 127 us; one sequence of 16384, 4 heads, causal:
-// 324 -> 248).
+// (512 rows against 16384 keys, 32 heads on 8, causal: whole items 215 us, shared 127; one sequence of 16384, 4 heads,
+// causal: 309 and 238).
 //
 // A second kernel at the end of this file serves small problems (few query
 // rows, however many keys): 32-row work items whose key blocks are shared out
@@ -85,8 +85,8 @@
 #ifndef ATTN_ITEM_OVERLAP
 #define ATTN_ITEM_OVERLAP 1
 #endif
-// ATTN_POOL: 1 (shipped); 0 every launch of the split-key kernel that would share its items among workgroups finds the
-// pool for partial results in use, and takes the path for that case.
+// ATTN_POOL: 1 (shipped); 0 every launch that shares its items among workgroups finds the device memory for their parts in
+// use, and takes the path for that case.
 #ifndef ATTN_POOL
 #define ATTN_POOL 1
 #endif
@@ -279,10 +279,10 @@ __device__ __forceinline__ unsigned long long phase_now() {
 // allocation and no host-side bookkeeping, and goes when the library is unloaded.  A launch takes a run of
 // units and gives it back, both on the device: a one-workgroup launch in front finds a free run and
 // leaves its number in the first LSE element of every item, which is the launch's own memory and is overwritten by the
-// result only after all workgroups of the item have read it.  The 256-row kernel's shared form takes 18 units or fewer.  Launches on any number of streams, from
-// any thread and replayed from graphs thus never share units; if no run is free (the pool serves at
-// least POOL_UNITS / SHARE_MAX_UNITS launches at a time), the first workgroup of each item takes all of its parts and
-// the others leave, which is slower but needs no memory.
+// result only after all workgroups of the item have read it.  Launches on any number of streams, from any thread and
+// replayed from graphs thus never share units.  If no run is free (the pool serves at least POOL_UNITS / SHARE_MAX_UNITS
+// launches at a time), the first workgroup of each item takes all of its parts and the others leave, which is slower but
+// needs no memory and gives the same bits.
 constexpr uint32_t POOL_NONE = 0xffu;
 // How the number (or POOL_NONE) stands in an LSE element: as a NaN whose low half is no result's.  (A NaN of a
 // result has the default payload or one that came in with a BF16 value, whose low 16 bits are zero.)  Where no run was
@@ -1549,7 +1549,7 @@ constexpr int SPLIT_Q_BASE = SPLIT_STATE_BASE + NWAVES * 3 * 32 * 4;   // then t
 constexpr int SPLIT_LDS_BYTES = SPLIT_Q_BASE + 32 * ROW_BYTES;
 static_assert(SPLIT_Q_BASE % 1024 == 0 && NWAVES * 4 == 32, "each wavefront requests four of the 32 Q rows, 1 KiB");
 static_assert(SPLIT_WAVE_BYTES == 32 * HD * 4, "a wavefront's partial accumulator takes the place of its two blocks");
-static_assert(SPLIT_LDS_BYTES <= LDS_BYTES, "the split kernel is launched with the same dynamic LDS size");
+static_assert(SPLIT_LDS_BYTES <= LDS_BYTES, "a workgroup fits a CU");
 
 // Two forms: items of one workgroup each, and SHARED ones (with the launch in front of them).  The mask is a number, not a
 // form: every block goes through the masked softmax anyway.  (One kernel for both, with the code of the shared items beside

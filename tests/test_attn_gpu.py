@@ -135,7 +135,7 @@ def test_deterministic_and_stream_gpu(shape):
 
 @pytest.mark.parametrize("shape", [(2, 8, 2, 700, 900), (4, 16, 4, 1000, 1100)], ids=["split_key_kernel", "main_kernel"])
 def test_launch_recorded_in_a_hip_graph_replays_identically(shape):
-    """attn_fwd only enqueues one kernel, so (after one ordinary call on the device) it can be recorded
+    """attn_fwd only enqueues one kernel or two, so (after one ordinary call on the device) it can be recorded
     into a HIP graph; every replay, with other work and synchronisations in between, must reproduce the
     directly launched result bit for bit."""
     B, Hq, Hkv, Sq, Skv = shape
