@@ -55,6 +55,7 @@
 // among the wavefronts of a workgroup and whose partial results are merged
 // through LDS.
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 #include <math.h>
 #include <float.h>
@@ -1533,15 +1534,18 @@ struct SplitParams {
     int tile_pos;           // query positions per work item = 32 / pack
     int ntile;              // ceil(Sq / tile_pos)
     int nrest;              // B * Hkv * chunks; items = ntile * nrest
+    Div d_nrs, d_chunks, d_hkv;     // exact division by nrest * splits, chunks, Hkv
+    int off;                // key j valid iff j <= i + off: Skv - Sq, or without a mask a number that makes all of them valid
+    float c;                // scale * log2(e)
+    // (up to here, within two cache lines, what items of one workgroup need; for the shared form:)
     int splits;             // workgroups that share an item
+    Div d_splits;
     int units;              // POOL_UNIT_BYTES units of device memory the launch needs, 0 if splits == 1
     int reserve;            // > 0: this launch is one workgroup that takes the units for the launch behind it, and clears
                             // this many counters per item (the item geometry is that launch's); < 0: one that gives them
                             // back, because there was no launch behind it
-    Div d_nrs, d_splits, d_chunks, d_hkv;       // exact division by nrest * splits, splits, chunks, Hkv
-    int off;                // key j valid iff j <= i + off: Skv - Sq, or without a mask a number that makes all of them valid
-    float c;                // scale * log2(e)
 };
+static_assert(offsetof(SplitParams, splits) <= 128, "two cache lines of kernel arguments");
 constexpr int SPLIT_TILE_BYTES = SPLIT_KEYS * ROW_BYTES;        // 8 KiB: one K or V block
 constexpr int SPLIT_WAVE_BYTES = 2 * SPLIT_TILE_BYTES;          // per wavefront: its K block, then its V block
 constexpr int SPLIT_STATE_BASE = NWAVES * SPLIT_WAVE_BYTES;     // after them: m, l, lr of every wavefront
