@@ -56,6 +56,7 @@ def test_grid_of_few_row_calls_stays_launchable(route):
 @pytest.mark.parametrize("shape,shared", [
     ((1, 32, 8, 1, 1280), True), ((2, 16, 16, 1, 1280), True), ((4, 16, 16, 1, 1280), True), ((1, 8, 8, 1, 1216), False),
     ((8, 16, 16, 1, 1600), False), ((8, 16, 16, 1, 1800), True),            # 128 items of one tile
+    ((85, 1, 1, 1, 1280), True), ((86, 1, 1, 1, 1280), False),              # three parts, two
     ((1, 32, 4, 51, 1700), False), ((1, 32, 4, 51, 2200), True),            # 13 tiles, 52 items
     ((1, 4, 4, 700, 2400), False), ((1, 4, 4, 700, 2700), True),            # 22 tiles, 88 items
 ])

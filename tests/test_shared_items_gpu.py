@@ -13,7 +13,7 @@ import gpu_util as U
 pytestmark = pytest.mark.gpu
 SCALE = 1.0 / math.sqrt(128)
 
-# B, Hq, Hkv, Sq, Skv: items x parts <= 256, from 40 blocks of 32 keys on (54 with more than 64 items, 66 with more than 2 tiles)
+# B, Hq, Hkv, Sq, Skv: items x parts <= 256, from 40 blocks of 32 keys on (54 with more than 85 items, 66 with more than 2 tiles)
 SHAPES = [
     (1, 1, 1, 1, 1248), (1, 1, 1, 1, 1249), (1, 8, 1, 4, 1280), (1, 8, 1, 5, 1281),   # 39 and 40 blocks, full and ragged; 32 and 40 rows
     (1, 32, 8, 1, 3001), (2, 6, 2, 7, 5000), (1, 4, 4, 33, 2049), (3, 16, 2, 16, 2199),
