@@ -160,12 +160,11 @@ inline int whole_items_length(const Route &p, bool causal, int extra)
 //
 // From how many blocks on it pays depends on where K and V come from, which more workgroups read faster from HBM.  One
 // part / shared, us, K and V from HBM (from the last cache, where a repeated call finds them): 8 items of 40 blocks
-// 16.6 / 13.5 (10.9 / 12.0); 64 of 40 18.6 / 16.7 (12.9 / 15.6); 80 of 41 19.4 / 18.5 (13.4 / 17.2); 128 in two parts, of 40 blocks
-// 20.7 / 22.5 (16.3 / 20.7), of 54
-// 27.2 / 27.0, of 66 32.0 / 30.9 (24.2 / 27.1).  Many tiles of a sequence read the same keys, which then come from a cache
-// either way: 13 tiles, 52 items of 54 blocks 14.5 / 15.2 (13.9 / 14.7), of 66 18.8 / 16.7 (15.5 / 15.3); 7 tiles, 84 items
-// of 66 21.5 / 17.9 (15.4 / 16.3); 22 tiles, 88 items
-// of 66 18.1 / 18.3 (15.4 / 16.4), of 82 22.6 / 20.8.
+// 16.6 / 13.5 (10.9 / 12.0); 64 of 40 18.6 / 16.7 (12.9 / 15.6); 80 of 41 19.4 / 18.5 (13.4 / 17.2); 128, in two parts, of 40
+// 20.7 / 22.5 (16.3 / 20.7), of 54 27.2 / 27.0, of 66 32.0 / 30.9 (24.2 / 27.1).  Many tiles of a sequence read the same keys,
+// which then come from a cache either way: 13 tiles, 52 items of 54 blocks 14.5 / 15.2 (13.9 / 14.7), of 66 18.8 / 16.7
+// (15.5 / 15.3); 7 tiles, 84 items of 66 21.5 / 17.9 (15.4 / 16.3); 22 tiles, 88 items of 66 18.1 / 18.3 (15.4 / 16.4), of 82
+// 22.6 / 20.8.
 inline int split_parts(int64_t items, int ntile, int blocks, int ncu)
 {
     const bool many = items * 3 > ncu;          // at most two parts
