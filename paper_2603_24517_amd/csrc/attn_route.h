@@ -206,6 +206,8 @@ inline int64_t split_ns(int64_t items, int ntile, int64_t blocks, int ncu)
     return (5000 + 163 * blocks / parts) * rounds + (parts > 1 ? 4000 + 250 * parts : 0);
 }
 
+constexpr int64_t LAST_CACHE_BYTES = 256ll << 20;       // of an MI355X
+
 // Sizes as attn_fwd() takes them, all positive: what the kernels' index arithmetic holds.  Returns a code of include/attn.h
 // (and, if that is ATTN_OK, the shape).
 inline int make_shape(int B, int Hq, int Hkv, int Sq, int Skv, Shape &sh, Sched &sc)
@@ -261,7 +263,8 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
     const int split_ntile = (Sq + split_tile_pos - 1) / split_tile_pos;
     const int64_t split_items = (int64_t)B * Hkv * sh.chunks * split_ntile;
     // The same work as a line cut into equal stretches.  From 4 items per compute unit on, whole items leave at most a fifth of the chip idle at the
-    // end, and sharing has not been faster.  (5 %: what the estimates are worth.)
+    // end, and sharing has not been faster.  (5 %: what the estimates are worth; of 60 calls that they put further ahead, none was
+    // slower shared.)
     Share &sr = p.share;
     sr.wgs = 8 * cu_slots;
     sr.groups = (int)((int64_t)B * Hkv * sh.chunks);
@@ -279,9 +282,14 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
             const int64_t slots = sr.wgs + (total < sr.wgs ? total : sr.wgs);
             sr.units = (int)((SHARE_HEADER_BYTES + slots * SHARE_SLOT_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
             const int64_t blocks32 = (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS;
-            const int64_t whole = total * 4 <= ncu && ATTN_SMALL_PATH == 1 ? split_ns(split_items, split_ntile, blocks32, ncu)
-                                                                           : whole_items_ns(p, causal != 0);
-            share = ATTN_SHARE == 2 || shared_ns(p, total) * 105 < whole * 100;
+            const bool few = total * 4 <= ncu && ATTN_SMALL_PATH == 1;      // (the other way is the split-key kernel)
+            const int64_t whole = few ? split_ns(split_items, split_ntile, blocks32, ncu) : whole_items_ns(p, causal != 0);
+            // Whole items that run at once walk through the keys of a group together, and one of them brings a block into the
+            // XCD's L2 for all.  Stretches of the line do not, which tells when K and V are larger than the last cache: 9 x 571 x
+            // 33965, 16 heads (2.5 GB), estimated 10 % faster shared, whole 1669, shared 1821; 20 x 281 x 25757 (4.2 GB), 12 %, 1912 and 2014;
+            // 13 x 1975 x 14973, 4 heads (0.4 GB), 14 %, 693 and 705; 12 x 221 x 9026 (0.9 GB), 15 %, 248 and 232.
+            const bool cached = (int64_t)B * Hkv * Skv * HD * 4 <= LAST_CACHE_BYTES;
+            share = ATTN_SHARE == 2 || shared_ns(p, total) * (few || cached ? 105 : 115) < whole * 100;
         }
     }
 

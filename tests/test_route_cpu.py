@@ -103,3 +103,11 @@ def test_header_states_the_device_memory_of_the_code_object(lib):
     text = open(os.path.join(os.path.dirname(HERE), "include", "attn.h")).read()
     stated = re.search(r"(\d+) MiB\s+\*\s+of device memory", text)
     assert stated and int(stated.group(1)) << 20 == lib.pool_bytes()
+
+
+@pytest.mark.parametrize("shape,causal,kind", [
+    ((9, 16, 16, 571, 33965), False, WHOLE), ((8, 4, 4, 1593, 21904), True, WHOLE), ((8, 40, 40, 413, 3398), False, WHOLE),
+    ((7, 40, 40, 153, 7606), False, SHARED), ((4, 16, 16, 439, 9822), True, SHARED),        # (far enough ahead all the same)
+])
+def test_keys_beyond_the_last_cache_are_shared_only_far_ahead(route, shape, causal, kind):
+    assert route(*shape, causal)["kind"] == kind
