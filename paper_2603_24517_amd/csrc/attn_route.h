@@ -289,7 +289,7 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
             // 33965, 16 heads (2.5 GB), estimated 10 % faster shared, whole 1669, shared 1821; 20 x 281 x 25757 (4.2 GB), 12 %, 1912 and 2014;
             // 13 x 1975 x 14973, 4 heads (0.4 GB), 14 %, 693 and 705; 12 x 221 x 9026 (0.9 GB), 15 %, 248 and 232.
             const bool cached = (int64_t)B * Hkv * Skv * HD * 4 <= LAST_CACHE_BYTES;
-            share = ATTN_SHARE == 2 || shared_ns(p, total) * (few || cached ? 105 : 115) < whole * 100;
+            share = ATTN_SHARE == 2 || shared_ns(p, total) * (few || cached ? 105 : 114) < whole * 100;
         }
     }
 
@@ -300,13 +300,15 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
     // 248.3 / 191.7 (1.07 GB of K and V); 4 x 500, 512 items 35.6 / 24.1; 1 x 8000, 256 items 232.9 / 175.2.
     // More than 32 of them are two tiles, which read the same keys.  That pays while all tiles run at once, and while the keys
     // are few enough for the second tile to find them in a cache, where 256-row items leave much of a round empty: up to three
-    // quarters of the compute units' number of them, and from one to five quarters.  64 rows x 5000, 256 tiles 93.2 / 70.1; 288 tiles,
-    // x 1500 40.1 / 36.1, x 5000 105.9 / 115.0, x 16000 292 / 386; 384 tiles, x 400 20.3 / 17.1, x 1500 47.0 / 44.9, x 5000 131.6 / 158.5;
-    // 512 tiles, x 1500 55.2 / 65.6; 544 .. 640 tiles, x 250 24.8 / 20.3, x 1000 57.0 / 51.2, x 1500 78.5 / 73.0, x 2048 96.4 / 110.4; 768
-    // tiles, x 1000 58.0 / 59.5; 56 rows, 1024 tiles, x 4096 257 / 381.
+    // quarters of the compute units' number of them, and from one to five quarters (six, for very few keys).  64 rows x 5000,
+    // 256 tiles 93.2 / 70.1; 288 tiles, x 1500 40.1 / 36.1, x 5000 105.9 / 115.0, x 16000 292 / 386; 384 tiles, x 400 20.3 / 17.1,
+    // x 1500 47.0 / 44.9, x 5000 131.6 / 158.5; 512 tiles, x 1500 55.2 / 65.6; 544 .. 640 tiles, x 250 24.8 / 20.3, x 1000 57.0 /
+    // 51.2, x 1500 78.5 / 73.0, x 2048 96.4 / 110.4; 672 tiles, x 354 30.2 / 25.3; 704, x 715 46.1 / 42.7; 768, x 1000 58.0 / 59.5;
+    // 56 rows, 1024 tiles, x 4096 257 / 381.
     const int64_t rows = (int64_t)Sq * sh.pack;
     const bool few_rows = rows <= 32 || (rows <= 64 && (total * 2 <= ncu || (total * 4 <= 3 * ncu && Skv <= 2048) ||
-                                                        (total > ncu && total * 4 <= 5 * ncu && Skv <= 1536)));
+                                                        (total > ncu && total * 4 <= 5 * ncu && Skv <= 1536) ||
+                                                        (total > ncu && total * 2 <= 3 * ncu && Skv <= 768)));
     const bool small = ATTN_SMALL_PATH == 2 || (ATTN_SMALL_PATH == 1 && ((total * 4 <= ncu && !share) || few_rows));
     p.kind = share ? ROUTE_SHARED : ROUTE_WHOLE;
     const int splits = split_parts(split_items, split_ntile, (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS, ncu);

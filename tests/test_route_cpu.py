@@ -69,7 +69,7 @@ def test_split_key_items_are_shared_only_where_that_pays(route, shape, shared):
     ((16, 64, 8, 4, 4096), SPLIT), ((64, 64, 8, 4, 4096), SPLIT), ((1024, 32, 8, 1, 128), SPLIT),       # up to 32 rows: any number
     ((16, 64, 8, 5, 4096), SPLIT), ((17, 64, 8, 8, 2048), SPLIT), ((24, 64, 8, 8, 2048), SPLIT),        # 33 .. 64: 256, 272, 384 tiles
     ((34, 64, 8, 8, 1500), SPLIT), ((40, 64, 8, 8, 1500), SPLIT),                                       # 544, 640
-    ((17, 64, 8, 8, 2049), SHARED), ((25, 64, 8, 8, 500), WHOLE), ((41, 64, 8, 8, 500), WHOLE), ((33, 64, 8, 8, 1600), WHOLE), ((64, 64, 8, 7, 4096), WHOLE), ((64, 16, 16, 33, 200), WHOLE),
+    ((17, 64, 8, 8, 2049), SHARED), ((25, 64, 8, 8, 500), WHOLE), ((41, 64, 8, 8, 500), SPLIT), ((41, 64, 8, 8, 1000), WHOLE), ((49, 64, 8, 8, 500), WHOLE), ((33, 64, 8, 8, 1600), WHOLE), ((64, 64, 8, 7, 4096), WHOLE), ((64, 16, 16, 33, 200), WHOLE),
 ])
 def test_few_rows_in_two_tiles_read_keys_twice(route, shape, kind):
     r = route(*shape)
