@@ -60,7 +60,8 @@ enum {
  * Hq / Hkv).  The launch is one kernel, with one workgroup per compute unit of
  * the current device (all of its LDS), each working through a list of such
  * items -- or, when those items would occupy at most a quarter of the compute
- * units or hold at most 64 rows each, one with one workgroup per
+ * units or hold few rows (at most 32, up to 64 where that is faster, and as long
+ * as the grid stays below 2^32 threads), one with one workgroup per
  * 32 query rows that share a K/V head (p heads x 32/p positions), whose
  * wavefronts share the item's keys and merge their partial results through LDS.
  * Where these are fewer than the compute units and the key sequence is long, or
