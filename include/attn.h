@@ -63,8 +63,10 @@ enum {
  * units or hold few rows (at most 32, up to 64 where that is faster, and as long
  * as the grid stays below 2^32 threads), one with one workgroup per
  * 32 query rows that share a K/V head (p heads x 32/p positions), whose
- * wavefronts share the item's keys and merge their partial results through LDS.
- * Where these are fewer than the compute units and the key sequence is long, or
+ * wavefronts share the item's keys and merge their partial results through LDS -- or,
+ * where whole items of 256 rows would be too few to fill the device evenly or mostly start and end, one
+ * with one workgroup of four wavefronts per 128 or 64 query rows.
+ * Where the 32-row items are fewer than the compute units and the key sequence is long, or
  * where whole 256-row items would leave compute units without work for long,
  * several workgroups share an item's keys; the launch is then preceded by one of a
  * single workgroup, which takes the device memory that the partial results pass

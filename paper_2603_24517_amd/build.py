@@ -41,6 +41,9 @@ VARIANTS = {
     "whole_items": ["-DATTN_SHARE=0"],
     "always_share": ["-DATTN_SHARE=2", "-DATTN_SMALL_PATH=0"],
     "always_share_no_pool": ["-DATTN_SHARE=2", "-DATTN_SMALL_PATH=0", "-DATTN_POOL=0"],
+    # every launch through the kernel with workgroups of four wavefronts, in items of 128 rows / of 64
+    "always_rows128": ["-DATTN_ROWS=2"],
+    "always_rows64": ["-DATTN_ROWS=3"],
     "lds_prefetch_1": ["-DATTN_LDS_PREFETCH=1"],
     "lds_prefetch_5": ["-DATTN_LDS_PREFETCH=5"],
     # the shipped kernel plus clock stamps of its first workgroup (exports attn_clocks_read as well)

@@ -50,7 +50,10 @@
 // (512 rows against 16384 keys, 32 heads on 8, causal: whole items 215 us, shared 127; one sequence of 16384, 4 heads,
 // causal: 309 and 238).
 //
-// A second kernel at the end of this file serves small problems (few query
+// A kernel with workgroups of four wavefronts, two on a compute unit, serves what lies between: calls of too few 256-row items to
+// fill the chip evenly, and short sequences (at the end of this file).
+//
+// Another kernel serves small problems (few query
 // rows, however many keys): 32-row work items whose key blocks are shared out
 // among the wavefronts of a workgroup and whose partial results are merged
 // through LDS.
@@ -153,6 +156,7 @@ constexpr int MAT_PREFETCH = ATTN_LDS_PREFETCH;   // LDS reads run this many MFM
 // after the wait that the next item's first tiles need.
 constexpr int wait_vmcnt(int n) { return 0x0F70 | n; }
 constexpr int WAIT_VMCNT0 = wait_vmcnt(0);
+constexpr int WAIT_LGKMCNT0 = 0xC07F;       // s_waitcnt lgkmcnt(0), other counters untouched
 // end of an iteration: everything but the loads of the last REQ_AHEAD-1 iterations has landed
 constexpr int WAIT_ITER_END = wait_vmcnt((REQ_AHEAD - 1) * 2 * LPT);
 
@@ -178,14 +182,9 @@ struct Params {
     Share share;
 };
 
-// "Extreme" below is the raw score that maximises score * c: the largest one for c >= 0, the smallest
-// for c < 0 (NEG), so that the running maximum of the scaled scores is c times the extreme.
-template <bool NEG>
-__device__ __forceinline__ float ext2(float a, float b) { return NEG ? fminf(a, b) : fmaxf(a, b); }
-template <bool NEG>
-__device__ __forceinline__ float lane32_ext(float x) {
+__device__ __forceinline__ float lane32_max(float x) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return ext2<NEG>(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 __device__ __forceinline__ float lane32_sum(float x) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -200,6 +199,7 @@ __device__ __forceinline__ float add_bf16_pair(uint32_t p, float acc) {
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p), ones, acc, false);
 }
+// The raw score that maximises score * c: the largest one for c >= 0, the smallest for c < 0 (NEG).
 template <bool NEG>
 __device__ __forceinline__ float ext3(float a, float b, float c) {
     float r;
@@ -356,14 +356,13 @@ __device__ inline void pool_give(uint32_t u, int n)
     __hip_atomic_fetch_and(&g_pool_taken, ~(((1ull << n) - 1) << u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The forms of the 256-row kernel: whole items for a scale >= 0 and < 0, shared items for both (Q is negated as it is
-// loaded; in the kernel of whole items the branch for that costs 0.2 % of a causal launch).
-enum { FORM_POS, FORM_NEG, FORM_SHARED };
-template <bool CAUSAL, int FORM>
+// The forms of the 256-row kernel: with or without the causal mask, whole items or shared ones.  A negative scale is a wave-uniform
+// branch in the kernel of whole items, where an extreme score is looked for (once per item and where the reference is raised); with shared
+// ones, which have no register for it, Q is negated as it is loaded (in the kernel of whole items that costs 0.2 % of a causal launch).
+template <bool CAUSAL, bool SHARED>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(ATTN_WAVES_PER_SIMD, ATTN_WAVES_PER_SIMD)))
 void attn_fwd_kernel(const Params p)
 {
-    constexpr bool NEG = FORM == FORM_NEG, SHARED = FORM == FORM_SHARED;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
     // Launch constants that only the per-item code needs are read from the kernel argument block where
@@ -844,15 +843,21 @@ void attn_fwd_kernel(const Params p)
     // Raise the running maximum to cover the unmasked block in s; rescale the accumulator and row sum.
     // Maximum of the scaled scores of an unmasked block, per query (log2 units).
     auto block_maximum = [&](f32x16 (&s)[2]) __attribute__((always_inline)) -> float {
-        float mx = ext3<NEG>(s[0][0], s[0][1], s[0][2]);
+        auto extreme = [&](auto sign) __attribute__((always_inline)) -> float {
+            constexpr bool NEG = decltype(sign)::value;
+            float mx = ext3<NEG>(s[0][0], s[0][1], s[0][2]);
 #pragma unroll
-        for (int i = 3; i < 31; i += 2) mx = ext3<NEG>(mx, s[i >> 4][i & 15], s[(i + 1) >> 4][(i + 1) & 15]);
-        mx = ext3<NEG>(mx, s[1][15], s[1][15]);
-        return lane32_ext<NEG>(mx) * c;
+            for (int i = 3; i < 31; i += 2) mx = ext3<NEG>(mx, s[i >> 4][i & 15], s[(i + 1) >> 4][(i + 1) & 15]);
+            return ext3<NEG>(mx, s[1][15], s[1][15]) * c;
+        };
+        return lane32_max(!SHARED && c < 0.0f ? extreme(std::true_type{}) : extreme(std::false_type{}));
     };
     auto raise_reference = [&](f32x16 (&s)[2]) __attribute__((always_inline)) {
-        const float mx = block_maximum(s);
-        const float mn = fmaxf(m, mx);
+        // (the same maximum without a branch on the sign: this code stands in the loop many times and is rarely run)
+        float mx = s[0][0] * c;
+#pragma unroll
+        for (int i = 1; i < 32; ++i) mx = fmaxf(mx, s[i >> 4][i & 15] * c);
+        const float mn = fmaxf(m, lane32_max(mx));
         rescale(mn, __builtin_amdgcn_exp2f(m - mn));
     };
     // Softmax of a block that may hold masked keys (diagonal block, tail block, or a block that lies
@@ -864,17 +869,15 @@ void attn_fwd_kernel(const Params p)
         int lim = keys() - 1;
         if (CAUSAL) lim = min(lim, q0 + (ln & 31) + offset());
         const int kidx = blk * BN + 4 * (ln >> 5);
-        constexpr float NONE = NEG ? INFINITY : -INFINITY;      // extreme of no score at all
-        float mx = NONE;
+        float mx = -INFINITY;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int key = kidx + 32 * t + 8 * (r >> 2) + (r & 3);
-                mx = ext2<NEG>(mx, key <= lim ? s[t][r] : NONE);
+                mx = fmaxf(mx, key <= lim ? s[t][r] * c : -INFINITY);
             }
-        mx = lane32_ext<NEG>(mx);
-        mx = (mx == NONE) ? -INFINITY : mx * c;
+        mx = lane32_max(mx);
         if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
             const float mn = fmaxf(m, mx);
             rescale(mn, (mn == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - mn));
@@ -1795,7 +1798,7 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
                 const int key = kidx + 8 * (r >> 2) + (r & 3);
                 mx = fmaxf(mx, key <= lim ? s[r] : -INFINITY);
             }
-            mx = lane32_ext<false>(mx);
+            mx = lane32_max(mx);
             mx = (mx == -INFINITY) ? -INFINITY : mx * c;
             if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
                 const float mn = fmaxf(m, mx);
@@ -2010,6 +2013,501 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
 #endif
 }
 
+// ---------------------------------------------------------------------------------------------------
+// The kernel with workgroups of four wavefronts, for everything between the two others: calls of too few 256-row items to fill the
+// chip evenly, and short sequences, whose items are mostly prologue and epilogue.  Two workgroups share a compute unit, with a barrier of their own
+// each, so that one computes where the other starts, waits or ends; workgroups are handed out by the hardware as others end,
+// longest first.  (One workgroup of eight wavefronts per compute unit in the same loop: 24 x 200 30.1 us instead of 20.0, 2 x 1500 56 instead of 44.)
+//
+// An item is 128 rows (KG = 1: each wavefront has 32 of them and all keys), or 64 (KG = 2: two pairs of wavefronts share the
+// rows' keys, every other block of 32 each, and add their results up through LDS at the end).  64 rows make twice as many items, each of half
+// as many turns, for twice the K/V traffic from L2 to LDS, which at 64 bytes per clock is what bounds them: 8 x 4096, 16 heads 963 us in items of 128
+// rows, 1242 in items of 64 (256-row kernel 890); 1 x 1111, 32 heads on 8, causal 21.4 and 17.7 (29.5).
+//
+// A turn is 16 MFMAs per wavefront, as in the 256-row kernel: O += P(t-1) V(t-1) and S(t+1) = K(t+1) Q^T alternating, with the softmax of S(t)
+// between them, one exponent ahead.  A wavefront alone on its SIMD takes 890 cycles for one (512 of matrix pipe; 700 without the vector
+// instructions), two of them 1500 together.  K and V stages: four (KG = 1) or two (KG = 2) of each, 64 KiB, requested that many
+// turns before use less one.
+struct RowsParams {
+    const __bf16 *q, *k, *v;
+    __bf16 *o;
+    float *lse;
+    int Hq, Hkv, Sq, Skv, G;
+    int pack, pack_log2;    // as in SplitParams: row r of an item is head r % pack, position r / pack
+    int chunks;             // G / pack
+    int tile_pos;           // query positions per work item = 128 / pack
+    int ntile;              // ceil(Sq / tile_pos)
+    int nrest;              // B * Hkv * chunks; items = ntile * nrest
+    int window, window0;    // (group, K/V head, batch entry) units that are worked through together; in the first window there may be fewer
+    Div d_per_win, d_window, d_window0, d_chunks, d_hkv;      // exact division by window * ntile, window, window0, chunks, Hkv
+    int off;                // as in SplitParams
+    float c;                // scale * log2(e)
+};
+constexpr int ROWS_BLOCK_BYTES = SPLIT_KEYS * ROW_BYTES;        // 8 KiB: 32 keys of K or V
+constexpr int rows_stages(int KG) { return 4 / KG; }
+constexpr int ROWS_LDS_BYTES = 8 * ROWS_BLOCK_BYTES + 3 * 4 * 32 * ROWS_WAVES;
+static_assert(2 * ROWS_LDS_BYTES <= LDS_BYTES, "two workgroups fit a CU");
+
+// R row groups of 32 rows, KG key groups; one wavefront for each pair of them.
+template <int KG>
+__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void attn_fwd_kernel_rows(const RowsParams p)
+{
+    constexpr int R = ROWS_WAVES / KG, NS = rows_stages(KG);
+    constexpr int STAGE = KG * ROWS_BLOCK_BYTES;        // one block of each key group
+    constexpr int VB = NS * STAGE, QB = VB;             // K stages, V stages (at first Q)
+    constexpr int STATE = 2 * VB;                       // m, l, lr
+    static_assert(R * 32 * ROW_BYTES <= NS * STAGE && STATE == 8 * ROWS_BLOCK_BYTES, "layout of LDS");
+    constexpr int LPW = 8 / R;                          // requests of 1 KiB per block and wavefront
+    constexpr int QPW = R * 8 / ROWS_WAVES;                 // and of Q
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    LDS_AS unsigned char *lds = (LDS_AS unsigned char *)smem;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, hh = lane >> 5;
+    const int rg = wave % R, kgrp = wave / R;           // row group, key group
+    // blockIdx.x -> (tile, rest): windows of `window` rests, tiles slowest in each, last tile first
+    int in_win = blockIdx.x, rest = 0, tile_r;
+    if (in_win < p.window0 * p.ntile) {
+        tile_r = fast_div(in_win, p.d_window0);
+        rest = in_win - tile_r * p.window0;
+    } else {
+        in_win -= p.window0 * p.ntile;
+        const int win = fast_div(in_win, p.d_per_win);
+        in_win -= win * (p.window * p.ntile);
+        tile_r = fast_div(in_win, p.d_window);
+        rest = p.window0 + win * p.window + in_win - tile_r * p.window;
+    }
+    const int tile = p.ntile - 1 - tile_r;
+    const int bh = fast_div(rest, p.d_chunks), chunk = rest - bh * p.chunks;
+    const int b = fast_div(bh, p.d_hkv), hkv = bh - b * p.Hkv;
+    const int q0 = tile * p.tile_pos;
+    const int row = 32 * rg + l32;                      // this lane's query: its row of the item
+    // blocks of 32 keys: of the item, of this wavefront's rows, and of those the leading ones without masked keys
+    const int klast = min(p.Skv - 1, min(q0 + p.tile_pos - 1, p.Sq - 1) + p.off);
+    const int nb = klast < 0 ? 0 : klast / SPLIT_KEYS + 1;
+    const int pos_lo = q0 + ((32 * rg) >> p.pack_log2), pos_hi = q0 + ((32 * rg + 31) >> p.pack_log2);
+    const int klast_w = min(p.Skv - 1, min(pos_hi, p.Sq - 1) + p.off);
+    const int n_w = klast_w < 0 ? 0 : klast_w / SPLIT_KEYS + 1;
+    const int kfirst_w = min(p.Skv, pos_lo + p.off + 1);
+    const int n_unm = kfirst_w <= 0 ? 0 : kfirst_w / SPLIT_KEYS;
+    const int n = (nb + KG - 1) / KG;                   // turns of the loop
+    const size_t pitch = (size_t)p.Hkv * HD * 2;
+    const unsigned char *kg = uniform_ptr((const unsigned char *)(p.k + ((size_t)b * p.Skv * p.Hkv + hkv) * HD));
+    const unsigned char *vg = uniform_ptr((const unsigned char *)(p.v + ((size_t)b * p.Skv * p.Hkv + hkv) * HD));
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+    const uint32_t lds_wave = lds0 + kgrp * ROWS_BLOCK_BYTES + rg * (LPW * 1024);
+
+    // ---- requests.  A key group's block is fetched by its R wavefronts.
+    uint32_t koff[LPW], voff[LPW];
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+        const int r = 4 * (LPW * rg + i) + (lane >> 4), unit = lane & 15;
+        koff[i] = (uint32_t)(r * pitch) + ((unit ^ (r & 15)) << 4);
+        voff[i] = (uint32_t)(r * pitch) + ((unit ^ ((r & 3) << 2)) << 4);
+    }
+    // Block of turn t into its stage.  (In the last turn a key group may have no block: it reads the item's last one once more.)
+    auto request = [&](int t, bool is_v) __attribute__((always_inline)) {
+        const int blk = min(t * KG + kgrp, nb - 1);
+        const unsigned char *g = uniform_ptr((is_v ? vg : kg) + (size_t)blk * SPLIT_KEYS * pitch);
+        const int last = p.Skv - 1 - blk * SPLIT_KEYS;      // rows past the end of K/V re-read the last row
+        const uint32_t dst = lds_wave + (is_v ? VB : 0) + (t & (NS - 1)) * STAGE;
+        if (last >= SPLIT_KEYS - 1) {
+#pragma unroll
+            for (int i = 0; i < LPW; ++i) lds_dma16(g, is_v ? voff[i] : koff[i], dst + i * 1024);
+        } else {
+            int ln = lane;
+            PIN(ln);
+#pragma unroll
+            for (int i = 0; i < LPW; ++i) {
+                const int r = 4 * (LPW * rg + i) + (ln >> 4);
+                lds_dma16(g, (is_v ? voff[i] : koff[i]) + (uint32_t)((min(r, last) - r) * (int)pitch), dst + i * 1024);
+            }
+        }
+    };
+    {
+        const int row0 = min(q0, p.Sq - 1);
+        const unsigned char *qg = uniform_ptr(
+            (const unsigned char *)(p.q + ((size_t)((size_t)b * p.Sq + row0) * p.Hq + hkv * p.G + chunk * p.pack) * HD));
+#pragma unroll
+        for (int i = 0; i < QPW; ++i) {
+            const int r = (wave * QPW + i) * 4 + (lane >> 4), unit = lane & 15;
+            const int drow = min(q0 + (r >> p.pack_log2), p.Sq - 1) - row0;         // 0 .. 127
+            const uint32_t o = (uint32_t)(drow * p.Hq + (r & (p.pack - 1))) * (uint32_t)(HD * 2) + ((unit ^ (r & 15)) << 4);
+            lds_dma16(qg, o, lds0 + QB + (wave * QPW + i) * 1024);
+        }
+    }
+    if (n > 0) {
+#pragma unroll
+        for (int t = 0; t < NS; ++t)
+            if (t < n) request(t, false);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    f32x16 acc[4], s[2];
+    uint32_t pb[2][8];
+    float m = -INFINITY, l = 0.0f, lr = 0.0f;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
+    int kaddr[8], vaddr[4];
+#pragma unroll
+    for (int st = 0; st < 8; ++st) kaddr[st] = kgrp * ROWS_BLOCK_BYTES + l32 * ROW_BYTES + (((2 * st + hh) ^ (l32 & 15)) << 4);
+    {
+        const int i16 = lane & 15, g = (lane >> 4) & 1;
+        const int r = 4 * hh + (i16 >> 2);
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) {
+            const int d = 32 * dt + 16 * g + 4 * (i16 & 3);
+            vaddr[dt] = VB + kgrp * ROWS_BLOCK_BYTES + r * ROW_BYTES + ((((d >> 3) ^ ((r & 3) << 2))) << 4) + (d & 7) * 2;
+        }
+    }
+    // (opaque from here on, so that the stage and the row stay immediate offsets)
+#pragma unroll
+    for (int st = 0; st < 8; ++st) PIN(kaddr[st]);
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) PIN(vaddr[dt]);
+
+    auto fetch_k = [&](int st, int at) __attribute__((always_inline)) -> bf16x8 {
+        return *(const LDS_AS bf16x8 *)(lds + kaddr[st] + at);
+    };
+    auto fetch_v = [&](int i, int at) __attribute__((always_inline)) -> bf16x8 {        // 16 keys i / 4, d tile i % 4
+        const int ro = at + (i >> 2) * 16 * ROW_BYTES;
+        s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4 *)(lds + vaddr[i & 3] + ro));
+        s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4 *)(lds + vaddr[i & 3] + (ro + 8 * ROW_BYTES)));
+        s16x8 av = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        return __builtin_bit_cast(bf16x8, av);
+    };
+    bf16x8 qf[8];           // Q^T operand: query l32, d = 16 s + 8 hh .. + 7
+    auto qk = [&](f32x16 &x, int at) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) x[r] = 0.0f;
+#pragma unroll
+        for (int st = 0; st < 8; ++st) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fetch_k(st, at), qf[st], x, 0, 0, 0);
+    };
+    auto pv_mfma = [&](bf16x8 av, const uint32_t (&pp)[8], int i) __attribute__((always_inline)) {
+        const int g = i >> 2;
+        u32x4 pw = {pp[4 * g], pp[4 * g + 1], pp[4 * g + 2], pp[4 * g + 3]};
+        acc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, pw), acc[i & 3], 0, 0, 0);
+    };
+    auto pv = [&](const uint32_t (&pp)[8], int at) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) pv_mfma(fetch_v(i, at), pp, i);
+    };
+    const float c = fabsf(p.c);
+    auto key_room = [&](int blk) __attribute__((always_inline)) -> int {       // key 4 hh + k of the block is valid for this lane's row iff k <= room
+        int ln = lane;
+        PIN(ln);
+        return min(p.Skv - 1, q0 + ((32 * rg + (ln & 31)) >> p.pack_log2) + p.off) - blk * SPLIT_KEYS - 4 * (ln >> 5);
+    };
+    // Exact online softmax of a block, masked per key.  (The reference is finite once there is a valid key.)  FIRST: against m as it stands.
+    auto softmax_exact = [&](auto first, const f32x16 &x, uint32_t (&pn)[8], int blk) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first)::value;
+        const int room = key_room(blk);
+        if (!FIRST) {
+            float mx = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, 8 * (r >> 2) + (r & 3) <= room ? fmaxf(x[r] * c, -FLT_MAX) : -INFINITY);
+            const float mn = fmaxf(m, lane32_max(mx));
+            const float alpha = (mn == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - mn);
+            m = mn;
+            l *= alpha;
+            lr *= alpha;
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[dt][r] *= alpha;
+        }
+        const float mu = (m == -INFINITY) ? 0.0f : m;
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+            const int key = 8 * (r >> 2) + (r & 3);
+            float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], c, -mu));
+            float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r + 1], c, -mu));
+            e0 = (key <= room) ? e0 : 0.0f;
+            e1 = (key + 1 <= room) ? e1 : 0.0f;
+            l += e0 + e1;
+            pn[r >> 1] = pack_bf16(e0, e1);
+            lr = add_bf16_pair(pn[r >> 1], lr);
+        }
+    };
+    // Largest scaled score of block blk's valid keys per query, at least -FLT_MAX; minus infinity if none is valid.
+    auto largest = [&](const f32x16 &x, int blk) __attribute__((always_inline)) -> float {
+        const int room = key_room(blk);
+        float mx = -INFINITY;
+        if (blk < n_unm) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, x[r]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, 8 * (r >> 2) + (r & 3) <= room ? x[r] : -INFINITY);
+        }
+        return lane32_max(room >= 0 ? fmaxf(mx * c, -FLT_MAX) : -INFINITY);
+    };
+    // Turn t: O += P(t-1) V(t-1) from stage vat, S(t+1) = K(t+1) Q^T from stage kat, and between the MFMAs P(t) from S(t) against the
+    // running maximum as it stands.  LDS reads run four MFMAs ahead of their consumer, from one turn into the next: before the last four MFMAs,
+    // when all of the turn's operands are in registers, come the turn's barrier (mid), which publishes the next turn's
+    // stages and frees this turn's, and the first reads from stages vat_next and kat_next.
+    constexpr int AHEAD = 4;
+    bf16x8 frag[16 + AHEAD];        // [0, AHEAD): read by the turn before
+    auto fetch = [&](int slot, int vat, int kat) __attribute__((always_inline)) -> bf16x8 {
+        return (slot & 1) ? fetch_k(slot >> 1, kat) : fetch_v(slot >> 1, vat);
+    };
+    auto turn = [&](auto masked_, auto more_, const f32x16 &x, f32x16 &y, const uint32_t (&pp)[8], uint32_t (&pn)[8],
+                    int vat, int kat, int vat_next, int kat_next, int blk, auto mid, auto after) __attribute__((always_inline)) {
+        constexpr bool MASKED = decltype(masked_)::value, MORE = decltype(more_)::value;
+        float ev[16], ls0 = 0.0f, ls1 = 0.0f, r0 = 0.0f, r1 = 0.0f, arg = 0.0f;
+        uint32_t pw[8];
+        const int room = MASKED ? key_room(blk) : 0;
+#pragma unroll
+        for (int slot = 0; slot < 16; ++slot) {
+            if (MORE && slot + AHEAD == 16) {
+                __builtin_amdgcn_s_waitcnt(WAIT_LGKMCNT0);
+                mid();
+            }
+            if (slot + AHEAD < 16 && (MORE || !(slot & 1))) frag[slot + AHEAD] = fetch(slot + AHEAD, vat, kat);
+            else if (MORE) frag[slot + AHEAD] = fetch(slot + AHEAD - 16, vat_next, kat_next);
+            if ((slot & 1) == 0) {
+                pv_mfma(frag[slot], pp, slot >> 1);
+            } else if (MORE) {
+                const int st = slot >> 1;
+                f32x16 z;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) z[r] = 0.0f;
+                y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[slot], qf[st], st == 0 ? z : y, 0, 0, 0);
+            }
+            // probability `slot`; its argument was formed a slot before, its sum and its pair's rounding follow a slot later, so that
+            // no instruction waits for the one in front of it
+            ev[slot] = __builtin_amdgcn_exp2f(slot == 0 ? __builtin_fmaf(x[0], c, -m) : arg);
+            if (MASKED) ev[slot] = 8 * (slot >> 2) + (slot & 3) <= room ? ev[slot] : 0.0f;
+            if (slot < 15) {
+                arg = __builtin_fmaf(x[slot + 1], c, -m);
+                PIN(arg);
+            }
+            if (slot & 1) {
+                ls0 += ev[slot - 1];
+                PIN(ls0);
+            } else if (slot > 0) {
+                ls1 += ev[slot - 1];
+                PIN(ls1);
+                pw[(slot >> 1) - 1] = pack_bf16(ev[slot - 2], ev[slot - 1]);
+                PIN(pw[(slot >> 1) - 1]);
+            }
+            if (MORE && slot + AHEAD >= 16) after(slot + AHEAD - 16);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        ls1 += ev[15];
+        pw[7] = pack_bf16(ev[14], ev[15]);
+        if (MORE) {
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) frag[i] = frag[16 + i];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; k += 2) {
+            r0 = add_bf16_pair(pw[k], r0);
+            r1 = add_bf16_pair(pw[k + 1], r1);
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) pn[k] = pw[k];
+        float ls = ls0 + ls1, lrn = r0 + r1;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(ls <= P_SUM_LIMIT)) != 0, 0)) {
+            softmax_exact(std::false_type{}, x, pn, blk);
+            ls = lrn = 0.0f;        // (it has added them)
+        }
+        l += ls;
+        lr += lrn;
+    };
+
+    // (waits: everything, where the item is too short for the counts of the steady state)
+    if (n >= NS) __builtin_amdgcn_s_waitcnt(wait_vmcnt((NS - 1) * LPW)); else __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
+    wg_barrier();           // Q and K(0) have landed
+#pragma unroll
+    for (int st = 0; st < 8; ++st) qf[st] = *(const LDS_AS bf16x8 *)(lds + QB + row * ROW_BYTES + (((2 * st + hh) ^ (l32 & 15)) << 4));
+    // a negative scale: the negated Q (exact) with the scale's absolute value
+    if (p.c < 0.0f) {
+#pragma unroll
+        for (int st = 0; st < 8; ++st) qf[st] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, qf[st]) ^ 0x80008000u);
+    }
+    if (n > 0) {
+        qk(s[0], 0);
+        if (n >= NS) __builtin_amdgcn_s_waitcnt(wait_vmcnt((NS - 2) * LPW)); else __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
+        wg_barrier();                                           // K(1) has landed, and everyone has read K(0) and Q
+#pragma unroll
+        for (int t = 0; t < NS - 1; ++t)
+            if (t < n) request(t, true);
+        if (NS < n) request(NS, false);
+        // Turn t requests K(t+1+NS) and V(t-1+NS) behind its barrier, into the stages that it has read; at the barrier what the next turn
+        // reads has landed, K(t+2) and V(t), requested NS - 1 turns before.
+        constexpr int IN_FLIGHT = (NS - 2) * 2 * LPW;
+        m = largest(s[0], kgrp);
+        if (n > 1) {
+            // (the reference of the first turns is the largest of two blocks, 64 keys, as in the 256-row kernel: one block alone leaves
+            // larger weights to rounding)
+            qk(s[1], STAGE);
+            m = fmaxf(m, largest(s[1], KG + kgrp));
+        }
+        softmax_exact(std::true_type{}, s[0], pb[0], kgrp);
+        if (n > 1) {
+            if (n > NS) __builtin_amdgcn_s_waitcnt(wait_vmcnt((NS - 1) / 2 * 3 * LPW)); else __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
+            wg_barrier();                                       // K(2), V(0) have landed, and everyone has read K(1)
+            if (1 + NS < n) request(1 + NS, false);
+            if (NS - 1 < n) request(NS - 1, true);
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) frag[i] = fetch(i, 0, 2 % NS * STAGE);
+        }
+        const std::true_type yes = {};
+        const std::false_type no = {};
+        int t = 1;
+        // turns below it see no masked key of this wavefront, and request full blocks
+        const int fast_end = min(n - 1, (min(n_unm, min(nb, p.Skv / SPLIT_KEYS) - (NS + 1) * KG) - kgrp + KG - 1) / KG);
+        const size_t step = (size_t)KG * SPLIT_KEYS * pitch;
+        const unsigned char *kp = uniform_ptr(kg + (size_t)((NS + 2) * KG + kgrp) * SPLIT_KEYS * pitch);
+        const unsigned char *vp = uniform_ptr(vg + (size_t)(NS * KG + kgrp) * SPLIT_KEYS * pitch);
+        auto wait = [&]() __attribute__((always_inline)) {
+            if (t + NS < n) __builtin_amdgcn_s_waitcnt(wait_vmcnt(IN_FLIGHT)); else __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
+            wg_barrier();
+        };
+        auto more_requests = [&]() __attribute__((always_inline)) {
+            if (t + 1 + NS < n) request(t + 1 + NS, false);
+            if (t - 1 + NS < n) request(t - 1 + NS, true);
+        };
+        auto fast = [&](auto phase) __attribute__((always_inline)) {
+            constexpr int T = decltype(phase)::value % NS;      // t % NS
+            constexpr int VA = (T + NS - 1) % NS * STAGE, KA = (T + 1) % NS * STAGE, VN = T * STAGE, KN = (T + 2) % NS * STAGE;
+            turn(no, yes, s[T & 1], s[1 - (T & 1)], pb[1 - (T & 1)], pb[T & 1], VA, KA, VN, KN, t * KG + kgrp,
+                 [&]() __attribute__((always_inline)) {
+                     __builtin_amdgcn_s_waitcnt(wait_vmcnt(IN_FLIGHT));
+                     wg_barrier();
+                 },
+                 [&](int i) __attribute__((always_inline)) {
+                     // (one of four: the first and the second half of K's requests, then of V's)
+                     constexpr int H = LPW / 2;
+                     if (i == 0) lds_dma16_imm<KA>(kp, koff[0], lds_wave);
+                     if (i == 0 && H == 2) lds_dma16_imm<KA + 1024>(kp, koff[1], lds_wave);
+                     if (i == 1) lds_dma16_imm<KA + H * 1024>(kp, koff[H], lds_wave);
+                     if (i == 1 && H == 2) lds_dma16_imm<KA + 3072>(kp, koff[LPW - 1], lds_wave);
+                     if (i == 2) lds_dma16_imm<VB + VA>(vp, voff[0], lds_wave);
+                     if (i == 2 && H == 2) lds_dma16_imm<VB + VA + 1024>(vp, voff[1], lds_wave);
+                     if (i == 3) lds_dma16_imm<VB + VA + H * 1024>(vp, voff[H], lds_wave);
+                     if (i == 3 && H == 2) lds_dma16_imm<VB + VA + 3072>(vp, voff[LPW - 1], lds_wave);
+                 });
+            kp += step;
+            vp += step;
+            ++t;
+        };
+#pragma nounroll
+        for (; t + NS - 1 < fast_end;) {
+            fast(std::integral_constant<int, 1>{});
+            fast(std::integral_constant<int, 2>{});
+            if (NS == 4) {
+                fast(std::integral_constant<int, 3>{});
+                fast(std::integral_constant<int, 4>{});
+            }
+        }
+        // The rest, masked, one after the other: s[1] holds S(t), pb[0] P(t-1).
+#pragma nounroll
+        for (; t < n - 1; ++t) {
+            turn(yes, yes, s[1], s[0], pb[0], pb[0], (t - 1) % NS * STAGE, (t + 1) % NS * STAGE, t % NS * STAGE, (t + 2) % NS * STAGE,
+                 t * KG + kgrp, wait, [](int) {});
+            more_requests();
+            s[1] = s[0];
+        }
+        // the last turn: no further scores
+        if (n > 1 && (n - 2) * KG + kgrp < n_w) {
+#pragma unroll
+            for (int i = 0; i < AHEAD; i += 2) frag[i] = fetch(i, (n - 2) % NS * STAGE, 0);
+            turn(yes, no, s[1], s[0], pb[0], pb[0], (n - 2) % NS * STAGE, 0, 0, 0, (n - 1) * KG + kgrp, []() {}, [](int) {});
+        }
+        __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);        // V(n-1) has landed
+        wg_barrier();
+        if ((n - 1) * KG + kgrp < n_w) pv(pb[0], (n - 1) % NS * STAGE);
+    }
+    __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
+    if (KG > 1) wg_barrier();       // the stages are read
+
+    // ---- merge of the key groups: wavefront (rg, kgrp) finishes d tiles DT kgrp .. DT kgrp + DT - 1 of its rows
+    constexpr int DT = 4 / KG;
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    auto part = [&](int to, int from) __attribute__((always_inline)) {
+        return (LDS_AS f32x4 *)(lds + ((rg * KG + to) * KG + from) * (DT * 4096)) + lane;
+    };
+    LDS_AS float *state = (LDS_AS float *)(lds + STATE) + rg * KG * 96;
+    if (KG > 1) {
+        const float lt = lane32_sum(l), lrt = lane32_sum(lr);
+        if (hh == 0) {
+            state[kgrp * 96 + l32] = m;
+            state[kgrp * 96 + 32 + l32] = lt;
+            state[kgrp * 96 + 64 + l32] = lrt;
+        }
+    }
+    const int head = hkv * p.G + chunk * p.pack + (row & (p.pack - 1));
+    const int qpos = q0 + (row >> p.pack_log2);
+    const bool valid = qpos < p.Sq;
+    float M = -INFINITY, L = 0.0f;
+    auto finish = [&](auto mine) __attribute__((always_inline)) {
+        constexpr int ME = decltype(mine)::value;
+#pragma unroll
+        for (int to = 0; to < KG; ++to) {
+            if (to == ME) continue;
+#pragma unroll
+            for (int i = 0; i < 4 * DT; ++i) {
+                const f32x16 &a = acc[to * DT + (i >> 2)];
+                part(to, ME)[64 * i] = f32x4{a[4 * (i & 3)], a[4 * (i & 3) + 1], a[4 * (i & 3) + 2], a[4 * (i & 3) + 3]};
+            }
+        }
+        float f[KG], LR = 0.0f;
+        if (KG == 1) {
+            f[0] = 1.0f;
+            M = m;
+            L = lane32_sum(l);
+            LR = lane32_sum(lr);
+        } else {
+            __syncthreads();
+#pragma unroll
+            for (int g = 0; g < KG; ++g) {
+                f[g] = state[g * 96 + l32];
+                M = fmaxf(M, f[g]);
+            }
+#pragma unroll
+            for (int g = 0; g < KG; ++g) {
+                f[g] = (f[g] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(f[g] - M);
+                L += f[g] * state[g * 96 + 32 + l32];
+                LR += f[g] * state[g * 96 + 64 + l32];
+            }
+        }
+        const float inv = LR > 0.0f ? 1.0f / LR : 0.0f;
+        unsigned char *op = (unsigned char *)(p.o + ((size_t)((size_t)b * p.Sq + qpos) * p.Hq + head) * HD + 32 * DT * ME + 8 * hh);
+#pragma unroll
+        for (int i = 0; i < 2 * DT; ++i) {      // 16 d: this lane's two pieces of four, then with its partner's one of eight
+            float y[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) y[j] = 0.0f;
+#pragma unroll
+            for (int g = 0; g < KG; ++g) {
+                const f32x16 &a = acc[ME * DT + (i >> 1)];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int e = 8 * (i & 1) + 4 * k;
+                    f32x4 z = {a[e], a[e + 1], a[e + 2], a[e + 3]};
+                    if (g != ME) z = part(ME, g)[64 * (2 * i + k)];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) y[4 * k + j] = KG == 1 ? z[j] : y[4 * k + j] + f[g] * z[j];
+                }
+            }
+            auto u = __builtin_amdgcn_permlane32_swap(pack_bf16(y[0] * inv, y[1] * inv), pack_bf16(y[4] * inv, y[5] * inv), false, false);
+            auto w = __builtin_amdgcn_permlane32_swap(pack_bf16(y[2] * inv, y[3] * inv), pack_bf16(y[6] * inv, y[7] * inv), false, false);
+            const u32x4 ww = {u[0], w[0], u[1], w[1]};
+            if (valid) *(u32x4 *)(op + 32 * i) = ww;
+        }
+    };
+    if (KG == 1 || kgrp == 0) finish(std::integral_constant<int, 0>{});
+    else finish(std::integral_constant<int, KG - 1>{});
+    if (valid && kgrp == 0 && hh == 0)
+        p.lse[((size_t)b * p.Hq + head) * p.Sq + qpos] = L > 0.0f ? (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f : -INFINITY;
+}
+
 }  // namespace
 
 extern "C" {
@@ -2037,18 +2535,18 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
     if (!cus[dev].load(std::memory_order_acquire)) {
         int n = 0;
         if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0 ||
-            hipFuncSetAttribute((const void *)attn_fwd_kernel<true, FORM_POS>,
+            hipFuncSetAttribute((const void *)attn_fwd_kernel<true, false>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess ||
-            hipFuncSetAttribute((const void *)attn_fwd_kernel<true, FORM_NEG>,
+            hipFuncSetAttribute((const void *)attn_fwd_kernel<true, true>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess ||
-            hipFuncSetAttribute((const void *)attn_fwd_kernel<true, FORM_SHARED>,
+            hipFuncSetAttribute((const void *)attn_fwd_kernel<false, false>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess ||
-            hipFuncSetAttribute((const void *)attn_fwd_kernel<false, FORM_POS>,
+            hipFuncSetAttribute((const void *)attn_fwd_kernel<false, true>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess ||
-            hipFuncSetAttribute((const void *)attn_fwd_kernel<false, FORM_NEG>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess ||
-            hipFuncSetAttribute((const void *)attn_fwd_kernel<false, FORM_SHARED>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess ||
+            hipFuncSetAttribute((const void *)attn_fwd_kernel_rows<1>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, ROWS_LDS_BYTES) != hipSuccess ||
+            hipFuncSetAttribute((const void *)attn_fwd_kernel_rows<2>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, ROWS_LDS_BYTES) != hipSuccess ||
             hipFuncSetAttribute((const void *)attn_fwd_split_kernel<true>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, SPLIT_LDS_BYTES) != hipSuccess ||
             hipFuncSetAttribute((const void *)attn_fwd_split_kernel<false>,
@@ -2067,10 +2565,8 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
     p.Hkv = Hkv; p.Skv = Skv;
     p.c = scale * 1.4426950408889634f;
     p.shape = sh; p.sched = r.sched; p.share = r.share;
-    // a negative scale turns the running maximum of the scaled scores into c times the smallest raw score
-    const bool neg = scale < 0.0f;
 
-    SplitParams sp = {};
+        SplitParams sp = {};
     sp.lse = lse;
     sp.Hq = Hq; sp.Hkv = Hkv; sp.Sq = Sq; sp.G = sh.G;
     sp.pack = sh.pack; sp.chunks = sh.chunks;
@@ -2093,10 +2589,26 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
         sp.nrest = r.share.groups;
         sp.units = r.share.units;
     }
+    RowsParams rp = {};
+    if (r.rows.kgroups != 0) {
+        const Rows &rw = r.rows;
+        rp.q = p.q; rp.k = p.k; rp.v = p.v; rp.o = p.o; rp.lse = lse;
+        rp.Hq = Hq; rp.Hkv = Hkv; rp.Sq = Sq; rp.Skv = Skv; rp.G = sh.G;
+        rp.pack = sh.pack; rp.pack_log2 = sh.pack_log2; rp.chunks = sh.chunks;
+        rp.tile_pos = rw.tile_pos; rp.ntile = rw.ntile; rp.nrest = rw.nrest;
+        rp.window = rw.window; rp.window0 = rw.window0;
+        rp.d_per_win = make_div((uint32_t)(rw.window * rw.ntile));
+        rp.d_window = make_div((uint32_t)rw.window);
+        rp.d_window0 = make_div((uint32_t)rw.window0);
+        rp.d_chunks = sh.d_chunks; rp.d_hkv = sh.d_hkv;
+        // (i + INT32_MAX - Sq - 128 is above every key for i >= 0 and within 32 bits for the i < Sq + 128 of a tile)
+        rp.off = causal ? Skv - Sq : INT32_MAX - Sq - 128;
+        rp.c = p.c;
+    }
     // Each launch is judged by its own status: the runtime's record of the thread's last error may hold an earlier
     // call's.  (One that fails is taken out of that record, as its report is the return value.)
-    auto launch = [&](const void *kernel, unsigned wgs, int lds, void *params) -> bool {
-        if (hipLaunchKernel(kernel, dim3(wgs), dim3(NTHREADS), &params, lds, st) == hipSuccess) return true;
+    auto launch = [&](const void *kernel, unsigned wgs, int lds, void *params, int threads = NTHREADS) -> bool {
+        if (hipLaunchKernel(kernel, dim3(wgs), dim3(threads), &params, lds, st) == hipSuccess) return true;
         (void)hipGetLastError();
         return false;
     };
@@ -2110,10 +2622,12 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
             return launch(sp.splits > 1 ? (const void *)attn_fwd_split_kernel<true> : (const void *)attn_fwd_split_kernel<false>,
                           (unsigned)sp.nrest * sp.ntile * sp.splits, SPLIT_LDS_BYTES, &sp);
         if (r.kind == ROUTE_SHARED)
-            return launch(causal ? (const void *)attn_fwd_kernel<true, FORM_SHARED> : (const void *)attn_fwd_kernel<false, FORM_SHARED>,
+            return launch(causal ? (const void *)attn_fwd_kernel<true, true> : (const void *)attn_fwd_kernel<false, true>,
                           r.share.wgs, LDS_BYTES, &p);
-        const void *whole = causal ? (neg ? (const void *)attn_fwd_kernel<true, FORM_NEG> : (const void *)attn_fwd_kernel<true, FORM_POS>)
-                                   : (neg ? (const void *)attn_fwd_kernel<false, FORM_NEG> : (const void *)attn_fwd_kernel<false, FORM_POS>);
+        if (r.rows.kgroups != 0)
+            return launch(r.rows.kgroups == 1 ? (const void *)attn_fwd_kernel_rows<1> : (const void *)attn_fwd_kernel_rows<2>,
+                          (unsigned)rp.nrest * rp.ntile, ROWS_LDS_BYTES, &rp, 64 * ROWS_WAVES);
+        const void *whole = causal ? (const void *)attn_fwd_kernel<true, false> : (const void *)attn_fwd_kernel<false, false>;
         return launch(whole, (unsigned)(r.sched.slots * 8), LDS_BYTES, &p);
     });
 }

@@ -18,6 +18,11 @@
 #ifndef ATTN_SHARE
 #define ATTN_SHARE 1
 #endif
+// ATTN_ROWS: which calls of the 256-row kernel go to the kernel with workgroups of four wavefronts instead: 1 (shipped, unless
+// one of the switches above asks for a certain kernel) those that it makes shorter; 0 none; 2 all, in items of 128 rows; 3 all, in items of 64.
+#ifndef ATTN_ROWS
+#define ATTN_ROWS (ATTN_SMALL_PATH == 1 && ATTN_SHARE == 1)
+#endif
 
 namespace attn {
 namespace {        // (nothing of it is exported by the library)
@@ -110,7 +115,21 @@ constexpr int SHARE_MAX_UNITS = (SHARE_HEADER_BYTES + 2 * SHARE_MAX_WGS * SHARE_
 static_assert((1 + SHARE_MAX_ITEMS * NWAVES) * 4 <= SHARE_HEADER_BYTES, "header holds a counter per item and wavefront");
 static_assert(SHARE_MAX_UNITS <= POOL_UNITS / 3, "several launches fit the pool");
 
-enum RouteKind { ROUTE_WHOLE, ROUTE_SHARED, ROUTE_SPLIT };     // 256-row kernel, its shared form, split-key kernel
+// How the work of the kernel with workgroups of four wavefronts is cut up: items of 128 / kgroups rows, whose keys are shared by
+// `kgroups` groups of wavefronts.
+struct Rows {
+    int kgroups;            // 1 or 2; 0 if the call is not this kernel's
+    int tile_pos;           // query positions per work item = 128 / kgroups / pack
+    int ntile;              // ceil(Sq / tile_pos)
+    int nrest;              // B * Hkv * chunks; items = ntile * nrest
+    // The workgroups run through windows of `window` of these nrest, tiles slowest, last tile first: enough of them that about as many
+    // workgroups as run at a time (64 per XCD) read the same few K/V heads.  (window a multiple of 8: a K/V head's tiles are on one XCD.)
+    // The first window is the one that may hold fewer, so that the launch ends with short tiles.
+    int window, window0;
+};
+constexpr int ROWS_WAVES = 4;
+
+enum RouteKind { ROUTE_WHOLE, ROUTE_SHARED, ROUTE_SPLIT };     // whole items of 256 rows (or of Rows), shared ones, split-key kernel
 struct Route {
     RouteKind kind;
     int Skv;
@@ -118,6 +137,7 @@ struct Route {
     Sched sched;
     Share share;
     Split split;
+    Rows rows;
 };
 
 // Key blocks of 64 of a 256-row item, as the kernel counts them.
@@ -207,6 +227,69 @@ inline int64_t split_ns(int64_t items, int ntile, int64_t blocks, int ncu)
 }
 
 constexpr int64_t LAST_CACHE_BYTES = 256ll << 20;       // of an MI355X
+
+// Whole items of 256 rows against items of 128 and 64 rows in workgroups of half the size: estimates, in us, fitted to 680 calls (4 to
+// 9500 items of 128 rows, 3 to 22000 keys, masked and not; 9 of 10 estimates are within 15 % of what was measured).  Of those calls, five that they
+// send to the smaller workgroups were 2 to 9 % slower there, none by more; all of them together took 0.85 of the time.  Measured (us, 256 rows /
+// 128 / 64): causal: 1 x 1111, 32 heads on 8 29.5 / 21.4 / 17.7; 24 x 200, 16 heads 25.3 / 20.0 / 21.2; 300 x 150, 4 heads 64 / 47 / 50; 1 x
+// 2000, 16 heads 37.9 / 31.3 / 27.1; 11 x 3694, 4 heads 168 / 156 / 177; 8 x 4096, 16 heads 497 / 530 / 658; no mask: 5 x 1200, 4 heads 30.6
+// / 23.3 / 23.0; 2 x 1500, 16 heads 41.7 / 44.0 / 46.5; 42 x 145, 40 heads 77 / 57 / 65.
+struct Lengths {
+    int Sq, Skv;
+    bool causal;
+    // blocks of `unit` keys in all tiles of `pos` positions of one head together
+    double blocks(int pos, int ntile, int unit) const
+    {
+        if (!causal) return (double)ntile * ((Skv + unit - 1) / unit);
+        // tile t ends with the key of position (t + 1) pos, the last one with Skv; with more rows than keys the first ones have none
+        const double off = (double)Skv - Sq;
+        const int first = off < 0 ? (int)(-off / pos) : 0, tiles = ntile - first;
+        const double ends = tiles * ((first + 1.0 + ntile) * pos * 0.5 + off) - (ntile * (double)pos - Sq);
+        return ends / unit + 0.5 * tiles;
+    }
+};
+inline double clamp01(double x) { return x < 0 ? 0 : x > 1 ? 1 : x; }
+// One workgroup of eight wavefronts per compute unit, one item after the other.
+inline double rows256_us(const Route &p, const Lengths &ln, int ncu, double bytes)
+{
+    const Sched &sc = p.sched;
+    const int groups = p.share.groups, per = item_blocks(p, false, 0);
+    // what an item costs beside its blocks, in blocks; an item of fewer than four does not load the next one's tiles
+    const double extra = ln.causal ? SHARE_EXTRA_CAUSAL : per < 4 ? 4.4 : SHARE_EXTRA;
+    const double all = groups * ln.blocks(p.shape.tile_pos, sc.ntile, BN) + extra * sc.total;
+    double longest = all / (8 * sc.slots) * 1.02;       // (many items: none ends much later than the others)
+    if (!ln.causal) longest = (sc.per_xcd + sc.slots - 1) / sc.slots * (per + extra);
+    else if (sc.total <= 4 * ncu) longest = whole_items_length(p, true, SHARE_EXTRA_CAUSAL);
+    const double busy = all / (ncu * longest);
+    const double t = longest * (1.149 + 0.026 * clamp01((busy - 0.5) * 4));
+    const double us = t * (1 + 0.27 * clamp01(t / 80) * busy);        // (a full chip lowers its clock)
+    return 3.5 + (us > bytes * 0.222e-6 ? us : bytes * 0.222e-6);
+}
+// Two workgroups of four wavefronts per compute unit.
+inline double rows_us(const Route &p, const Lengths &ln, int kgroups, int ncu, double bytes, bool cached)
+{
+    struct Fit { double start, extra, alone, pair, tail, clock, byte, cold; };
+    // us: of a launch; turns that an item costs beside its own; of a turn where one or two workgroups are on a compute unit
+    static const Fit fits[2] = {{2.99, 6.85, 0.398, 0.731, 0.276, 0.161, 0.181e-6, 0.15}, {2.51, 3.68, 0.538, 0.874, 0.253, 0.133, 0.204e-6, 0.71}};
+    const Fit &f = fits[kgroups - 1];
+    const int pos = 128 / kgroups / p.shape.pack, ntile = (ln.Sq + pos - 1) / pos;
+    const double items = (double)p.share.groups * ntile;
+    const double most = (ln.Skv + SPLIT_KEYS * kgroups - 1) / (SPLIT_KEYS * kgroups) + f.extra;
+    const double all = p.share.groups * ln.blocks(pos, ntile, SPLIT_KEYS * kgroups) + f.extra * items;
+    // the longest item, beside another one for as long as there are others; without a mask the rounds of equal ones
+    const double others = all / (2 * ncu) / most, beside = items / ncu - 1;
+    double longest = most * (f.alone + (f.pair - f.alone) * clamp01(others < beside ? others : beside));
+    if (!ln.causal) {
+        const int rounds = (int)(items / (2 * ncu));
+        const double rest = items - 2.0 * ncu * rounds;
+        longest = rounds < 3 ? most * (rounds * f.pair + (rest == 0 ? 0 : rest <= ncu ? f.alone : f.pair)) : 0;
+    }
+    if (!cached) longest *= 1 + f.cold;
+    double t = all / (2 * ncu) * f.pair;
+    t = t * (1 + f.clock * clamp01(t / 80)) + f.tail * most * f.alone;
+    const double us = longest > t ? longest : t;
+    return f.start + (us > bytes * f.byte ? us : bytes * f.byte);
+}
 
 // Sizes as attn_fwd() takes them, all positive: what the kernels' index arithmetic holds.  Returns a code of include/attn.h
 // (and, if that is ATTN_OK, the shape).
@@ -321,6 +404,38 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
         sp.splits = splits;
         if (sp.splits > 1)
             sp.units = (int)((SPLIT_HEADER_BYTES + split_items * sp.splits * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
+    }
+
+    // What is left may be faster in smaller workgroups.  (Not what the split-key kernel gets: it rounds its weights against more maxima, and
+    // its results are 10 % closer to the exact ones.)
+    Rows &rw = p.rows;
+    rw.kgroups = 0;
+    if (ATTN_ROWS != 0 && (ATTN_ROWS != 1 || p.kind != ROUTE_SPLIT)) {
+        int kgroups = ATTN_ROWS == 2 ? 1 : ATTN_ROWS == 3 ? 2 : 0;
+        if (ATTN_ROWS == 1) {
+            const Lengths ln = {Sq, Skv, causal != 0};
+            const double kv = (double)B * Hkv * Skv * HD * 4, bytes = kv + (double)B * Hkv * sh.G * Sq * HD * 4;
+            const bool cached = kv <= (double)LAST_CACHE_BYTES;
+            const double r1 = rows_us(p, ln, 1, ncu, bytes, cached), r2 = rows_us(p, ln, 2, ncu, bytes, cached);
+            // (What the estimates are worth.  Shared items: of seven calls of less than 80 us that are put 10 to 15 % ahead, the measured gain was
+            // 12 to 23 %; of seven longer ones between 9 % and, once, a loss of 2 %.)
+            const double shared = shared_ns(p, total) * 1e-3;
+            const double limit = p.kind != ROUTE_SHARED ? rows256_us(p, ln, ncu, bytes) / 1.06 : shared / (shared < 80 ? 1.10 : 1.15);
+            if ((r1 < r2 ? r1 : r2) < limit) kgroups = r1 < r2 ? 1 : 2;
+        }
+        if (kgroups != 0) {
+            const int pos = 128 / kgroups / sh.pack, ntile = (Sq + pos - 1) / pos;
+            if ((int64_t)sr.groups * ntile <= MAX_WGS) {
+                p.kind = ROUTE_WHOLE;
+                rw.kgroups = kgroups;
+                rw.tile_pos = pos;
+                rw.ntile = ntile;
+                rw.nrest = sr.groups;
+                rw.window = (2 * cu_slots + ntile - 1) / ntile * 8;
+                if (rw.window > rw.nrest) rw.window = rw.nrest;
+                rw.window0 = rw.nrest - (rw.nrest - 1) / rw.window * rw.window;
+            }
+        }
     }
 }
 
