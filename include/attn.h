@@ -11,7 +11,7 @@
  * nothing, never synchronises and never throws; its code object brings 256 MiB
  * of device memory for partial results (once per device that the library is used
  * on, whether or not a call needs it), which launches share out among
- * themselves on the device.
+ * themselves on the device, and 84 MiB more for the launches of the device's null stream.
  */
 #ifndef PAPER_2603_24517_ATTN_H
 #define PAPER_2603_24517_ATTN_H
@@ -68,8 +68,8 @@ enum {
  * with one workgroup of four wavefronts per 128 or 64 query rows.
  * Where the 32-row items are fewer than the compute units and the key sequence is long, or
  * where whole 256-row items would leave compute units without work for long,
- * several workgroups share an item's keys; the launch is then preceded by one of a
- * single workgroup, which takes the device memory that the partial results pass
+ * several workgroups share an item's keys; the launch is then preceded, on other streams than
+ * the null stream, by one of a single workgroup, which takes the device memory that the partial results pass
  * through.  Any number of threads and streams may do so at a time: a launch
  * that finds the memory in use goes without it, which is slower and gives the
  * same result bit for bit.  Nothing is allocated in any case.

@@ -180,6 +180,7 @@ struct Params {
     Shape shape;
     Sched sched;
     Share share;
+    uint32_t unit;  // SHARED: REGION_SHARE_UNIT if the launch has the region, or POOL_NONE
 };
 
 __device__ __forceinline__ float lane32_max(float x) {
@@ -284,19 +285,25 @@ __device__ __forceinline__ unsigned long long phase_now() {
 // replayed from graphs thus never share units.  If no run is free (the pool serves at least POOL_UNITS / SHARE_MAX_UNITS
 // launches at a time), the first workgroup of each item takes all of its parts and the others leave, which is slower but
 // needs no memory and gives the same bits.
+//
+// The launch in front takes 4.8 us, with the gap behind it.  A device's null stream, whose launches never overlap, which cannot be captured
+// into a graph and whose handle never stands for another, has memory of its own instead and no such launch: it is told the unit by the
+// host and reads no mark.  The region's counters are zero when a launch starts, because whoever takes a counter to its last value sets it
+// back.  (us, K and V from HBM: 1 x 1 x 32768, 32 heads on 8 38.7, with the region 35.9; 16 x 1 x 4000, 32 on 8 51.8 and 48.4; 1 x 512 x 16384, 32 on 8
+// 131.0 and 128.9.)
 constexpr uint32_t POOL_NONE = 0xffu;
 // How the number (or POOL_NONE) stands in an LSE element: as a NaN whose low half is no result's.  (A NaN of a
 // result has the default payload or one that came in with a BF16 value, whose low 16 bits are zero.)  Where no run was
 // free, a late workgroup may find the item's result there instead, already stored by the first one, and has to
 // take anything but the mark for "none".
 constexpr uint32_t POOL_MARK = 0xffe5a500u;
-static_assert(POOL_UNITS <= POOL_NONE, "a unit's number fits the low byte of the mark");
+static_assert(POOL_UNITS + REGION_UNITS <= POOL_NONE, "no unit has the number for none, which fits the low byte of the mark");
 __host__ __device__ inline uint32_t pool_mark(uint32_t unit) { return POOL_MARK | unit; }
 __host__ __device__ inline uint32_t pool_unmark(uint32_t word) {
     return (word ^ POOL_MARK) < POOL_UNITS ? (word ^ POOL_MARK) : POOL_NONE;
 }
 __device__ unsigned long long g_pool_taken;         // bit u: unit u belongs to a launch in flight
-__device__ __attribute__((aligned(4096))) unsigned char g_pool[POOL_UNITS * POOL_UNIT_BYTES];
+__device__ __attribute__((aligned(4096))) unsigned char g_pool[(size_t)(POOL_UNITS + REGION_UNITS) * POOL_UNIT_BYTES];
 // The one lane that takes a run of n units: first free run, or POOL_NONE.
 __device__ inline uint32_t pool_take(int n)
 {
@@ -349,10 +356,12 @@ __device__ inline u32x4 pool_load16(__amdgpu_buffer_rsrc_t rs, uint32_t lane_at,
 {
     return __builtin_amdgcn_raw_buffer_load_b128(rs, lane_at, at, POOL_SC1);
 }
+__device__ inline void pool_clear(uint32_t *counter) { __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline void pool_store(float *at, float a) { __hip_atomic_store(at, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline float pool_load(const float *at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline void pool_give(uint32_t u, int n)
 {
+    if (u >= POOL_UNITS) return;        // the region
     __hip_atomic_fetch_and(&g_pool_taken, ~(((1ull << n) - 1) << u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -1080,6 +1089,7 @@ void attn_fwd_kernel(const Params p)
                 seen = __builtin_amdgcn_readfirstlane(__hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             }
             asm volatile("" ::: "memory");
+            if (ln == 0) pool_clear(arrived);
             const uint32_t in = slot_of(1 - mine);
             const u32x4 st = pool_load16(rs, lane_at, in + 16 * 1024);
             u32x4 x[16];
@@ -1106,6 +1116,7 @@ void attn_fwd_kernel(const Params p)
         leave();
         if (count(1) != (uint32_t)parts - 1) return false;
         asm volatile("" ::: "memory");
+        if (ln == 0) pool_clear(arrived);
         // Part after part in halves of 32 accumulator elements, the next half always in flight.
         reset_state();
         u32x4 st, xa[8], xb[8];
@@ -1195,10 +1206,13 @@ void attn_fwd_kernel(const Params p)
             const Shape sh = load_shape();
             const int bh = fast_div(grp, sh.d_chunks), b = fast_div(bh, sh.d_hkv);
             const int head = (bh - b * p.Hkv) * sh.G + (grp - bh * sh.chunks) * sh.pack;
-            unit = ((const __attribute__((address_space(4))) uint32_t *)(uintptr_t)cold().lse)
-                [((size_t)b * sh.Hq + head) * sh.Sq + tile * sh.tile_pos];
-            asm volatile("" : "+s"(unit));      // read once, here
-            unit = pool_unmark(unit);
+            unit = cold().unit;
+            if (unit == POOL_NONE) {
+                unit = ((const __attribute__((address_space(4))) uint32_t *)(uintptr_t)cold().lse)
+                    [((size_t)b * sh.Hq + head) * sh.Sq + tile * sh.tile_pos];
+                asm volatile("" : "+s"(unit));      // read once, here
+                unit = pool_unmark(unit);
+            }
             pooled = unit != POOL_NONE;
             if (!pooled) {
                 grp = grp0; tile = tile0; at = at0;
@@ -1509,7 +1523,10 @@ void attn_fwd_kernel(const Params p)
             const Share sr = load_share();
             uint32_t *left = (uint32_t *)(g_pool + (size_t)unit * POOL_UNIT_BYTES);
             const uint32_t n = __hip_atomic_fetch_add(left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (n == (uint32_t)sr.wgs - 1) pool_give(unit, sr.units);
+            if (n == (uint32_t)sr.wgs - 1) {
+                pool_clear(left);
+                pool_give(unit, sr.units);
+            }
         }
     }
 #ifdef ATTN_CLOCKS
@@ -1550,6 +1567,7 @@ struct SplitParams {
     int splits;             // workgroups that share an item
     Div d_splits;
     int units;              // POOL_UNIT_BYTES units of device memory the launch needs, 0 if splits == 1
+    uint32_t unit;          // REGION_SPLIT_UNIT if the launch has the region, or POOL_NONE
     int reserve;            // > 0: this launch is one workgroup that takes the units for the launch behind it, and clears
                             // this many counters per item (the item geometry is that launch's); < 0: one that gives them
                             // back, because there was no launch behind it
@@ -1634,9 +1652,12 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
     uint32_t unit = POOL_NONE;
     if (SHARED) {
         // (read as a constant: where units were taken, nothing writes it until every workgroup of the item has read it)
-        unit = ((const __attribute__((address_space(4))) uint32_t *)(uintptr_t)p.lse)[item_lse(rest, q0)];
-        asm volatile("" : "+s"(unit));      // read once, here
-        unit = pool_unmark(unit);
+        unit = p.unit;
+        if (unit == POOL_NONE) {
+            unit = ((const __attribute__((address_space(4))) uint32_t *)(uintptr_t)p.lse)[item_lse(rest, q0)];
+            asm volatile("" : "+s"(unit));      // read once, here
+            unit = pool_unmark(unit);
+        }
         if (unit == POOL_NONE && part != 0) return;
         take_part(part);
     }
@@ -1984,8 +2005,11 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
             }
             __syncthreads();                // everything of this item is read
             if (tid == 0) {
-                const uint32_t done = __hip_atomic_fetch_add(&header[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (done == (uint32_t)(p.nrest * p.ntile) - 1) pool_give(unit, p.units);
+                pool_clear(&header[1 + item]);
+                if (unit < POOL_UNITS) {        // (the region is not given back)
+                    const uint32_t done = __hip_atomic_fetch_add(&header[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (done == (uint32_t)(p.nrest * p.ntile) - 1) pool_give(unit, p.units);
+                }
             }
         } else if (!SHARED) {
             M = mp; L = lp; LR = rp;
@@ -2566,8 +2590,12 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
     p.c = scale * 1.4426950408889634f;
     p.shape = sh; p.sched = r.sched; p.share = r.share;
 
-        SplitParams sp = {};
+        const bool region = ATTN_POOL && shares_items(r) && st == nullptr;
+    p.unit = region ? REGION_SHARE_UNIT : POOL_NONE;
+
+    SplitParams sp = {};
     sp.lse = lse;
+    sp.unit = region ? REGION_SPLIT_UNIT : POOL_NONE;
     sp.Hq = Hq; sp.Hkv = Hkv; sp.Sq = Sq; sp.G = sh.G;
     sp.pack = sh.pack; sp.chunks = sh.chunks;
     sp.d_chunks = sh.d_chunks;
@@ -2629,7 +2657,7 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
                           (unsigned)rp.nrest * rp.ntile, ROWS_LDS_BYTES, &rp, 64 * ROWS_WAVES);
         const void *whole = causal ? (const void *)attn_fwd_kernel<true, false> : (const void *)attn_fwd_kernel<false, false>;
         return launch(whole, (unsigned)(r.sched.slots * 8), LDS_BYTES, &p);
-    });
+    }, region);
 }
 
 const char *attn_strerror(int code)

@@ -114,6 +114,11 @@ constexpr int SHARE_MAX_WGS = 256;                  // two slots each at most: o
 constexpr int SHARE_MAX_UNITS = (SHARE_HEADER_BYTES + 2 * SHARE_MAX_WGS * SHARE_SLOT_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES;
 static_assert((1 + SHARE_MAX_ITEMS * NWAVES) * 4 <= SHARE_HEADER_BYTES, "header holds a counter per item and wavefront");
 static_assert(SHARE_MAX_UNITS <= POOL_UNITS / 3, "several launches fit the pool");
+// Behind the pool: the region of the device's null stream.  Its launches follow one another, whoever makes them, so that each finds the region
+// free, and its counters zero, as every launch leaves them.  Each kernel has a part of it to itself, because where one has counters the other has
+// results.
+constexpr int REGION_UNITS = SHARE_MAX_UNITS + SPLIT_MAX_UNITS;
+constexpr uint32_t REGION_SHARE_UNIT = POOL_UNITS, REGION_SPLIT_UNIT = POOL_UNITS + SHARE_MAX_UNITS;       // first units
 
 // How the work of the kernel with workgroups of four wavefronts is cut up: items of 128 / kgroups rows, whose keys are shared by
 // `kgroups` groups of wavefronts.
@@ -439,14 +444,15 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
     }
 }
 
-// The launches of a call: where items are shared, one that takes the device memory for the parts stands in front of the one
-// that uses it and gives it back, and if that fails, another one gives the memory back (or, if none can be launched any more,
+// The launches of a call: where items are shared and the stream has no region, one that takes the device memory for the parts stands in
+// front of the one that uses it and gives it back, and if that fails, another one gives the memory back (or, if none can be launched any more,
 // nothing does).  `go` enqueues a step and says whether the runtime took it.  Returns a code of include/attn.h.
+inline bool shares_items(const Route &p) { return p.kind == ROUTE_SHARED || (p.kind == ROUTE_SPLIT && p.split.splits > 1); }
 enum Step { STEP_TAKE, STEP_MAIN, STEP_GIVE };
 template <class Go>
-int enqueue(const Route &p, Go &&go)
+int enqueue(const Route &p, Go &&go, bool region = false)
 {
-    const bool takes = p.kind == ROUTE_SHARED || (p.kind == ROUTE_SPLIT && p.split.splits > 1);
+    const bool takes = shares_items(p) && !region;
     if (takes && !go(STEP_TAKE)) return ATTN_E_LAUNCH;
     if (go(STEP_MAIN)) return ATTN_OK;
     if (takes) (void)go(STEP_GIVE);
