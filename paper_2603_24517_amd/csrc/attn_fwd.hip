@@ -230,6 +230,14 @@ __device__ __forceinline__ void lds_dma16(const unsigned char *base, uint32_t vo
                  : "s"(lds_base), "v"(voffset), "s"(base)
                  : "memory", "m0");
 }
+// The same for data that is read once: it passes the caches by (nt).
+__device__ __forceinline__ void lds_dma16_once(const unsigned char *base, uint32_t voffset, uint32_t lds_base) {
+    base = uniform_ptr(base);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                 :
+                 : "s"(lds_base), "v"(voffset), "s"(base)
+                 : "memory", "m0");
+}
 // The same with the LDS address given as a scalar plus a compile-time constant (one scalar instruction).
 template <int IMM>
 __device__ __forceinline__ void lds_dma16_imm(const unsigned char *base, uint32_t voffset, uint32_t lds_base) {
@@ -1563,6 +1571,7 @@ struct SplitParams {
     Div d_nrs, d_chunks, d_hkv;     // exact division by nrest * splits, chunks, Hkv
     int off;                // key j valid iff j <= i + off: Skv - Sq, or without a mask a number that makes all of them valid
     float c;                // scale * log2(e)
+    int once;               // K and V are read once and past the caches
     // (up to here, within two cache lines, what items of one workgroup need; for the shared form:)
     int splits;             // workgroups that share an item
     Div d_splits;
@@ -1680,7 +1689,10 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
         const unsigned char *g = uniform_ptr((is_v ? vg : kg) + (size_t)blk * SPLIT_KEYS * kv_row_bytes);
         const int last = p.Skv - 1 - blk * SPLIT_KEYS;      // rows past the end of K/V re-read the last row
         const uint32_t dst = lds0 + (is_v ? vbase : kbase);
-        if (last >= SPLIT_KEYS - 1) {
+        if (last >= SPLIT_KEYS - 1 && p.once) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) lds_dma16_once(g, is_v ? voff[i] : koff[i], dst + i * 1024);
+        } else if (last >= SPLIT_KEYS - 1) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) lds_dma16(g, is_v ? voff[i] : koff[i], dst + i * 1024);
         } else {
@@ -2611,6 +2623,7 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
         // (i + INT32_MAX - Sq - 64 is above every key for i >= 0 and within 32 bits for the i < Sq + 32 of a tile)
         sp.off = causal ? Skv - Sq : INT32_MAX - Sq - 64;
         sp.c = p.c;
+        sp.once = r.split.once;
     } else {
         sp.tile_pos = sh.tile_pos;
         sp.ntile = r.sched.ntile;

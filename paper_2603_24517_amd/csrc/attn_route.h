@@ -93,6 +93,7 @@ struct Split {
     int nrest;              // B * Hkv * chunks; items = ntile * nrest
     int splits;             // workgroups that share an item
     int units;              // POOL_UNIT_BYTES units of device memory, 0 if splits == 1
+    bool once;              // K and V are each read by one work item and come from memory
 };
 
 // Device memory for partial results (g_pool of the kernels): sizes of its units, and of what a launch keeps there.
@@ -407,6 +408,12 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
         sp.ntile = split_ntile;
         sp.nrest = sr.groups;
         sp.splits = splits;
+        // Loads past the caches (nt) get 7.0 TB/s from HBM on this card, ordinary ones 6.1 (a kernel that only reads); but then the next call does
+        // not find K and V in the last cache, and several items of a K/V head not in an L2: 2 x 16 x 8192, 64 heads on 8, four items 26.0 us
+        // and 34.3.  Read once, us, from memory, ordinary / past the caches: 16 x 1 x 4000, 32 heads on 8 (262 MB) 52.1 / 48.4; 1 x 1 x 32768 (134 MB) 38.9 /
+        // 37.2; 4 x 1 x 4096 (67 MB) 23.0 / 21.3; 1 x 1 x 8192 (34 MB, six calls' K and V in turn fit the cache) 18.2 / 21.3.  So from a quarter of the
+        // last cache on, where four calls' would fill it.
+        sp.once = split_ntile == 1 && sh.chunks == 1 && (int64_t)B * Hkv * Skv * HD * 4 >= LAST_CACHE_BYTES / 4;
         if (sp.splits > 1)
             sp.units = (int)((SPLIT_HEADER_BYTES + split_items * sp.splits * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
     }
