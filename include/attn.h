@@ -11,7 +11,7 @@
  * nothing, never synchronises and never throws; its code object brings 256 MiB
  * of device memory for partial results (once per device that the library is used
  * on, whether or not a call needs it), which launches share out among
- * themselves on the device, and 84 MiB more for the launches of the device's null stream.
+ * themselves on the device, and 108 MiB more for the launches of the device's null stream.
  */
 #ifndef PAPER_2603_24517_ATTN_H
 #define PAPER_2603_24517_ATTN_H

@@ -99,8 +99,8 @@ struct Split {
 // Device memory for partial results (g_pool of the kernels): sizes of its units, and of what a launch keeps there.
 constexpr int POOL_UNITS = 64;
 constexpr uint32_t POOL_UNIT_BYTES = 4u << 20;
-constexpr int SPLIT_MAX_ITEMS = 256;                // of a launch with splits > 1
-constexpr int SPLIT_MAX_WGS = 512;                  // items * splits of such a launch
+constexpr int SPLIT_MAX_ITEMS = 1023;               // of a launch with splits > 1
+constexpr int SPLIT_MAX_WGS = 2048;                 // items * splits of such a launch
 constexpr int SPLIT_PART_BYTES = 32 * HD * 4 + 3 * 32 * 4;          // one partial result: accumulator, m, l, lr
 constexpr uint32_t SPLIT_HEADER_BYTES = 4096;       // at the start of a run: [0] finished items, [1 + item] workgroups that arrived
 constexpr int SPLIT_MAX_UNITS = (SPLIT_HEADER_BYTES + SPLIT_MAX_WGS * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES;
@@ -194,10 +194,29 @@ inline int whole_items_length(const Route &p, bool causal, int extra)
 inline int split_parts(int64_t items, int ntile, int blocks, int ncu)
 {
     const bool many = items * 3 > ncu;          // at most two parts
-    if (items > SPLIT_MAX_ITEMS || blocks < (ntile > 2 ? (many ? 82 : 66) : (many ? 54 : 40))) return 1;
+    if (items > ncu || blocks < (ntile > 2 ? (many ? 82 : 66) : (many ? 54 : 40))) return 1;
     int s = 1;
-    while ((s + 1) * items <= (ncu < SPLIT_MAX_WGS ? ncu : SPLIT_MAX_WGS) && 5 * (s + 1) * (s + 1) <= 2 * blocks) ++s;
+    while ((s + 1) * items <= (ncu < 512 ? ncu : 512) && 5 * (s + 1) * (s + 1) <= 2 * blocks) ++s;
     return s;
+}
+
+// The same for more items than half of the compute units, which are too many for one round of parts, where K and V come from memory: several
+// rounds of shorter workgroups, where whole items leave part of a round empty.  A full round reads 6.64 TB/s, a compute unit by itself
+// at most 1.47 times its share of that, a workgroup costs about six blocks beside its own, and the merge at the end three.  (One row, whole items /
+// in parts, us: 16384 keys, 144 items 220.2 / 203.5; 264 487.1 / 358.3; 272 492.7 / 370.0; 384 535.3 / 486.0; 2000 keys, 264 items 64.5 / 60.8; 4000 keys, 136 items
+// 55.7 / 51.9; but 1000 keys, 320 items 36.3 / 39.7.)
+inline int split_rounds(int64_t items, int blocks, int ncu)
+{
+    auto cost = [&](int s) {
+        const int64_t wgs = items * s, rest = wgs % ncu;
+        const double last = rest == 0 ? 0 : (double)rest / ncu > 0.68 ? (double)rest / ncu : 0.68;
+        return ((blocks + s - 1) / s + 6) * ((double)(wgs / ncu) + last) + (s > 1 ? 3 : 0);
+    };
+    int best = 1;
+    if (items * 2 <= ncu || items > SPLIT_MAX_ITEMS) return best;
+    for (int s = 2; s <= 16 && items * s <= SPLIT_MAX_WGS && blocks >= 16 * s; ++s)
+        if (cost(s) < (best == 1 ? 0.95 : 1.0) * cost(best)) best = s;
+    return best;
 }
 
 // Estimates, in ns, of the three ways to run a launch; they only choose among them.  Measured (us, whole items or split-key
@@ -400,7 +419,15 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
                                                         (total > ncu && total * 2 <= 3 * ncu && Skv <= 768)));
     const bool small = ATTN_SMALL_PATH == 2 || (ATTN_SMALL_PATH == 1 && ((total * 4 <= ncu && !share) || few_rows));
     p.kind = share ? ROUTE_SHARED : ROUTE_WHOLE;
-    const int splits = split_parts(split_items, split_ntile, (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS, ncu);
+    // Loads past the caches (nt) get 7.0 TB/s from HBM on this card, ordinary ones 6.1 (a kernel that only reads); but then the next call does
+    // not find K and V in the last cache, and several items of a K/V head not in an L2: 2 x 16 x 8192, 64 heads on 8, four items 26.0 us
+    // and 34.3.  Read once, us, from memory, ordinary / past the caches: 16 x 1 x 4000, 32 heads on 8 (262 MB) 52.1 / 48.4; 1 x 1 x 32768 (134 MB) 38.9 /
+    // 37.2; 4 x 1 x 4096 (67 MB) 23.0 / 21.3; 1 x 1 x 8192 (34 MB, six calls' K and V in turn fit the cache) 18.2 / 21.3.  So from a quarter of the
+    // last cache on, where four calls' would fill it.
+    const bool once = split_ntile == 1 && sh.chunks == 1 && (int64_t)B * Hkv * Skv * HD * 4 >= LAST_CACHE_BYTES / 4;
+    const int split_blocks = (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS;
+    int splits = split_parts(split_items, split_ntile, split_blocks, ncu);
+    if (splits == 1 && once) splits = split_rounds(split_items, split_blocks, ncu);
     if (small && split_items * splits <= MAX_WGS) {
         Split &sp = p.split;
         p.kind = ROUTE_SPLIT;
@@ -408,12 +435,7 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
         sp.ntile = split_ntile;
         sp.nrest = sr.groups;
         sp.splits = splits;
-        // Loads past the caches (nt) get 7.0 TB/s from HBM on this card, ordinary ones 6.1 (a kernel that only reads); but then the next call does
-        // not find K and V in the last cache, and several items of a K/V head not in an L2: 2 x 16 x 8192, 64 heads on 8, four items 26.0 us
-        // and 34.3.  Read once, us, from memory, ordinary / past the caches: 16 x 1 x 4000, 32 heads on 8 (262 MB) 52.1 / 48.4; 1 x 1 x 32768 (134 MB) 38.9 /
-        // 37.2; 4 x 1 x 4096 (67 MB) 23.0 / 21.3; 1 x 1 x 8192 (34 MB, six calls' K and V in turn fit the cache) 18.2 / 21.3.  So from a quarter of the
-        // last cache on, where four calls' would fill it.
-        sp.once = split_ntile == 1 && sh.chunks == 1 && (int64_t)B * Hkv * Skv * HD * 4 >= LAST_CACHE_BYTES / 4;
+        sp.once = once;
         if (sp.splits > 1)
             sp.units = (int)((SPLIT_HEADER_BYTES + split_items * sp.splits * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
     }

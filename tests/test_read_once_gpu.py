@@ -1,0 +1,31 @@
+"""Few rows against keys and values that are read once, past the caches, in rounds of parts where whole items would leave a round partly empty:
+the oracle's rows, and the bits of the path without device memory."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_24517_amd as A
+import gpu_util as U
+import test_shared_bits_gpu as T
+
+pytestmark = pytest.mark.gpu
+SCALE = 1.0 / math.sqrt(128)
+
+
+@pytest.mark.parametrize("shape", [(17, 16, 16, 1, 2000), (33, 32, 8, 2, 2111), (9, 16, 16, 7, 8200), (150, 6, 2, 3, 1001)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_rounds_of_parts(shape):
+    print(f"shape {shape}", flush=True)
+    B, Hq, Hkv, Sq, Skv = shape
+    x = U.rand_qkv(*shape, seed=9970 + B)
+    rng = np.random.default_rng(B)
+    rows = np.stack([rng.integers(0, n, 64) for n in (B, Hq, Sq)], axis=1)
+    rows[0], rows[1] = (0, 0, 0), (B - 1, Hq - 1, Sq - 1)
+    for causal in (False, True):
+        U.check_rows(*x, rows, causal, SCALE, what=f"{shape} causal={causal}")
+    dev = tuple(t.cuda() for t in x)
+    ref = T._run(dev, True, "no_pool")
+    for rep in range(3):
+        assert T._same(T._run(dev, True), ref), rep
