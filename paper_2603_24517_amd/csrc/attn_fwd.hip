@@ -300,12 +300,13 @@ __device__ __forceinline__ unsigned long long phase_now() {
 // back.  (us, K and V from HBM: 1 x 1 x 32768, 32 heads on 8 38.7, with the region 35.9; 16 x 1 x 4000, 32 on 8 51.8 and 48.4; 1 x 512 x 16384, 32 on 8
 // 131.0 and 128.9.)
 constexpr uint32_t POOL_NONE = 0xffu;
+constexpr uint32_t POOL_SOLO = 0xfeu;       // split-key kernel: items of one workgroup each in the form for shared ones
 // How the number (or POOL_NONE) stands in an LSE element: as a NaN whose low half is no result's.  (A NaN of a
 // result has the default payload or one that came in with a BF16 value, whose low 16 bits are zero.)  Where no run was
 // free, a late workgroup may find the item's result there instead, already stored by the first one, and has to
 // take anything but the mark for "none".
 constexpr uint32_t POOL_MARK = 0xffe5a500u;
-static_assert(POOL_UNITS + REGION_UNITS <= POOL_NONE, "no unit has the number for none, which fits the low byte of the mark");
+static_assert(POOL_UNITS + REGION_UNITS <= POOL_SOLO, "no unit has the number for none, which fits the low byte of the mark");
 __host__ __device__ inline uint32_t pool_mark(uint32_t unit) { return POOL_MARK | unit; }
 __host__ __device__ inline uint32_t pool_unmark(uint32_t word) {
     return (word ^ POOL_MARK) < POOL_UNITS ? (word ^ POOL_MARK) : POOL_NONE;
@@ -1571,12 +1572,12 @@ struct SplitParams {
     Div d_nrs, d_chunks, d_hkv;     // exact division by nrest * splits, chunks, Hkv
     int off;                // key j valid iff j <= i + off: Skv - Sq, or without a mask a number that makes all of them valid
     float c;                // scale * log2(e)
-    int once;               // K and V are read once and past the caches
     // (up to here, within two cache lines, what items of one workgroup need; for the shared form:)
     int splits;             // workgroups that share an item
+    int once;               // K and V are read once and past the caches
     Div d_splits;
     int units;              // POOL_UNIT_BYTES units of device memory the launch needs, 0 if splits == 1
-    uint32_t unit;          // REGION_SPLIT_UNIT if the launch has the region, or POOL_NONE
+    uint32_t unit;          // REGION_SPLIT_UNIT if the launch has the region, POOL_SOLO if splits == 1, or POOL_NONE
     int reserve;            // > 0: this launch is one workgroup that takes the units for the launch behind it, and clears
                             // this many counters per item (the item geometry is that launch's); < 0: one that gives them
                             // back, because there was no launch behind it
@@ -1591,7 +1592,8 @@ static_assert(SPLIT_Q_BASE % 1024 == 0 && NWAVES * 4 == 32, "each wavefront requ
 static_assert(SPLIT_WAVE_BYTES == 32 * HD * 4, "a wavefront's partial accumulator takes the place of its two blocks");
 static_assert(SPLIT_LDS_BYTES <= LDS_BYTES, "a workgroup fits a CU");
 
-// Two forms: items of one workgroup each, and SHARED ones (with the launch in front of them).  The mask is a number, not a
+// Two forms: items of one workgroup each, and SHARED ones (with the launch in front of them), which also takes the calls whose K and V are
+// read past the caches: 1.3 KB more code, which cost small launches 0.2 us of 12.5 in the other form.  The mask is a number, not a
 // form: every block goes through the masked softmax anyway.  (One kernel for both, with the code of the shared items beside
 // the rest: 64 items of 512 keys 8.0 us instead of 7.7, 60 of 45 keys 5.7 instead of 5.45.)
 template <bool SHARED>
@@ -1689,7 +1691,7 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
         const unsigned char *g = uniform_ptr((is_v ? vg : kg) + (size_t)blk * SPLIT_KEYS * kv_row_bytes);
         const int last = p.Skv - 1 - blk * SPLIT_KEYS;      // rows past the end of K/V re-read the last row
         const uint32_t dst = lds0 + (is_v ? vbase : kbase);
-        if (last >= SPLIT_KEYS - 1 && p.once) {
+        if (SHARED && last >= SPLIT_KEYS - 1 && p.once) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) lds_dma16_once(g, is_v ? voff[i] : koff[i], dst + i * 1024);
         } else if (last >= SPLIT_KEYS - 1) {
@@ -1962,7 +1964,7 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
         reset_state();
     }
     {
-        if (SHARED && unit != POOL_NONE) {
+        if (SHARED && unit < POOL_SOLO) {
             // Leave this part's result; every thread of the merging workgroup reads what the same thread of
             // the others wrote, so the accumulators lie in thread order.
             unsigned char *run = g_pool + (size_t)unit * POOL_UNIT_BYTES;
@@ -2023,7 +2025,7 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
                     if (done == (uint32_t)(p.nrest * p.ntile) - 1) pool_give(unit, p.units);
                 }
             }
-        } else if (!SHARED) {
+        } else if (!SHARED || unit == POOL_SOLO) {
             M = mp; L = lp; LR = rp;
             // (pinned in front of the branch on qpos: moved behind it, the compiler no longer keeps all LDS reads of the merge in
             // flight, 0.2 .. 0.4 us of 8)
@@ -2607,7 +2609,7 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
 
     SplitParams sp = {};
     sp.lse = lse;
-    sp.unit = region ? REGION_SPLIT_UNIT : POOL_NONE;
+    sp.unit = region ? REGION_SPLIT_UNIT : shares_items(r) ? POOL_NONE : POOL_SOLO;
     sp.Hq = Hq; sp.Hkv = Hkv; sp.Sq = Sq; sp.G = sh.G;
     sp.pack = sh.pack; sp.chunks = sh.chunks;
     sp.d_chunks = sh.d_chunks;
@@ -2660,7 +2662,7 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
         }
         sp.reserve = 0;
         if (r.kind == ROUTE_SPLIT)
-            return launch(sp.splits > 1 ? (const void *)attn_fwd_split_kernel<true> : (const void *)attn_fwd_split_kernel<false>,
+            return launch(sp.splits > 1 || sp.once ? (const void *)attn_fwd_split_kernel<true> : (const void *)attn_fwd_split_kernel<false>,
                           (unsigned)sp.nrest * sp.ntile * sp.splits, SPLIT_LDS_BYTES, &sp);
         if (r.kind == ROUTE_SHARED)
             return launch(causal ? (const void *)attn_fwd_kernel<true, true> : (const void *)attn_fwd_kernel<false, true>,
