@@ -1,7 +1,7 @@
 """MI355X-native fused attention forward: thin Python binding over the C ABI of include/attn.h.
 
-Argument marshalling only: every step of the computation runs in the HIP
-kernels of csrc/attn_fwd.hip.  There is no CPU or PyTorch fallback; if the
+Argument marshalling only (attention() does it natively, in csrc/attn_call.cpp): every step of the
+computation runs in the HIP kernels of csrc/attn_fwd.hip.  There is no CPU or PyTorch fallback; if the
 shared library has not been built, importing the entry points fails loudly.
 """
 import ctypes
@@ -9,6 +9,7 @@ import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libattn_mi355x.so")
+CALL_PATH = os.path.join(_HERE, "_attn_call.so")
 
 ATTN_OK = 0
 ATTN_E_NULL = -1
@@ -79,39 +80,64 @@ def attn_version():
     return int(load().attn_version())
 
 
+def _check(q, k, v):
+    import torch
+    if not (q.is_cuda and k.is_cuda and v.is_cuda):
+        raise ValueError("attention() needs device tensors; there is no CPU path")
+    for t in (q, k, v):
+        if t.dtype != torch.bfloat16 or not t.is_contiguous() or t.dim() != 4:
+            raise ValueError("q, k, v must be contiguous 4-d BF16 tensors [B, S, H, D]")
+    B, _, _, D = q.shape
+    if (k.shape[0], k.shape[3]) != (B, D) or v.shape != k.shape:
+        raise ValueError("inconsistent q/k/v shapes")
+
+
+_call = None        # csrc/attn_call.cpp, once it is loaded
+
+
+def _load_call():
+    global _call
+    if not os.path.exists(CALL_PATH):
+        raise ImportError(f"{CALL_PATH} is missing: build it with `python -m paper_2603_24517_amd.build [--all]`")
+    import importlib.util
+    import torch  # noqa: F401  (its libraries are the module's dependencies)
+    spec = importlib.util.spec_from_file_location(__name__ + "._attn_call", CALL_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    module.bind(ctypes.cast(load().attn_fwd, ctypes.c_void_p).value)
+    _call = module.call
+
+
 def attention(q, k, v, causal=False, scale=None):
     """Allocate O and LSE with torch on q's device and run attn_fwd on torch's current stream.
 
     q [B,Sq,Hq,D], k/v [B,Skv,Hkv,D], BF16, contiguous, on a ROCm device.
     Returns (O BF16 [B,Sq,Hq,D], LSE FP32 [B,Hq,Sq]).
     """
+    if _call is None:
+        _check(q, k, v)
+        _load_call()
+    out = _call(q, k, v, causal, scale)
+    if type(out) is tuple:
+        return out
+    if out is None:
+        return _attention(q, k, v, causal, scale)
+    raise AttnError(out)
+
+
+def _attention(q, k, v, causal, scale):
+    """attention() in general: tensor subclasses, torch function modes."""
     import torch
-    if not (q.is_cuda and k.is_cuda and v.is_cuda):
-        raise ValueError("attention() needs device tensors; there is no CPU path")
-    bf16 = torch.bfloat16
-    for t in (q, k, v):
-        if t.dtype != bf16 or not t.is_contiguous() or t.dim() != 4:
-            raise ValueError("q, k, v must be contiguous 4-d BF16 tensors [B, S, H, D]")
+    _check(q, k, v)
     B, Sq, Hq, D = q.shape
-    kv_shape = k.shape
-    Bk, Skv, Hkv, Dk = kv_shape
-    if (Bk, Dk) != (B, D) or v.shape != kv_shape:
-        raise ValueError("inconsistent q/k/v shapes")
+    _, Skv, Hkv, _ = k.shape
     if scale is None:
         scale = D ** -0.5
     o = torch.empty_like(q)
     lse = torch.empty((B, Hq, Sq), dtype=torch.float32, device=q.device)
-    # The raw stream handle, and no change of device where q's is the current one: the Stream object and the device
-    # context of the general form cost more than the launch itself.
-    from torch._C import _cuda_getCurrentRawStream
-    index = q.get_device()
-    args = (q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), B, Hq, Hkv, Sq, Skv, D,
-            1 if causal else 0, float(scale), _cuda_getCurrentRawStream(index))
-    if index == torch.cuda.current_device():
-        rc = load().attn_fwd(*args)
-    else:
-        with torch.cuda.device(index):
-            rc = load().attn_fwd(*args)
+    with torch.cuda.device(q.get_device()):
+        rc = load().attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), B, Hq, Hkv, Sq, Skv, D,
+                             1 if causal else 0, float(scale), torch.cuda.current_stream().cuda_stream)
     if rc != ATTN_OK:
         raise AttnError(rc)
     return o, lse

@@ -1,6 +1,6 @@
 """Build the gfx950 shared libraries in-tree with hipcc.
 
-    python -m paper_2603_24517_amd.build            the attention library (C ABI of include/attn.h)
+    python -m paper_2603_24517_amd.build            the attention library (C ABI of include/attn.h) and the binding's native part
     python -m paper_2603_24517_amd.build --all      that, the measurement-aid library (include/attn_probe.h)
                                                      and every variant of the attention kernel
 
@@ -18,6 +18,8 @@ LIB = os.path.join(HERE, "libattn_mi355x.so")
 PROBE_SRC = os.path.join(HERE, "csrc", "attn_probe.hip")
 PROBE_LIB = os.path.join(HERE, "libattn_probe.so")
 VARIANT_DIR = os.path.join(HERE, "variants")
+CALL_SRC = os.path.join(HERE, "csrc", "attn_call.cpp")
+CALL_LIB = os.path.join(HERE, "_attn_call.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -74,6 +76,21 @@ def build_probe(verbose=False):
     return _hipcc([], PROBE_LIB, PROBE_SRC, verbose)
 
 
+def build_call(verbose=False):
+    """The Python binding's native part: host code against torch's headers and libraries."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{root}/include", f"-I{root}/include/torch/csrc/api/include",
+           "-I/opt/rocm/include", f"-I{sysconfig.get_paths()['include']}", "-o", CALL_LIB, CALL_SRC, f"-L{root}/lib", f"-Wl,-rpath,{root}/lib",
+           "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return CALL_LIB
+
+
 def build_variants(names=None, verbose=False):
     os.makedirs(VARIANT_DIR, exist_ok=True)
     return [build_library(VARIANTS[n], variant_path(n), verbose) for n in (names or VARIANTS)]
@@ -83,7 +100,7 @@ def build_all(verbose=False, jobs=4):
     """Everything, a few compilations at a time (each is a single-threaded hipcc run of about ten seconds)."""
     from concurrent.futures import ThreadPoolExecutor
     os.makedirs(VARIANT_DIR, exist_ok=True)
-    tasks = [lambda: build_library(verbose=verbose), lambda: build_probe(verbose=verbose)]
+    tasks = [lambda: build_call(verbose=verbose), lambda: build_library(verbose=verbose), lambda: build_probe(verbose=verbose)]
     tasks += [lambda n=n: build_library(VARIANTS[n], variant_path(n), verbose) for n in VARIANTS]
     with ThreadPoolExecutor(max_workers=jobs) as pool:
         for f in [pool.submit(t) for t in tasks]:
@@ -95,3 +112,4 @@ if __name__ == "__main__":
         build_all(verbose=True)
     else:
         print(build_library(extra_flags=sys.argv[1:], verbose=True))
+        print(build_call(verbose=True))
