@@ -1554,8 +1554,8 @@ void attn_fwd_kernel(const Params p)
 //     M = max_w m_w,  f_w = 2^(m_w - M),  O = sum_w f_w acc_w / sum_w f_w lr_w,  LSE = ln2 (M + log2 sum_w f_w l_w).
 // No barrier inside the key loop.
 //
-// When the items are fewer than the compute units, each item is shared by `splits` workgroups, which
-// take contiguous ranges of its key blocks.  They leave (acc, m, l, lr) in device memory and the one that arrives last
+// When the items are fewer than the compute units, or would leave part of a round of them without work for long, each item is
+// shared by `splits` workgroups, which take contiguous ranges of its key blocks.  They leave (acc, m, l, lr) in device memory and the one that arrives last
 // merges them, in the order of the ranges, whatever the order of arrival, so that the result does not depend on it.  Nor does it
 // depend on the memory: where none is free, an item's first workgroup takes the same ranges one after the other and adds them up
 // the same way.
@@ -2055,7 +2055,7 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
 // The kernel with workgroups of four wavefronts, for everything between the two others: calls of too few 256-row items to fill the
 // chip evenly, and short sequences, whose items are mostly prologue and epilogue.  Two workgroups share a compute unit, with a barrier of their own
 // each, so that one computes where the other starts, waits or ends; workgroups are handed out by the hardware as others end,
-// longest first.  (One workgroup of eight wavefronts per compute unit in the same loop: 24 x 200 30.1 us instead of 20.0, 2 x 1500 56 instead of 44.)
+// longest first.  (One workgroup of eight wavefronts per compute unit, in an earlier form of the loop: 24 x 200 30.1 us instead of 22.4, 2 x 1500 56 instead of 45.)
 //
 // An item is 128 rows (KG = 1: each wavefront has 32 of them and all keys), or 64 (KG = 2: two pairs of wavefronts share the
 // rows' keys, every other block of 32 each, and add their results up through LDS at the end).  64 rows make twice as many items, each of half
