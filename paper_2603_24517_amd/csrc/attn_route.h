@@ -202,15 +202,15 @@ inline int split_parts(int64_t items, int ntile, int blocks, int ncu)
 
 // The same for more items than half of the compute units, which are too many for one round of parts, where K and V come from memory: several
 // rounds of shorter workgroups, where whole items leave part of a round empty.  A full round reads 6.64 TB/s, a compute unit by itself
-// at most 1.47 times its share of that, a workgroup costs about six blocks beside its own, and the merge at the end three.  (One row, whole items /
-// in parts, us: 16384 keys, 144 items 220.2 / 203.5; 264 487.1 / 358.3; 272 492.7 / 370.0; 384 535.3 / 486.0; 2000 keys, 264 items 64.5 / 60.8; 4000 keys, 136 items
-// 55.7 / 51.9; but 1000 keys, 320 items 36.3 / 39.7.)
+// at most 1.47 times its share of that, a workgroup costs about six blocks beside its own, and the launch in front or the merge five.  (One row, whole items /
+// in parts, us: 16384 keys, 144 items 220.2 / 203.5; 264 487.1 / 358.3; 272 492.7 / 370.0; 384 535.3 / 486.0; 2000 keys, 264 items 64.5 / 60.8, on another
+// stream than the null stream 68.5 before and 64.9; but 1000 keys, 320 items 36.3 / 39.7, and 1500 keys, 280 items on another stream 52.9 before and 55.3.)
 inline int split_rounds(int64_t items, int blocks, int ncu)
 {
     auto cost = [&](int s) {
         const int64_t wgs = items * s, rest = wgs % ncu;
         const double last = rest == 0 ? 0 : (double)rest / ncu > 0.68 ? (double)rest / ncu : 0.68;
-        return ((blocks + s - 1) / s + 6) * ((double)(wgs / ncu) + last) + (s > 1 ? 3 : 0);
+        return ((blocks + s - 1) / s + 6) * ((double)(wgs / ncu) + last) + (s > 1 ? 5 : 0);
     };
     int best = 1;
     if (items * 2 <= ncu || items > SPLIT_MAX_ITEMS) return best;
