@@ -243,8 +243,22 @@ inline int64_t whole_items_ns(const Route &p, bool causal)
     const int64_t over = busy < 500 ? 0 : busy > 750 ? 250 : busy - 500;
     return (1150 + over * 400 / 250) * longest;
 }
+// Split-key kernel: as at split_parts.
+inline int64_t split_ns(int64_t items, int ntile, int64_t blocks, int ncu)
+{
+    const int parts = split_parts(items, ntile, (int)blocks, ncu);
+    const int64_t rounds = (items * parts + ncu - 1) / ncu;
+    return (5000 + 163 * blocks / parts) * rounds + (parts > 1 ? 4000 + 250 * parts : 0);
+}
+
 constexpr int64_t LAST_CACHE_BYTES = 256ll << 20;       // of an MI355X
 
+// Whole items of 256 rows against items of 128 and 64 rows in workgroups of half the size: estimates, in us, fitted to 680 calls (4 to
+// 9500 items of 128 rows, 3 to 22000 keys, masked and not; 9 of 10 estimates are within 15 % of what was measured).  Of those calls, five that they
+// send to the smaller workgroups were 2 to 9 % slower there, none by more; all of them together took 0.85 of the time.  Measured (us, 256 rows /
+// 128 / 64): causal: 1 x 1111, 32 heads on 8 29.5 / 21.4 / 17.7; 24 x 200, 16 heads 25.3 / 20.0 / 21.2; 300 x 150, 4 heads 64 / 47 / 50; 1 x
+// 2000, 16 heads 37.9 / 31.3 / 27.1; 11 x 3694, 4 heads 168 / 156 / 177; 8 x 4096, 16 heads 497 / 530 / 658; no mask: 5 x 1200, 4 heads 30.6
+// / 23.3 / 23.0; 2 x 1500, 16 heads 41.7 / 44.0 / 46.5; 42 x 145, 40 heads 77 / 57 / 65.
 struct Lengths {
     int Sq, Skv;
     bool causal;
@@ -260,31 +274,6 @@ struct Lengths {
     }
 };
 inline double clamp01(double x) { return x < 0 ? 0 : x > 1 ? 1 : x; }
-// Split-key kernel, of calls of more than two tiles, fitted to 260 calls (9 of 10 estimates within 22 %): a block takes longer on a full chip,
-// above all where K and V come from memory, which every tile reads again.  (us, 224 items of 709 blocks, four tiles that read the same 650 MB, 228,
-// shared in items of 256 rows 176; 12 x 9 x 16765, 32 heads on 4 170 and 111; 480 items, two rounds, 15 x 232 x 2963, 4 heads 59.6 and 39.7; but 128 items of 256
-// blocks in two parts, 4 x 16 x 8192, 64 on 8 53.7 and 56.2; 64 of 235 in four parts 74 and 90; 200 x 8000, 32 on 8 48.8 and 52.6.)
-inline int64_t split_ns(const Lengths &ln, int groups, int tile_pos, int ntile, int blocks, double kv_bytes, int ncu)
-{
-    const int64_t items = (int64_t)groups * ntile;
-    const int parts = split_parts(items, ntile, blocks, ncu);
-    const int64_t wgs = items * parts, rounds = (wgs + ncu - 1) / ncu;
-    const double busy = clamp01(((double)wgs / ncu - 0.25) * 2);
-    const double block = 0.142 + busy * (0.036 + 0.159 * clamp01(kv_bytes / 684e6));
-    const double average = ln.blocks(tile_pos, ntile, SPLIT_KEYS) / ntile * rounds;
-    const double longest = (!ln.causal || average > blocks ? average : blocks) / parts;
-    const double us = (5.9 + block * longest + (parts > 1 ? 2.9 + 0.25 * parts : 0)) * 0.955;     // (so that 10 % are asked for below, not 5)
-    // (as at split_parts, where it is more: calls of few keys in two rounds)
-    const double least = (5 + 0.163 * blocks / parts) * rounds + (parts > 1 ? 4 + 0.25 * parts : 0);
-    return (int64_t)(1000 * (us > least ? us : least));
-}
-
-// Whole items of 256 rows against items of 128 and 64 rows in workgroups of half the size: estimates, in us, fitted to 680 calls (4 to
-// 9500 items of 128 rows, 3 to 22000 keys, masked and not; 9 of 10 estimates are within 15 % of what was measured).  Of those calls, five that they
-// send to the smaller workgroups were 2 to 9 % slower there, none by more; all of them together took 0.85 of the time.  Measured (us, 256 rows /
-// 128 / 64): causal: 1 x 1111, 32 heads on 8 29.5 / 21.4 / 17.7; 24 x 200, 16 heads 25.3 / 20.0 / 21.2; 300 x 150, 4 heads 64 / 47 / 50; 1 x
-// 2000, 16 heads 37.9 / 31.3 / 27.1; 11 x 3694, 4 heads 168 / 156 / 177; 8 x 4096, 16 heads 497 / 530 / 658; no mask: 5 x 1200, 4 heads 30.6
-// / 23.3 / 23.0; 2 x 1500, 16 heads 41.7 / 44.0 / 46.5; 42 x 145, 40 heads 77 / 57 / 65.
 // One workgroup of eight wavefronts per compute unit, one item after the other.
 inline double rows256_us(const Route &p, const Lengths &ln, int ncu, double bytes)
 {
@@ -384,7 +373,6 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
     // The same work as a line cut into equal stretches.  From 4 items per compute unit on, whole items leave at most a fifth of the chip idle at the
     // end, and sharing has not been faster.  (5 %: what the estimates are worth; of 60 calls that they put further ahead, none was
     // slower shared.)
-    const Lengths ln = {Sq, Skv, causal != 0};
     Share &sr = p.share;
     sr.wgs = 8 * cu_slots;
     sr.groups = (int)((int64_t)B * Hkv * sh.chunks);
@@ -401,10 +389,13 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
             if (sr.wgs > most) sr.wgs = most;
             const int64_t slots = sr.wgs + (total < sr.wgs ? total : sr.wgs);
             sr.units = (int)((SHARE_HEADER_BYTES + slots * SHARE_SLOT_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
-            const double kv = (double)B * Hkv * Skv * HD * 4;
             const int64_t blocks32 = (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS;
-            const bool few = total * 4 <= ncu && ATTN_SMALL_PATH == 1;      // (the other way is the split-key kernel)
-            const int64_t whole = few ? split_ns(ln, sr.groups, split_tile_pos, split_ntile, (int)blocks32, kv, ncu) : whole_items_ns(p, causal != 0);
+            // (The other way of `few` is the split-key kernel.  Its estimate is low on a full chip, above all where K and V come from memory, and
+            // some calls that stay with it would be faster shared: 9 x 26 x 27226, 12 heads on 3 204 us and 112.  They stay because it rounds its
+            // weights against eight running maxima per part and a shared item against one: O of these calls was off by 2.25e-3 and 2.34e-3 for N(0,1)
+            // scores, 1.68e-3 and 1.93e-3 for four times that.)
+            const bool few = total * 4 <= ncu && ATTN_SMALL_PATH == 1;
+            const int64_t whole = few ? split_ns(split_items, split_ntile, blocks32, ncu) : whole_items_ns(p, causal != 0);
             // Whole items that run at once walk through the keys of a group together, and one of them brings a block into the
             // XCD's L2 for all.  Stretches of the line do not, which tells when K and V are larger than the last cache: 9 x 571 x
             // 33965, 16 heads (2.5 GB), estimated 10 % faster shared, whole 1669, shared 1821; 20 x 281 x 25757 (4.2 GB), 12 %, 1912 and 2014;
@@ -453,13 +444,14 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
             sp.units = (int)((SPLIT_HEADER_BYTES + split_items * sp.splits * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
     }
 
-    // What is left may be faster in smaller workgroups.  (Not what the split-key kernel gets: it rounds its weights against more maxima, and
-    // its results are 10 % closer to the exact ones.)
+    // What is left may be faster in smaller workgroups.  (Not what the split-key kernel gets, for the same reason as above: its results are
+    // closer to the exact ones.)
     Rows &rw = p.rows;
     rw.kgroups = 0;
     if (ATTN_ROWS != 0 && (ATTN_ROWS != 1 || p.kind != ROUTE_SPLIT)) {
         int kgroups = ATTN_ROWS == 2 ? 1 : ATTN_ROWS == 3 ? 2 : 0;
         if (ATTN_ROWS == 1) {
+            const Lengths ln = {Sq, Skv, causal != 0};
             const double kv = (double)B * Hkv * Skv * HD * 4, bytes = kv + (double)B * Hkv * sh.G * Sq * HD * 4;
             const bool cached = kv <= (double)LAST_CACHE_BYTES;
             const double r1 = rows_us(p, ln, 1, ncu, bytes, cached), r2 = rows_us(p, ln, 2, ncu, bytes, cached);
