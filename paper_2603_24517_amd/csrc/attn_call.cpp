@@ -9,6 +9,7 @@
 #include <c10/core/DeviceGuard.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <climits>
@@ -26,7 +27,7 @@ PyObject *refuse(const char *why)
 }
 
 // call(q, k, v, causal, scale): (O, LSE); a status code of the C entry if it is not 0; None if this is not its business (a tensor of another
-// type than torch.Tensor itself, a torch function mode, sizes beyond an int, a scale that is no number, an exception of torch's): the
+// type than torch.Tensor itself, a torch function mode, sizes beyond an int, a scale that is no number, a C++ exception of torch's): the
 // caller has a general form.
 PyObject *call(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
@@ -84,9 +85,12 @@ PyObject *call(PyObject *, PyObject *const *args, Py_ssize_t nargs)
         Py_XDECREF(po_);
         Py_XDECREF(pl_);
         return both;
+    } catch (python_error &e) {     // of a dispatch mode, for instance: the exception itself, whether the interpreter still holds it or `e` does
+        e.restore();
     } catch (const std::exception &) {
-        Py_RETURN_NONE;     // (the general form meets it again, and torch raises its own exception)
     }
+    if (PyErr_Occurred()) return nullptr;
+    Py_RETURN_NONE;         // (the general form meets it again, and torch raises its own exception)
 }
 
 // bind(address of attn_fwd)
