@@ -365,12 +365,15 @@ __device__ inline u32x4 pool_load16(__amdgpu_buffer_rsrc_t rs, uint32_t lane_at,
 {
     return __builtin_amdgcn_raw_buffer_load_b128(rs, lane_at, at, POOL_SC1);
 }
-__device__ inline void pool_clear(uint32_t *counter) { __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void pool_clear(uint32_t unit, uint32_t *counter)
+{
+    if (sets_counters_back(unit)) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ inline void pool_store(float *at, float a) { __hip_atomic_store(at, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline float pool_load(const float *at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline void pool_give(uint32_t u, int n)
 {
-    if (u >= POOL_UNITS) return;        // the region
+    if (sets_counters_back(u)) return;        // the region
     __hip_atomic_fetch_and(&g_pool_taken, ~(((1ull << n) - 1) << u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -1098,7 +1101,7 @@ void attn_fwd_kernel(const Params p)
                 seen = __builtin_amdgcn_readfirstlane(__hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             }
             asm volatile("" ::: "memory");
-            if (ln == 0) pool_clear(arrived);
+            if (ln == 0) pool_clear(unit, arrived);
             const uint32_t in = slot_of(1 - mine);
             const u32x4 st = pool_load16(rs, lane_at, in + 16 * 1024);
             u32x4 x[16];
@@ -1125,7 +1128,7 @@ void attn_fwd_kernel(const Params p)
         leave();
         if (count(1) != (uint32_t)parts - 1) return false;
         asm volatile("" ::: "memory");
-        if (ln == 0) pool_clear(arrived);
+        if (ln == 0) pool_clear(unit, arrived);
         // Part after part in halves of 32 accumulator elements, the next half always in flight.
         reset_state();
         u32x4 st, xa[8], xb[8];
@@ -1533,7 +1536,7 @@ void attn_fwd_kernel(const Params p)
             uint32_t *left = (uint32_t *)(g_pool + (size_t)unit * POOL_UNIT_BYTES);
             const uint32_t n = __hip_atomic_fetch_add(left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (n == (uint32_t)sr.wgs - 1) {
-                pool_clear(left);
+                pool_clear(unit, left);
                 pool_give(unit, sr.units);
             }
         }
@@ -2019,8 +2022,8 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
             }
             __syncthreads();                // everything of this item is read
             if (tid == 0) {
-                pool_clear(&header[1 + item]);
-                if (unit < POOL_UNITS) {        // (the region is not given back)
+                pool_clear(unit, &header[1 + item]);
+                if (!sets_counters_back(unit)) {        // (the region is not given back)
                     const uint32_t done = __hip_atomic_fetch_add(&header[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     if (done == (uint32_t)(p.nrest * p.ntile) - 1) pool_give(unit, p.units);
                 }

@@ -120,6 +120,10 @@ static_assert(SHARE_MAX_UNITS <= POOL_UNITS / 3, "several launches fit the pool"
 // results.
 constexpr int REGION_UNITS = SHARE_MAX_UNITS + SPLIT_MAX_UNITS;
 constexpr uint32_t REGION_SHARE_UNIT = POOL_UNITS, REGION_SPLIT_UNIT = POOL_UNITS + SHARE_MAX_UNITS;       // first units
+// Whether a launch's counters are set back to zero by whoever takes them to their last value.  Those of the region are: the end of the launch
+// comes between that store and the next launch's first count.  Units of the pool belong to another launch as soon as they are given back, which
+// nothing orders behind such a store, so that a late one would erase arrivals of that launch; the launch in front clears theirs.
+constexpr bool sets_counters_back(uint32_t unit) { return unit >= (uint32_t)POOL_UNITS; }
 
 // How the work of the kernel with workgroups of four wavefronts is cut up: items of 128 / kgroups rows, whose keys are shared by
 // `kgroups` groups of wavefronts.

@@ -26,3 +26,7 @@ extern "C" int steps(int B, int Hq, int Hkv, int Sq, int Skv, int causal, int nc
 }
 
 extern "C" long long pool_bytes() { return (long long)attn::POOL_UNITS * attn::POOL_UNIT_BYTES; }
+
+extern "C" int pool_units() { return attn::POOL_UNITS; }
+extern "C" int region_units() { return attn::REGION_UNITS; }
+extern "C" int sets_counters_back(unsigned unit) { return attn::sets_counters_back(unit); }

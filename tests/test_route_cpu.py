@@ -119,3 +119,13 @@ def test_few_rows_against_long_keys_keep_the_smaller_error(route, shape, causal)
     """The split-key kernel rounds its weights against eight running maxima per part, a shared item of 256 rows against one per part, with
     up to 17 % more error, whichever of the two is faster."""
     assert route(*shape, causal)["kind"] == SPLIT
+
+
+def test_only_the_regions_counters_are_set_back_by_the_launch(lib):
+    """A pool unit is another launch's once it is given back, with nothing to order an earlier store to its counters before that launch's
+    counts: those are cleared by the launch in front, never behind the last count.  The region's have no launch in front."""
+    pool, region = lib.pool_units(), lib.region_units()
+    assert [lib.sets_counters_back(u) for u in range(pool + region)] == [0] * pool + [1] * region
+    source = open(os.path.join(os.path.dirname(HERE), "paper_2603_24517_amd", "csrc", "attn_fwd.hip")).read()
+    stores = re.findall(r".*\b__hip_atomic_store\([^,]*counter.*", source)
+    assert len(stores) == 1 and "if (sets_counters_back(unit))" in stores[0], stores
