@@ -258,8 +258,8 @@ inline int64_t split_ns(int64_t items, int ntile, int64_t blocks, int ncu)
 constexpr int64_t LAST_CACHE_BYTES = 256ll << 20;       // of an MI355X
 
 // Whole items of 256 rows against items of 128 and 64 rows in workgroups of half the size: estimates, in us, fitted to 680 calls (4 to
-// 9500 items of 128 rows, 3 to 22000 keys, masked and not; 9 of 10 estimates are within 15 % of what was measured).  Of those calls, five that they
-// send to the smaller workgroups were 2 to 9 % slower there, none by more; all of them together took 0.85 of the time.  Measured (us, 256 rows /
+// 9500 items of 128 rows, 3 to 22000 keys, masked and not; 9 of 10 estimates are within 15 % of what was measured, K and V in the last cache).  How far
+// ahead the smaller workgroups have to be stands where they are compared.  Measured (us, 256 rows /
 // 128 / 64): causal: 1 x 1111, 32 heads on 8 29.5 / 21.4 / 17.7; 24 x 200, 16 heads 25.3 / 20.0 / 21.2; 300 x 150, 4 heads 64 / 47 / 50; 1 x
 // 2000, 16 heads 37.9 / 31.3 / 27.1; 11 x 3694, 4 heads 168 / 156 / 177; 8 x 4096, 16 heads 497 / 530 / 658; no mask: 5 x 1200, 4 heads 30.6
 // / 23.3 / 23.0; 2 x 1500, 16 heads 41.7 / 44.0 / 46.5; 42 x 145, 40 heads 77 / 57 / 65.
@@ -459,11 +459,23 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
             const double kv = (double)B * Hkv * Skv * HD * 4, bytes = kv + (double)B * Hkv * sh.G * Sq * HD * 4;
             const bool cached = kv <= (double)LAST_CACHE_BYTES;
             const double r1 = rows_us(p, ln, 1, ncu, bytes, cached), r2 = rows_us(p, ln, 2, ncu, bytes, cached);
-            // (What the estimates are worth.  Shared items: of seven calls of less than 80 us that are put 10 to 15 % ahead, the measured gain was
-            // 12 to 23 %; of seven longer ones between 9 % and, once, a loss of 2 %.)
-            const double shared = shared_ns(p, total) * 1e-3;
-            const double limit = p.kind != ROUTE_SHARED ? rows256_us(p, ln, ncu, bytes) / 1.06 : shared / (shared < 80 ? 1.10 : 1.15);
-            if ((r1 < r2 ? r1 : r2) < limit) kgroups = r1 < r2 ? 1 : 2;
+            // How far ahead the smaller workgroups have to be estimated, so that calls are not slower there than in 256-row items, with K and V in the
+            // last cache or from memory.  6 % (shared items: 10 to 15) were not enough: of 1020 measured calls that went there, 44 were more than 2 %
+            // slower one way or the other.  Of 646 others that the margins below send there from whole items, none was slower; from shared ones,
+            // whose margins were raised once more since, 3 of 45, at 17 % ahead.
+            // - Keys more than twice as long as the rows: each tile reads them again, and the two stages of items of 64 rows do not cover reads from
+            //   memory, which the estimates do not know (us, 256 rows / smaller, from memory: 2 x 104 x 5599, 64 heads on 8 58.1 / 90.7; 4 x 35 x
+            //   4426 48.6 / 74.7; 4 x 264 x 3506, 32 on 4 73.2 / 81.1; 20 x 269 x 2017, 12 on 3 80.9 / 86.6; 9 x 517 x 4612, 6 on 2 97.3 / 106.9).
+            // - More rows than keys, masked: most rows have no key, which neither estimate knows well (4 x 1607 x 63, 16 heads 11.3 / 11.8).
+            // - From one and a half rounds of 256-row items on, these leave little idle: of 200 calls put 6 to 23 % ahead 27 were slower, up to 14 %
+            //   (22 x 391, 40 heads, masked 105.7 / 120.1); put 25 % ahead or more, none.
+            // - Other calls of shared items against items of 64 rows: 21 % ahead, 2 x 2300, 4 heads 32.9 / 35.0; 1 x 3222, 16 heads 58.1 / 59.5.
+            const bool far = Skv > 2 * (int64_t)Sq, is_shared = p.kind == ROUTE_SHARED;
+            const int best = r1 < r2 || (far && is_shared) ? 1 : 2;
+            const double now = is_shared ? shared_ns(p, total) * 1e-3 : rows256_us(p, ln, ncu, bytes);
+            const double ahead = is_shared ? (far ? 0.78 : best == 2 ? 0.80 : now < 80 ? 1 / 1.10 : 1 / 1.15) : far || (causal && Sq > Skv) ? 0.70
+                                 : 2 * (int64_t)total > 3 * ncu ? 0.80 : 1 / 1.06;
+            if ((best == 1 ? r1 : r2) < now * ahead) kgroups = best;
         }
         if (kgroups != 0) {
             const int pos = 128 / kgroups / sh.pack, ntile = (Sq + pos - 1) / pos;

@@ -49,6 +49,18 @@ def test_which_calls(rows, shape, causal, kgroups):
     assert r["kgroups"] == kgroups and (kgroups == 0 or r["kind"] == WHOLE), r
 
 
+@pytest.mark.parametrize("shape,causal", [
+    ((2, 64, 8, 104, 5599), True), ((4, 64, 8, 35, 4426), False), ((2, 40, 40, 105, 5604), True), ((1, 40, 40, 293, 3978), False),     # shared
+    ((9, 6, 2, 517, 4612), True), ((20, 12, 3, 269, 2017), True), ((2, 4, 4, 2300, 2300), True), ((1, 16, 16, 3222, 3222), True),             # shared
+    ((20, 32, 8, 63, 6726), True), ((9, 40, 40, 148, 2876), True), ((4, 40, 40, 218, 2809), True), ((4, 32, 4, 264, 3506), True),       # far keys
+    ((22, 40, 40, 391, 391), True), ((91, 16, 16, 242, 242), False), ((59, 16, 16, 400, 400), True), ((162, 4, 4, 221, 221), False),    # many items
+    ((4, 16, 16, 1607, 63), True), ((4, 32, 4, 2481, 34), True),                                                                        # rows without keys
+])
+def test_calls_that_smaller_workgroups_made_slower(rows, shape, causal):
+    """Measured 3 to 56 % slower there than in 256-row items, with K and V from memory or from the last cache."""
+    assert rows(*shape, causal)["kgroups"] == 0
+
+
 def _item(r, bid):
     """Workgroup -> (tile, rest), as the kernel does it."""
     if bid < r["window0"] * r["ntile"]:
@@ -60,7 +72,7 @@ def _item(r, bid):
     return r["ntile"] - 1 - tile_r, rest
 
 
-@pytest.mark.parametrize("shape,ncu", [((24, 16, 16, 200, 200), 256), ((24, 16, 16, 200, 200), 80), ((1, 32, 8, 1111, 1111), 256), ((11, 4, 4, 998, 998), 256),
+@pytest.mark.parametrize("shape,ncu", [((24, 16, 16, 200, 200), 256), ((24, 16, 16, 150, 150), 80), ((1, 32, 8, 1111, 1111), 256), ((11, 4, 4, 998, 998), 256),
                                        ((11, 4, 4, 998, 998), 80), ((35, 4, 4, 150, 150), 256), ((7, 12, 3, 600, 700), 256),
                                        ((1, 3, 3, 5000, 90), 80), ((13, 40, 40, 133, 135), 256)])
 def test_every_item_once(rows, shape, ncu):
