@@ -2628,7 +2628,7 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
         // (i + INT32_MAX - Sq - 64 is above every key for i >= 0 and within 32 bits for the i < Sq + 32 of a tile)
         sp.off = causal ? Skv - Sq : INT32_MAX - Sq - 64;
         sp.c = p.c;
-        sp.once = r.split.once;
+        sp.once = r.split.once || (region && r.split.once_region);
     } else {
         sp.tile_pos = sh.tile_pos;
         sp.ntile = r.sched.ntile;

@@ -93,7 +93,8 @@ struct Split {
     int nrest;              // B * Hkv * chunks; items = ntile * nrest
     int splits;             // workgroups that share an item
     int units;              // POOL_UNIT_BYTES units of device memory, 0 if splits == 1
-    bool once;              // K and V are each read by one work item and come from memory
+    bool once;              // K and V are each read by one work item, and are more than the last cache holds
+    bool once_region;       // the launch reads them past the caches where it has the region, too
 };
 
 // Device memory for partial results (g_pool of the kernels): sizes of its units, and of what a launch keeps there.
@@ -207,8 +208,8 @@ inline int split_parts(int64_t items, int ntile, int blocks, int ncu)
 // The same for more items than half of the compute units, which are too many for one round of parts, where K and V come from memory: several
 // rounds of shorter workgroups, where whole items leave part of a round empty.  A full round reads 6.64 TB/s, a compute unit by itself
 // at most 1.47 times its share of that, a workgroup costs about six blocks beside its own, and the launch in front or the merge five.  (One row, whole items /
-// in parts, us: 16384 keys, 144 items 220.2 / 203.5; 264 487.1 / 358.3; 272 492.7 / 370.0; 384 535.3 / 486.0; 2000 keys, 264 items 64.5 / 60.8, on another
-// stream than the null stream 68.5 before and 64.9; but 1000 keys, 320 items 36.3 / 39.7, and 1500 keys, 280 items on another stream 52.9 before and 55.3.)
+// in parts, us: 16384 keys, 144 items 220.2 / 203.5; 264 487.1 / 358.3; 272 492.7 / 370.0; 384 535.3 / 486.0; but 1000 keys, 320 items
+// 36.3 / 39.7, and 1500 keys, 280 items, with a launch in front 52.9 / 55.3.)
 inline int split_rounds(int64_t items, int blocks, int ncu)
 {
     auto cost = [&](int s) {
@@ -427,15 +428,23 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
                                                         (total > ncu && total * 2 <= 3 * ncu && Skv <= 768)));
     const bool small = ATTN_SMALL_PATH == 2 || (ATTN_SMALL_PATH == 1 && ((total * 4 <= ncu && !share) || few_rows));
     p.kind = share ? ROUTE_SHARED : ROUTE_WHOLE;
-    // Loads past the caches (nt) get 7.0 TB/s from HBM on this card, ordinary ones 6.1 (a kernel that only reads); but then the next call does
-    // not find K and V in the last cache, and several items of a K/V head not in an L2: 2 x 16 x 8192, 64 heads on 8, four items 26.0 us
-    // and 34.3.  Read once, us, from memory, ordinary / past the caches: 16 x 1 x 4000, 32 heads on 8 (262 MB) 52.1 / 48.4; 1 x 1 x 32768 (134 MB) 38.9 /
-    // 37.2; 4 x 1 x 4096 (67 MB) 23.0 / 21.3; 1 x 1 x 8192 (34 MB, six calls' K and V in turn fit the cache) 18.2 / 21.3.  So from a quarter of the
-    // last cache on, where four calls' would fill it.
-    const bool once = split_ntile == 1 && sh.chunks == 1 && (int64_t)B * Hkv * Skv * HD * 4 >= LAST_CACHE_BYTES / 4;
+    // Loads past the caches (nt) get 7.0 TB/s from HBM on this card, ordinary ones 6.1 (a kernel that only reads); but then a call that is repeated
+    // does not find K and V in the last cache, and several items of a K/V head not in an L2: 2 x 16 x 8192, 64 heads on 8, four items 26.0 us
+    // and 34.3.  Where they are read by one item, us, ordinary / past the caches, K and V from memory; repeated: items of one workgroup 18 x 1 x 2000,
+    // 32 heads on 8 (147 MB) 32.4 / 31.0; 25.9 / 30.2; 9 x 7 x 3200, 16 heads (236 MB) 50.6 / 47.6; 38.7 / 47.1; 280 MB 58.4 / 55.3; 49.3 / 53.5; 299 MB 63.7 /
+    // 59.8; 58.5 / 59.1; 306 MB 64.1 / 60.7; 61.4 / 59.9; 328 MB 64.6 / 60.3; 62.9 / 59.4: from nine eighths of the last cache on, nothing is lost.  Shared items
+    // 1 x 1 x 32768 (134 MB) 36.1 / 34.5; 31.0 / 33.4; 14 x 1 x 4000 (229 MB) 44.1 / 40.6; 37.5 / 39.6; 16 x 1 x 4000 (262 MB) 48.8 / 44.8; 43.0 / 43.9; 4 x 1 x
+    // 4096 (67 MB) 20.0 / 18.6; 17.3 / 16.9; 1 x 1 x 8192 (34 MB, six calls' K and V in turn fit the cache) 15.3 / 18.4.  On the null stream they go past the
+    // caches from a quarter on: with no launch in front a repeated call takes no longer than it does on another stream with ordinary loads (33.8, 40.0, 45.3,
+    // 20.1).  On other streams it would take up to 2.6 us more than that.
+    const int64_t kv_bytes = (int64_t)B * Hkv * Skv * HD * 4;
+    const bool read_once = split_ntile == 1 && sh.chunks == 1;
     const int split_blocks = (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS;
     int splits = split_parts(split_items, split_ntile, split_blocks, ncu);
-    if (splits == 1 && once) splits = split_rounds(split_items, split_blocks, ncu);
+    const bool shared_once = splits > 1 && read_once && kv_bytes >= LAST_CACHE_BYTES / 4;
+    // Rounds of parts pay from memory only, and on other streams a little later, as they have a launch in front (us, whole items / rounds, from memory;
+    // repeated: 317 MB, 18 x 1 x 4300 64.7 / 62.4; 59.7 / 61.8; 410 MB, 40 x 1 x 2500 88.4 / 81.5; 88.3 / 81.1).
+    if (splits == 1 && read_once && 3 * kv_bytes >= 4 * LAST_CACHE_BYTES) splits = split_rounds(split_items, split_blocks, ncu);
     if (small && split_items * splits <= MAX_WGS) {
         Split &sp = p.split;
         p.kind = ROUTE_SPLIT;
@@ -443,7 +452,8 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
         sp.ntile = split_ntile;
         sp.nrest = sr.groups;
         sp.splits = splits;
-        sp.once = once;
+        sp.once = read_once && 8 * kv_bytes >= 9 * LAST_CACHE_BYTES;
+        sp.once_region = shared_once;
         if (sp.splits > 1)
             sp.units = (int)((SPLIT_HEADER_BYTES + split_items * sp.splits * SPLIT_PART_BYTES + POOL_UNIT_BYTES - 1) / POOL_UNIT_BYTES);
     }

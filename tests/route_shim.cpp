@@ -12,6 +12,8 @@ extern "C" int route(int B, int Hq, int Hkv, int Sq, int Skv, int causal, int nc
     out[2] = r.kind == attn::ROUTE_SPLIT ? out[1] * r.split.splits
                                          : r.kind == attn::ROUTE_SHARED ? r.share.wgs : 8 * r.sched.slots;      // workgroups
     out[3] = r.kind == attn::ROUTE_SPLIT ? r.split.units : r.kind == attn::ROUTE_SHARED ? r.share.units : 0;    // pool units
+    out[4] = r.kind == attn::ROUTE_SPLIT && r.split.once;
+    out[5] = r.kind == attn::ROUTE_SPLIT && (r.split.once || r.split.once_region);                              // on the null stream
     return ATTN_OK;
 }
 

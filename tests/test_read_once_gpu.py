@@ -14,8 +14,12 @@ pytestmark = pytest.mark.gpu
 SCALE = 1.0 / math.sqrt(128)
 
 
-@pytest.mark.parametrize("shape", [(17, 16, 16, 1, 2000), (33, 32, 8, 2, 2111), (9, 16, 16, 7, 8200), (150, 6, 2, 3, 1001)],
-                         ids=lambda s: "x".join(map(str, s)))
+# B, Hq, Hkv, Sq, Skv: rounds of parts (272, 264, 144 and 560 items), and shared items that go past the caches on the null stream alone
+ROUNDS = [(17, 16, 16, 1, 2711), (33, 32, 8, 2, 2711), (9, 16, 16, 7, 8200), (280, 16, 2, 1, 2811)]
+REGION = [(1, 32, 8, 1, 32768), (16, 32, 8, 2, 1811)]
+
+
+@pytest.mark.parametrize("shape", ROUNDS + REGION, ids=lambda s: "x".join(map(str, s)))
 def test_rounds_of_parts(shape):
     print(f"shape {shape}", flush=True)
     B, Hq, Hkv, Sq, Skv = shape

@@ -25,10 +25,10 @@ def lib(tmp_path_factory):
 @pytest.fixture(scope="module")
 def route(lib):
     def call(B, Hq, Hkv, Sq, Skv, causal=True, ncu=NCU):
-        out = (ctypes.c_longlong * 4)()
+        out = (ctypes.c_longlong * 6)()
         rc = lib.route(B, Hq, Hkv, Sq, Skv, int(causal), ncu, out)
         assert rc == A.ATTN_OK
-        return dict(zip(("kind", "items", "wgs", "units"), out))
+        return dict(zip(("kind", "items", "wgs", "units", "once", "once_null"), out))
     return call
 
 
@@ -129,3 +129,23 @@ def test_only_the_regions_counters_are_set_back_by_the_launch(lib):
     source = open(os.path.join(os.path.dirname(HERE), "paper_2603_24517_amd", "csrc", "attn_fwd.hip")).read()
     stores = re.findall(r".*\b__hip_atomic_store\([^,]*counter.*", source)
     assert len(stores) == 1 and "if (sets_counters_back(unit))" in stores[0], stores
+
+
+@pytest.mark.parametrize("shape,once,once_null,parts", [
+    ((18, 32, 8, 1, 2000), 0, 0, 1), ((9, 16, 16, 7, 3200), 0, 0, 1), ((18, 32, 8, 1, 4050), 0, 0, 1),      # a repeated call finds them in the last cache
+    ((18, 16, 16, 1, 1600), 0, 0, 1), ((17, 16, 16, 1, 2000), 0, 0, 1), ((35, 32, 8, 1, 1500), 0, 0, 1),    # nor are they cut into rounds of parts
+    ((18, 32, 8, 1, 4150), 1, 1, 1), ((20, 32, 8, 1, 4000), 1, 1, 1), ((40, 32, 8, 1, 2500), 1, 1, 2),
+    ((1, 32, 8, 1, 32768), 0, 1, 20), ((16, 32, 8, 1, 4000), 0, 1, 2), ((1, 32, 8, 1, 8192), 0, 0, 10), ((2, 64, 8, 16, 8192), 0, 0, 4),
+])
+def test_keys_that_the_last_cache_holds_are_not_read_past_it(route, shape, once, once_null, parts):
+    r = route(*shape)
+    assert (r["kind"], r["once"], r["once_null"], r["wgs"] / r["items"]) == (SPLIT, once, once_null, parts), r
+
+
+def test_calls_of_the_read_once_test_are(route):
+    import test_read_once_gpu as T
+    rounds = [route(*shape, causal) for shape in T.ROUNDS for causal in (False, True)]
+    assert all(r["kind"] == SPLIT and r["once"] and r["wgs"] > r["items"] for r in rounds), rounds
+    assert max(r["items"] for r in rounds) > 512 and max(r["wgs"] for r in rounds) > 1024
+    region = [route(*shape, causal) for shape in T.REGION for causal in (False, True)]
+    assert all(r["kind"] == SPLIT and not r["once"] and r["once_null"] and r["wgs"] > r["items"] for r in region), region
