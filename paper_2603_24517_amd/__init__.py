@@ -81,15 +81,17 @@ def attn_version():
 
 
 def _check(q, k, v):
+    """The shapes of q and of k and v (each asked for once: under a function mode that takes a microsecond)."""
     import torch
     if not (q.is_cuda and k.is_cuda and v.is_cuda):
         raise ValueError("attention() needs device tensors; there is no CPU path")
     for t in (q, k, v):
         if t.dtype != torch.bfloat16 or not t.is_contiguous() or t.dim() != 4:
             raise ValueError("q, k, v must be contiguous 4-d BF16 tensors [B, S, H, D]")
-    B, _, _, D = q.shape
-    if (k.shape[0], k.shape[3]) != (B, D) or v.shape != k.shape:
+    q_shape, kv_shape = q.shape, k.shape
+    if (kv_shape[0], kv_shape[3]) != (q_shape[0], q_shape[3]) or v.shape != kv_shape:
         raise ValueError("inconsistent q/k/v shapes")
+    return q_shape, kv_shape
 
 
 _call = None        # csrc/attn_call.cpp, once it is loaded
@@ -128,16 +130,22 @@ def attention(q, k, v, causal=False, scale=None):
 def _attention(q, k, v, causal, scale):
     """attention() in general: tensor subclasses, torch function modes."""
     import torch
-    _check(q, k, v)
-    B, Sq, Hq, D = q.shape
-    _, Skv, Hkv, _ = k.shape
+    (B, Sq, Hq, D), (_, Skv, Hkv, _) = _check(q, k, v)
     if scale is None:
         scale = D ** -0.5
     o = torch.empty_like(q)
     lse = torch.empty((B, Hq, Sq), dtype=torch.float32, device=q.device)
-    with torch.cuda.device(q.get_device()):
-        rc = load().attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), B, Hq, Hkv, Sq, Skv, D,
-                             1 if causal else 0, float(scale), torch.cuda.current_stream().cuda_stream)
+    # The raw stream handle, and no change of device where q's is the current one: the Stream object and the device
+    # context take longer than the rest of the call.
+    from torch._C import _cuda_getCurrentRawStream
+    index = q.get_device()
+    args = (q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), B, Hq, Hkv, Sq, Skv, D,
+            1 if causal else 0, float(scale), _cuda_getCurrentRawStream(index))
+    if index == torch.cuda.current_device():
+        rc = load().attn_fwd(*args)
+    else:
+        with torch.cuda.device(index):
+            rc = load().attn_fwd(*args)
     if rc != ATTN_OK:
         raise AttnError(rc)
     return o, lse
