@@ -2076,7 +2076,7 @@ struct RowsParams {
     int Hq, Hkv, Sq, Skv, G;
     int pack, pack_log2;    // as in SplitParams: row r of an item is head r % pack, position r / pack
     int chunks;             // G / pack
-    int tile_pos;           // query positions per work item = 128 / pack
+    int tile_pos;           // query positions per work item = 128 / KG / pack
     int ntile;              // ceil(Sq / tile_pos)
     int nrest;              // B * Hkv * chunks; items = ntile * nrest
     int window, window0;    // (group, K/V head, batch entry) units that are worked through together; in the first window there may be fewer
@@ -2091,7 +2091,7 @@ static_assert(2 * ROWS_LDS_BYTES <= LDS_BYTES, "two workgroups fit a CU");
 
 // R row groups of 32 rows, KG key groups; one wavefront for each pair of them.
 template <int KG>
-__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__(64 * ROWS_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_fwd_kernel_rows(const RowsParams p)
 {
     constexpr int R = ROWS_WAVES / KG, NS = rows_stages(KG);
@@ -2607,7 +2607,7 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
     p.c = scale * 1.4426950408889634f;
     p.shape = sh; p.sched = r.sched; p.share = r.share;
 
-        const bool region = ATTN_POOL && shares_items(r) && st == nullptr;
+    const bool region = ATTN_POOL && shares_items(r) && st == nullptr;
     p.unit = region ? REGION_SHARE_UNIT : POOL_NONE;
 
     SplitParams sp = {};

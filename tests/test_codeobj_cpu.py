@@ -15,14 +15,20 @@ LIBS = [("shipped", B.LIB)] + [(n, B.variant_path(n)) for n in B.VARIANTS]
 @pytest.mark.parametrize("name,path", LIBS, ids=[n for n, _ in LIBS])
 def test_attention_kernels_have_no_scratch_and_fit_the_register_file(name, path):
     meta = codeobj.kernel_metadata(path)
-    kernels = {k: v for k, v in meta.items() if "attn_fwd_kernel" in k or "attn_fwd_split_kernel" in k}
-    assert len(kernels) == 8 and len(meta) == 8, sorted(meta)       # 256-row: causal x (scale >= 0, < 0, shared items); split-key: shared or not
-    for k, f in kernels.items():
-        assert f["private_segment_fixed_size"] == 0, (name, k, f)
-        assert f["vgpr_spill_count"] == 0, (name, k, f)
-        assert f["vgpr_count"] + f.get("agpr_count", 0) <= 256, (name, k, f)    # two wavefronts per SIMD
-        assert f["group_segment_fixed_size"] == 0, (name, k, f)                 # LDS is dynamic: all 160 KiB
-        assert f["max_flat_workgroup_size"] == 512, (name, k, f)
+    # kernel, its forms and the threads that it is launched with: 256-row (masked or not, whole or shared items), rows (items of 128, of 64), split-key (shared
+    # items or not)
+    kinds = [("attn_fwd_kernelI", 4, 512), ("attn_fwd_kernel_rowsI", 2, 256), ("attn_fwd_split_kernelI", 2, 512)]
+    assert len(meta) == sum(n for _, n, _ in kinds), sorted(meta)
+    for kind, n, threads in kinds:
+        kernels = {k: f for k, f in meta.items() if kind in k}
+        assert len(kernels) == n, (kind, sorted(meta))
+        for k, f in kernels.items():
+            assert f["private_segment_fixed_size"] == 0, (name, k, f)
+            assert f["vgpr_spill_count"] == 0, (name, k, f)
+            # two wavefronts per SIMD: one workgroup of 512 threads on a compute unit, or two of 256
+            assert f["vgpr_count"] + f.get("agpr_count", 0) <= 256, (name, k, f)
+            assert f["group_segment_fixed_size"] == 0, (name, k, f)                 # LDS is dynamic
+            assert f["max_flat_workgroup_size"] == threads, (name, k, f)
 
 
 def test_probe_kernels_have_no_scratch():
