@@ -15,6 +15,19 @@ pytestmark = pytest.mark.gpu
 SCALE = 1.0 / math.sqrt(128)
 
 
+@pytest.fixture(params=["null_stream", "other_stream"], autouse=True)
+def stream(request):
+    """The null stream's launches have memory of their own for the parts, others take units of the pool."""
+    if request.param == "null_stream":
+        assert torch.cuda.current_stream().cuda_stream == 0
+        yield
+    else:
+        with torch.cuda.stream(torch.cuda.Stream()):
+            assert torch.cuda.current_stream().cuda_stream != 0
+            yield
+    torch.cuda.synchronize()
+
+
 def _run(x, causal, entry=None, scale=SCALE):
     q, k, v = x
     (B, Sq, Hq, D), (_, Skv, Hkv, _) = q.shape, k.shape

@@ -13,6 +13,15 @@ pytestmark = pytest.mark.gpu
 SCALE = 1.0 / math.sqrt(128)
 
 
+@pytest.fixture
+def other_stream():
+    """Launches on the null stream have memory of their own: the pool is what those on other streams take units of."""
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        yield
+    torch.cuda.synchronize()
+
+
 def _call(shape, entry=None, causal=False):
     B, Hq, Hkv, Sq, Skv = shape
     q, k, v = (t.cuda() for t in U.rand_qkv(*shape, seed=9700))
@@ -24,9 +33,10 @@ def _call(shape, entry=None, causal=False):
 
 @pytest.mark.parametrize("entry,shape", [(None, (1, 8, 8, 1, 65536)), ("always_share", (1, 1, 1, 256, 65536))],
                          ids=["split_key_kernel", "256_row_kernel"])
-def test_units_are_given_back(entry, shape):
+def test_units_are_given_back(other_stream, entry, shape):
     """Without units one workgroup takes all of an item, which for these items takes several times as long (measured: 10 and
     more).  Were a launch's units lost, the pool of 64 would be used up after at most that many launches."""
+    assert torch.cuda.current_stream().cuda_stream != 0
     call, _, _ = _call(shape, entry)
 
     def ms(n=10):
@@ -49,9 +59,13 @@ def test_units_are_given_back(entry, shape):
     assert last < 2 * first and without > 4 * first
 
 
-def test_call_after_an_error_of_another_call():
+@pytest.mark.parametrize("null", [True, False], ids=["null_stream", "other_stream"])
+def test_call_after_an_error_of_another_call(request, null):
     """A HIP call that failed before, and whose error nobody has fetched, is no business of a launch: it runs, says so, and
     leaves the record as it is."""
+    if not null:
+        request.getfixturevalue("other_stream")
+    assert (torch.cuda.current_stream().cuda_stream == 0) == null
     lib = A.load()          # (its dependencies hold the HIP runtime)
     lib.hipSetDevice.argtypes, lib.hipGetLastError.argtypes = [ctypes.c_int], []
     call, o, lse = _call((1, 32, 8, 1, 8192))
