@@ -1,5 +1,5 @@
 """Few rows against keys and values that are read once, past the caches, in rounds of parts where whole items would leave a round partly empty:
-the oracle's rows, and the bits of the path without device memory."""
+the oracle's rows, and the bits of the path without device memory, on the null stream, on another one and from a graph."""
 import math
 
 import numpy as np
@@ -33,3 +33,21 @@ def test_rounds_of_parts(shape):
     ref = T._run(dev, True, "no_pool")
     for rep in range(3):
         assert T._same(T._run(dev, True), ref), rep
+    out = torch.empty_like(ref[0]), torch.empty_like(ref[1])
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+
+    def launch():
+        rc = A.attn_fwd(*dev, *out, B, Hq, Hkv, Sq, Skv, 128, True, SCALE, side.cuda_stream)
+        assert rc == 0, A.attn_strerror(rc)
+
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        launch()
+    for rep in range(6):
+        for t in out:
+            t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            graph.replay() if rep % 2 else launch()
+        torch.cuda.synchronize()
+        assert T._same(out, ref), rep
