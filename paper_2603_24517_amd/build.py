@@ -27,12 +27,14 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 
+# every launch through the 256-row kernel, in whole items: for switches that act there
+ALL_256_ROWS = ["-DATTN_SMALL_PATH=0", "-DATTN_SHARE=0"]
 # name -> extra compiler flags; what each stands for is described where the switches are defined
 VARIANTS = {
-    "softmax_blockmax_always": ["-DATTN_SOFTMAX=1"],
-    "softmax_blockmax_vote": ["-DATTN_SOFTMAX=2"],
-    "softmax_blockmax_threshold": ["-DATTN_SOFTMAX=3"],
-    "no_item_overlap": ["-DATTN_ITEM_OVERLAP=0"],
+    "softmax_blockmax_always": ["-DATTN_SOFTMAX=1", *ALL_256_ROWS],
+    "softmax_blockmax_vote": ["-DATTN_SOFTMAX=2", *ALL_256_ROWS],
+    "softmax_blockmax_threshold": ["-DATTN_SOFTMAX=3", *ALL_256_ROWS],
+    "no_item_overlap": ["-DATTN_ITEM_OVERLAP=0", *ALL_256_ROWS],
     # every launch through the 256-row kernel / every launch through the split-key kernel for small problems
     "no_small_path": ["-DATTN_SMALL_PATH=0"],
     "always_small_path": ["-DATTN_SMALL_PATH=2"],
@@ -46,8 +48,8 @@ VARIANTS = {
     # every launch through the kernel with workgroups of four wavefronts, in items of 128 rows / of 64
     "always_rows128": ["-DATTN_ROWS=2"],
     "always_rows64": ["-DATTN_ROWS=3"],
-    "lds_prefetch_1": ["-DATTN_LDS_PREFETCH=1"],
-    "lds_prefetch_5": ["-DATTN_LDS_PREFETCH=5"],
+    "lds_prefetch_1": ["-DATTN_LDS_PREFETCH=1", *ALL_256_ROWS],
+    "lds_prefetch_5": ["-DATTN_LDS_PREFETCH=5", *ALL_256_ROWS],
     # the shipped kernel plus clock stamps of its first workgroup (exports attn_clocks_read as well)
     "clocks": ["-DATTN_CLOCKS"],
     # the same plus cycle sums per phase of one work item (exports attn_phases_read as well)

@@ -25,10 +25,10 @@ def lib(tmp_path_factory):
 @pytest.fixture(scope="module")
 def route(lib):
     def call(B, Hq, Hkv, Sq, Skv, causal=True, ncu=NCU):
-        out = (ctypes.c_longlong * 6)()
+        out = (ctypes.c_longlong * 7)()
         rc = lib.route(B, Hq, Hkv, Sq, Skv, int(causal), ncu, out)
         assert rc == A.ATTN_OK
-        return dict(zip(("kind", "items", "wgs", "units", "once", "once_null"), out))
+        return dict(zip(("kind", "items", "wgs", "units", "once", "once_null", "kgroups"), out))
     return call
 
 
@@ -87,15 +87,17 @@ def test_calls_of_the_bits_test_are_shared(route):
 @pytest.mark.parametrize("shape,takes", [((1, 32, 8, 1, 32768), True), ((1, 32, 8, 512, 16384), True),
                                          ((1, 4, 4, 512, 512), False), ((8, 16, 16, 4096, 4096), False)])
 def test_memory_taken_for_a_launch_that_fails_is_given_back(lib, shape, takes):
-    def steps(refused):
+    def steps(refused, region=0):
         log = ctypes.create_string_buffer(8)
-        rc = lib.steps(*shape, 1, NCU, refused, log)
+        rc = lib.steps(*shape, 1, NCU, refused, region, log)
         return rc, log.value.decode()
     TAKE, MAIN, GIVE = range(3)
     assert steps(-1) == (A.ATTN_OK, "TM" if takes else "M")
     assert steps(MAIN) == (A.ATTN_E_LAUNCH, "TMG" if takes else "M")
     assert steps(TAKE) == ((A.ATTN_E_LAUNCH, "T") if takes else (A.ATTN_OK, "M"))
     assert steps(GIVE)[0] == A.ATTN_OK
+    # a launch that has the region takes nothing and gives nothing back
+    assert steps(-1, 1) == (A.ATTN_OK, "M") and steps(MAIN, 1) == (A.ATTN_E_LAUNCH, "M")
 
 
 def test_header_states_the_device_memory_of_the_code_object(lib):
@@ -149,3 +151,44 @@ def test_calls_of_the_read_once_test_are(route):
     assert max(r["items"] for r in rounds) > 512 and max(r["wgs"] for r in rounds) > 1024
     region = [route(*shape, causal) for shape in T.REGION for causal in (False, True)]
     assert all(r["kind"] == SPLIT and not r["once"] and r["once_null"] and r["wgs"] > r["items"] for r in region), region
+
+
+def test_rounds_of_parts_fit_the_device_memory(lib, route):
+    limits = (ctypes.c_longlong * 4)()
+    lib.split_limits(limits)
+    items, wgs, units, counters = limits
+    assert items <= counters
+    seen = 0
+    for hq, hkv in ((16, 16), (32, 8), (16, 2), (4, 1)):
+        for batch in list(range(1, 300, 7)) + [511, 512, 1023, 1024]:
+            for keys in (700, 1700, 2811, 5000, 16384, 65537):
+                for ncu in (256, 304, 80):
+                    r = route(batch, hq, hkv, 1, keys, True, ncu)
+                    if r["kind"] == SPLIT and r["wgs"] > r["items"]:
+                        seen += r["items"] * 2 > ncu
+                        assert r["items"] <= items and r["wgs"] <= wgs and 0 < r["units"] <= units, (batch, hq, hkv, keys, ncu, r)
+    assert seen > 200, seen
+
+
+def _with_flags(tmp_path, flags):
+    so = str(tmp_path / "route.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", *flags, "-o", so, os.path.join(HERE, "route_shim.cpp")], check=True)
+    shim = ctypes.CDLL(so)
+
+    def call(B, Hq, Hkv, Sq, Skv, causal):
+        out = (ctypes.c_longlong * 7)()
+        assert shim.route(B, Hq, Hkv, Sq, Skv, int(causal), NCU, out) == A.ATTN_OK
+        return dict(zip(("kind", "items", "wgs", "units", "once", "once_null", "kgroups"), out))
+    return call
+
+
+@pytest.mark.parametrize("name", ["softmax_blockmax_always", "softmax_blockmax_vote", "softmax_blockmax_threshold", "no_item_overlap", "lds_prefetch_1",
+                                  "lds_prefetch_5"])
+def test_small_shapes_of_the_256_row_kernels_variants_reach_it(tmp_path, name):
+    """Their switches act in the 256-row kernel alone; the other kernels would pass the parity tests whatever the switch did."""
+    import test_variants_gpu as T
+    from paper_2603_24517_amd import build
+    call = _with_flags(tmp_path, build.VARIANTS[name])
+    routes = [call(*shape[:5], causal) for shape in T.SHAPES + T.JUMP_SHAPES for causal in (False, True)]
+    assert all(r["kind"] == WHOLE and r["kgroups"] == 0 for r in routes), routes
+    assert any(r["items"] > r["wgs"] for r in routes)       # several items per workgroup

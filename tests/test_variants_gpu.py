@@ -24,6 +24,10 @@ SHAPES = [
 ]
 
 
+# of test_variant_scores_jump_and_sorted_keys
+JUMP_SHAPES = [(1, 2, 2, 2048, 2048), (1, 1, 1, 64, 512)]
+
+
 def _entry(name):
     return lambda *a: P.variant_attn_fwd(name, *a)
 
@@ -88,7 +92,7 @@ def test_variant_parity_small_shapes(name, causal):
 @pytest.mark.parametrize("name", sorted(B.VARIANTS))
 def test_variant_scores_jump_and_sorted_keys(name):
     """Maxima that keep rising: where the variants differ from each other."""
-    q, k, v = U.rand_qkv(1, 2, 2, 2048, 2048, seed=32)
+    q, k, v = U.rand_qkv(*JUMP_SHAPES[0], seed=32)
     k = k.float()
     k[:, 1024:] *= 40.0
     for causal in (False, True):
