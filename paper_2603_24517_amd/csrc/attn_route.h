@@ -436,7 +436,8 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
     // 1 x 1 x 32768 (134 MB) 36.1 / 34.5; 31.0 / 33.4; 14 x 1 x 4000 (229 MB) 44.1 / 40.6; 37.5 / 39.6; 16 x 1 x 4000 (262 MB) 48.8 / 44.8; 43.0 / 43.9; 4 x 1 x
     // 4096 (67 MB) 20.0 / 18.6; 17.3 / 16.9; 1 x 1 x 8192 (34 MB, six calls' K and V in turn fit the cache) 15.3 / 18.4.  On the null stream they go past the
     // caches from a quarter on: with no launch in front a repeated call takes no longer than it does on another stream with ordinary loads (33.8, 40.0, 45.3,
-    // 20.1).  On other streams it would take up to 2.6 us more than that.
+    // 20.1; of 150 calls measured one group was slower, 3600 keys, 236 MB, 4 K/V heads: repeated 44.6 / 40.4, from memory 43.0 / 50.8).  On other streams it would
+    // take up to 2.6 us more than that.
     const int64_t kv_bytes = (int64_t)B * Hkv * Skv * HD * 4;
     const bool read_once = split_ntile == 1 && sh.chunks == 1;
     const int split_blocks = (Skv + SPLIT_KEYS - 1) / SPLIT_KEYS;
@@ -471,20 +472,23 @@ inline void make_route(int B, int Hkv, int Skv, int causal, int ncu, Route &p)
             const double r1 = rows_us(p, ln, 1, ncu, bytes, cached), r2 = rows_us(p, ln, 2, ncu, bytes, cached);
             // How far ahead the smaller workgroups have to be estimated, so that calls are not slower there than in 256-row items, with K and V in the
             // last cache or from memory.  6 % (shared items: 10 to 15) were not enough: of 1020 measured calls that went there, 44 were more than 2 %
-            // slower one way or the other.  Of 646 others that the margins below send there from whole items, none was slower; from shared ones,
-            // whose margins were raised once more since, 3 of 45, at 17 % ahead.
+            // slower one way or the other.  Chosen on 5000 calls:
             // - Keys more than twice as long as the rows: each tile reads them again, and the two stages of items of 64 rows do not cover reads from
             //   memory, which the estimates do not know (us, 256 rows / smaller, from memory: 2 x 104 x 5599, 64 heads on 8 58.1 / 90.7; 4 x 35 x
             //   4426 48.6 / 74.7; 4 x 264 x 3506, 32 on 4 73.2 / 81.1; 20 x 269 x 2017, 12 on 3 80.9 / 86.6; 9 x 517 x 4612, 6 on 2 97.3 / 106.9).
             // - More rows than keys, masked: most rows have no key, which neither estimate knows well (4 x 1607 x 63, 16 heads 11.3 / 11.8).
-            // - From one and a half rounds of 256-row items on, these leave little idle: of 200 calls put 6 to 23 % ahead 27 were slower, up to 14 %
-            //   (22 x 391, 40 heads, masked 105.7 / 120.1); put 25 % ahead or more, none.
+            // - From one and a half rounds of 256-row items on, these leave little idle, and where each K/V head has one query head and at most three tiles
+            //   (768 rows) both ways are mostly memory: of 131 calls put 6 to 25 % ahead 33 were slower, up to 19 % (22 x 391, 40 heads, masked 105.7 /
+            //   120.1; 162 x 221, 4 heads 40.6 / 48.1), of 269 further ahead none.  Above nine rounds 22 of 118 others put 6 to 18 % ahead were slower, up to 6 %
+            //   (208 x 315, 12 on 3, masked 141 / 146; 57 x 694, 32 on 8 323 / 336), of 186 further ahead none.
+            // - Others are asked for 11 %: of 353 put 6 to 10 % ahead 6 were slower, up to 7 % (4 x 592 x 814, 32 on 4, masked 30.2 / 32.5), of 2439 further
+            //   ahead 5 (64 x 64, 32 on 8, no mask 20.4 / 22.4; the others by 1 to 4 %).
             // - Other calls of shared items against items of 64 rows: 21 % ahead, 2 x 2300, 4 heads 32.9 / 35.0; 1 x 3222, 16 heads 58.1 / 59.5.
             const bool far = Skv > 2 * (int64_t)Sq, is_shared = p.kind == ROUTE_SHARED;
             const int best = r1 < r2 || (far && is_shared) ? 1 : 2;
             const double now = is_shared ? shared_ns(p, total) * 1e-3 : rows256_us(p, ln, ncu, bytes);
             const double ahead = is_shared ? (far ? 0.78 : best == 2 ? 0.80 : now < 80 ? 1 / 1.10 : 1 / 1.15) : far || (causal && Sq > Skv) ? 0.70
-                                 : 2 * (int64_t)total > 3 * ncu ? 0.80 : 1 / 1.06;
+                                 : 2 * (int64_t)total > 3 * ncu && sh.pack == 1 && Sq <= 768 ? 0.80 : total > 9 * ncu ? 0.85 : 0.90;
             if ((best == 1 ? r1 : r2) < now * ahead) kgroups = best;
         }
         if (kgroups != 0) {

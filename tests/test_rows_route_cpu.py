@@ -53,7 +53,7 @@ def test_which_calls(rows, shape, causal, kgroups):
     ((2, 64, 8, 104, 5599), True), ((4, 64, 8, 35, 4426), False), ((2, 40, 40, 105, 5604), True), ((1, 40, 40, 293, 3978), False),     # shared
     ((9, 6, 2, 517, 4612), True), ((20, 12, 3, 269, 2017), True), ((2, 4, 4, 2300, 2300), True), ((1, 16, 16, 3222, 3222), True),             # shared
     ((20, 32, 8, 63, 6726), True), ((9, 40, 40, 148, 2876), True), ((4, 40, 40, 218, 2809), True), ((4, 32, 4, 264, 3506), True),       # far keys
-    ((22, 40, 40, 391, 391), True), ((91, 16, 16, 242, 242), False), ((59, 16, 16, 400, 400), True), ((162, 4, 4, 221, 221), False),    # many items
+    ((22, 40, 40, 391, 391), True), ((91, 16, 16, 242, 242), False), ((59, 16, 16, 400, 400), True), ((162, 4, 4, 221, 221), False), ((57, 32, 8, 694, 694), True),      # many items
     ((4, 16, 16, 1607, 63), True), ((4, 32, 4, 2481, 34), True),                                                                        # rows without keys
 ])
 def test_calls_that_smaller_workgroups_made_slower(rows, shape, causal):
