@@ -378,7 +378,8 @@ __device__ inline void pool_give(uint32_t u, int n)
 }
 
 // The forms of the 256-row kernel: with or without the causal mask, whole items or shared ones.  A negative scale is a wave-uniform
-// branch in the kernel of whole items, where an extreme score is looked for (once per item and where the reference is raised); with shared
+// branch in the kernel of whole items, where an extreme score is looked for (once per item and where the reference is raised; us, negative scale, a form
+// of its own / the branch: 8 x 4096, 16 heads 869.4 / 864.0, masked 494.1 / 490.1, 4 x 4096, 32 on 8, masked 468.2 / 468.1); with shared
 // ones, which have no register for it, Q is negated as it is loaded (in the kernel of whole items that costs 0.2 % of a causal launch).
 template <bool CAUSAL, bool SHARED>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(ATTN_WAVES_PER_SIMD, ATTN_WAVES_PER_SIMD)))
@@ -968,8 +969,8 @@ void attn_fwd_kernel(const Params p)
         }
         mfma_block(snxt, s0, s2, [&](int slot) __attribute__((always_inline)) {
             // element `slot` of the 32 scores of this lane: its exponent was formed one slot earlier, exp now, row-sum add one
-            // slot later, so that no instruction waits for the one in front of it (fma and exp in the same slot, us: 8 x 4096, 16
-            // heads 896 instead of 893, causal with peaked rows 522 instead of 518, 24 x 200, causal 25.8 instead of 25.3)
+            // slot later, so that no instruction waits for the one in front of it (fma and exp in the same slot, us, in turn: 8 x
+            // 4096, 16 heads 874.8 instead of 872.5, masked 494.4 instead of 488.4, 16 x 2048, masked 284.1 instead of 282.1: up to 1 %, little more than two runs differ)
             ev[slot] = __builtin_amdgcn_exp2f(slot == 0 ? __builtin_fmaf(scur[0][0], c, -mref) : arg);
             if (slot < 31) {
                 arg = __builtin_fmaf(scur[(slot + 1) >> 4][(slot + 1) & 15], c, -mref);
@@ -2062,12 +2063,13 @@ __global__ __launch_bounds__(NTHREADS) void attn_fwd_split_kernel(const SplitPar
 //
 // An item is 128 rows (KG = 1: each wavefront has 32 of them and all keys), or 64 (KG = 2: two pairs of wavefronts share the
 // rows' keys, every other block of 32 each, and add their results up through LDS at the end).  64 rows make twice as many items, each of half
-// as many turns, for twice the K/V traffic from L2 to LDS, which at 64 bytes per clock is what bounds them: 8 x 4096, 16 heads 963 us in items of 128
-// rows, 1242 in items of 64 (256-row kernel 890); 1 x 1111, 32 heads on 8, causal 21.4 and 17.7 (29.5).
+// as many turns, for twice the K/V traffic from L2 to LDS with half the stages to cover it: 8 x 4096, 16 heads 963 us in items of 128
+// rows, 1242 in items of 64 (256-row kernel 890), where counters show 21 and 29 bytes per clock and compute unit, a read from L2 under way for 142 and 489
+// clocks, wavefronts waiting 17 and 40 % of their time and the matrix pipe busy for 67 and 45 %; 1 x 1111, 32 heads on 8, causal 21.4 and 17.7 (29.5).
 //
 // A turn is 16 MFMAs per wavefront, as in the 256-row kernel: O += P(t-1) V(t-1) and S(t+1) = K(t+1) Q^T alternating, with the softmax of S(t)
-// between them, one exponent ahead.  A wavefront alone on its SIMD takes 890 cycles for one (512 of matrix pipe; 700 without the vector
-// instructions), two of them 1500 together.  K and V stages: four (KG = 1) or two (KG = 2) of each, 64 KiB, requested that many
+// between them, one exponent ahead.  By its own clock a wavefront alone on its SIMD takes 890 cycles for one (512 of matrix pipe; 700 without the vector
+// instructions), two of them 1500 together; whole launches against 8192 keys, start and memory included, 1090 and 1610 (KG = 1), 1600 and 1950 (KG = 2).  K and V stages: four (KG = 1) or two (KG = 2) of each, 64 KiB, requested that many
 // turns before use less one.
 struct RowsParams {
     const __bf16 *q, *k, *v;

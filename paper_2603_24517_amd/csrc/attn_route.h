@@ -7,8 +7,7 @@
 
 #include "../../include/attn.h"
 
-// ATTN_SMALL_PATH: which launches go to the split-key kernel for small problems (at the end of this
-// file): 1 (shipped) those whose 256-row work items would occupy at most a quarter of the compute
+// ATTN_SMALL_PATH: which launches go to the split-key kernel for small problems: 1 (shipped) those whose 256-row work items would occupy at most a quarter of the compute
 // units and those of few query rows; 0 none; 2 all.
 #ifndef ATTN_SMALL_PATH
 #define ATTN_SMALL_PATH 1
@@ -184,7 +183,8 @@ inline int whole_items_length(const Route &p, bool causal, int extra)
 
 // Workgroups that share one item of the split-key kernel, whose key sequence is `blocks` blocks of 32 keys.
 // One workgroup takes about 5 us + 1.3 us per 8 blocks as long as memory keeps up (measured, 8 items: 7.0 us at 16 blocks,
-// 15.0 at 64, 43 at 256, 189 at 1024); sharing an item adds about 4 us for the reserving launch and
+// 15.0 at 64, 43 at 256, 189 at 1024); sharing an item adds about 4 us for the launch in front (which the null stream does not
+// have; the number of parts, and with it a call's bits, is the same on every stream) and
 // 0.25 us per part to merge, so the sum is least at parts^2 = 0.65 blocks (measured, 8 items: 64 blocks 12.5 us
 // with 4 parts, 12.8 with 8; 256 blocks 17.4 with 8 or 16, 20.1 with 24; 1024 blocks 32.9 with 16, 36.2 with 32).
 // More workgroups than compute units start a second round: 160 items in two parts 26.5 us, in one 16.2.
@@ -230,8 +230,9 @@ inline int split_rounds(int64_t items, int blocks, int ncu)
 // 220 / 203; 512, 32768 x 32768 889 / 899; split-key: 64 items, 512 x 16384 234 / 140; 48, 700 x 20000 224 / 123; 64, 4096 x 4096 (not
 // causal) 60.7 / 49.7; 32, 200 x 8000 48.8 / 52.6; 8, 64 x 30000 57.3 / 87.9.
 //
-// Shared: the chip is full and at the clock that goes with it; 17 us for the launch in front and the parts, 1 us for each
-// part of an item beyond the second.
+// Shared: the chip is full and at the clock that goes with it; 17 us for the parts and the launch in front, 1 us for each
+// part of an item beyond the second.  (The null stream has no launch in front and takes 3 to 5 us less; one estimate for all streams, so that a call's bits
+// do not depend on its stream.)
 inline int64_t shared_ns(const Route &p, int64_t items)
 {
     const Share &sr = p.share;
