@@ -7,6 +7,7 @@ import torch
 
 import oracle
 import paper_2603_24517_amd as A
+from paper_2603_24517_amd import probe as P
 from paper_2603_24517_amd import workloads as W
 import gpu_util as U
 
@@ -119,11 +120,11 @@ def test_split_merge_gpu():
     assert np.abs(o - (w1 * o1 + w2 * o2)).max() <= 2e-2
 
 
-# (B, Hq, Hkv, Sq, Skv): one launch that goes to the split-key kernel (few rows) and one that goes to the 256-row kernel
-BOTH_KERNELS = [(2, 4, 2, 333, 333), (4, 16, 4, 1000, 1100)]
+# (B, Hq, Hkv, Sq, Skv): launches that go to the split-key kernel (few rows), to the one with workgroups of four wavefronts, and to the 256-row kernel
+EACH_KERNEL = [(2, 4, 2, 333, 333), (4, 16, 4, 1000, 1100), (27, 16, 16, 192, 192)]
 
 
-@pytest.mark.parametrize("shape", BOTH_KERNELS, ids=["split_key_kernel", "main_kernel"])
+@pytest.mark.parametrize("shape", EACH_KERNEL, ids=["split_key_kernel", "rows_kernel", "main_kernel"])
 def test_deterministic_and_stream_gpu(shape):
     q, k, v = U.rand_qkv(*shape, seed=26)
     o1, l1 = U.run_gpu(q, k, v, True, SCALE)
@@ -133,7 +134,7 @@ def test_deterministic_and_stream_gpu(shape):
     assert np.array_equal(o1, o2) and np.array_equal(l1, l2)
 
 
-@pytest.mark.parametrize("shape", [(2, 8, 2, 700, 900), (4, 16, 4, 1000, 1100)], ids=["split_key_kernel", "main_kernel"])
+@pytest.mark.parametrize("shape", [(2, 8, 2, 700, 900), *EACH_KERNEL[1:]], ids=["split_key_kernel", "rows_kernel", "main_kernel"])
 def test_launch_recorded_in_a_hip_graph_replays_identically(shape):
     """attn_fwd only enqueues one kernel or two, so (after one ordinary call on the device) it can be recorded
     into a HIP graph; every replay, with other work and synchronisations in between, must reproduce the
@@ -312,22 +313,28 @@ MANY_ITEMS = [
 ]
 
 
+@pytest.mark.parametrize("entry", [None, "whole_items"], ids=["shipped", "256_row_kernel"])
 @pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
 @pytest.mark.parametrize("shape", MANY_ITEMS, ids=lambda s: "x".join(map(str, s)))
-def test_many_items_per_workgroup(shape, causal):
+def test_many_items_per_workgroup(shape, causal, entry):
+    """(The shipped library sends half of these calls to other kernels, whose workgroups take one item each.)"""
+    fwd = None if entry is None else (lambda *a: P.variant_attn_fwd(entry, *a))
     B, Hq, Hkv, Sq, Skv = shape
     q, k, v = U.rand_qkv(B, Hq, Hkv, Sq, Skv, seed=7000 + hash(shape) % 1000)
-    print(f"case shape={shape} causal={causal}", flush=True)
-    U.check_full(q, k, v, causal, SCALE, what=f"{shape} causal={causal}")
+    print(f"case shape={shape} causal={causal} {entry}", flush=True)
+    U.check_full(q, k, v, causal, SCALE, what=f"{shape} causal={causal}", attn_fwd=fwd)
 
 
 def test_back_to_back_launches_of_different_shapes():
-    """LDS and registers carry nothing from one launch to the next: alternate two shapes, compare each time."""
+    """LDS and registers carry nothing from one launch to the next: alternate three shapes, one for each kernel, compare each time."""
     a = U.rand_qkv(6, 16, 16, 600, 600, seed=7101)
     b = U.rand_qkv(2, 8, 2, 333, 1000, seed=7102)
+    c = U.rand_qkv(*EACH_KERNEL[2], seed=7103)
     ref_a = oracle.attn_ref(*a, True, SCALE)
+    ref_c = oracle.attn_ref(*c, True, SCALE)
     ref_b = oracle.attn_ref(*b, False, SCALE)
     for n in range(3):
         print(f"round {n}", flush=True)
         U.compare(*U.run_gpu(*a, True, SCALE), *ref_a, what=f"A round {n}")
         U.compare(*U.run_gpu(*b, False, SCALE), *ref_b, what=f"B round {n}")
+        U.compare(*U.run_gpu(*c, True, SCALE), *ref_c, what=f"C round {n}")

@@ -192,3 +192,18 @@ def test_small_shapes_of_the_256_row_kernels_variants_reach_it(tmp_path, name):
     routes = [call(*shape[:5], causal) for shape in T.SHAPES + T.JUMP_SHAPES for causal in (False, True)]
     assert all(r["kind"] == WHOLE and r["kgroups"] == 0 for r in routes), routes
     assert any(r["items"] > r["wgs"] for r in routes)       # several items per workgroup
+
+
+def test_calls_that_stand_for_each_kernel_reach_it(tmp_path, route):
+    import test_attn_gpu as T
+    from paper_2603_24517_amd import build
+    import __graft_entry__ as G
+    for shapes in (T.EACH_KERNEL, G.SMOKE):
+        split, rows, main = (route(*s) for s in shapes)
+        assert split["kind"] == SPLIT and rows["kind"] == main["kind"] == WHOLE and rows["kgroups"] != 0 == main["kgroups"]
+        assert main["items"] > main["wgs"]
+    whole = _with_flags(tmp_path, build.VARIANTS["whole_items"])
+    for shape in T.MANY_ITEMS:
+        for causal in (False, True):
+            r = whole(*shape, causal)
+            assert r["kind"] == WHOLE and r["kgroups"] == 0 and r["items"] > 200, (shape, r)
